@@ -232,6 +232,14 @@ struct rbsog_ctx {
     int32_t *flag = nullptr;
     uint32_t *sys_done = nullptr;
     uint32_t *bin_done = nullptr;
+    // transfers: first non-finite particle of one (device), and pinned host
+    // memory: the status block that kernels write, then kPinBytes at most of
+    // staging for small transfers
+    int32_t *bad = nullptr;
+    IoStat *stat = nullptr;
+    char *pin = nullptr;
+    int64_t pin_bytes = 0;
+    int64_t builds_made = -1;  // list builds at the end of the latest call that evaluated (-1: read from the device)
     double *kin_part = nullptr;
     ListItem *list_items = nullptr;
     NearItem *near_items = nullptr;  // cell runs of the build-every-evaluation mode
@@ -823,9 +831,10 @@ rbsog_status apply_skin(rbsog_ctx *c, double skin) {
 rbsog_status adapt_skin(rbsog_ctx *c) {
     c->adapt_steps = 0;
     if (!(c->skin > 0.0)) return RBSOG_OK;
-    int64_t nb = 0;
-    HIPCHK(c, hipMemcpyAsync(&nb, c->nbuild, sizeof nb, hipMemcpyDeviceToHost, c->stream));
+    launch_status(make_args(c, false, 0.0), c->bad, c->stat, c->stream);
+    HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    const int64_t nb = c->stat->nbuild;
     const int64_t builds = nb - c->adapt_nb0;
     c->adapt_nb0 = nb;
     const bool busy = 2 * builds >= c->adapt_window;
@@ -916,14 +925,12 @@ rbsog_status size_list(rbsog_ctx *c, int64_t largest) {
 
 // After a call's evaluations: overflow fails it (the forces after it were
 // incomplete); a list close to full is grown for the next call.
-rbsog_status check_list(rbsog_ctx *c, int32_t flag) {
+rbsog_status check_list(rbsog_ctx *c, int32_t flag, int32_t pm) {
     if (flag & 8) {
         c->poisoned = true;
         return fail(c, RBSOG_E_STATE, "a home's near list exceeded its capacity of %lld pairs",
                     (long long)(c->icap / kListHomes));
     }
-    int32_t pm = 0;
-    HIPCHK(c, hipMemcpy(&pm, c->pmax, sizeof pm, hipMemcpyDeviceToHost));
     if (4 * (int64_t)pm > 3 * (c->icap / kListHomes)) TRY(size_list(c, pm));
     return RBSOG_OK;
 }
@@ -961,31 +968,60 @@ rbsog_status current_ids(rbsog_ctx *c, std::vector<int32_t> &id) {
     return RBSOG_OK;
 }
 
-// host n x 3 in caller order -> device SoA in the current cell order
-rbsog_status upload_by_id(rbsog_ctx *c, const double *host, double *dev, const char *what) {
-    std::vector<int32_t> id;
-    TRY(current_ids(c, id));
-    std::vector<double> soa((size_t)c->N * 3);
-    for (int64_t t = 0; t < c->N; ++t)
-        for (int d = 0; d < 3; ++d) {
-            const double v = host[3 * (int64_t)id[t] + d];
-            if (!std::isfinite(v)) return fail(c, RBSOG_E_NONFINITE, "%s of particle %d is not finite", what, id[t]);
-            soa[(size_t)d * c->N + t] = v;
+// A transfer up to this size goes through the context's pinned memory (the
+// runtime's path for pageable memory costs 25-100 us whatever the size: 24 kB
+// to the device 25 us against 13, 240 kB 106 against 17 and the copy); larger
+// ones go straight between the caller's array and the device.
+constexpr int64_t kPinBytes = 512 << 10;
+
+// One piece of a transfer to the host.
+struct Fetch {
+    const void *dev;
+    void *host;
+    int64_t bytes;
+};
+
+// The pieces to the host, after everything enqueued; waits for them.
+rbsog_status fetch(rbsog_ctx *c, std::initializer_list<Fetch> list) {
+    int64_t off = 0;
+    for (const Fetch &f : list) {
+        if (!f.bytes) continue;
+        const bool pin = off + f.bytes <= c->pin_bytes;
+        HIPCHK(c, hipMemcpyAsync(pin ? (void *)(c->pin + off) : f.host, f.dev, (size_t)f.bytes, hipMemcpyDeviceToHost,
+                                 c->stream));
+        if (pin) off += f.bytes;
+    }
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    off = 0;
+    for (const Fetch &f : list)
+        if (f.bytes && off + f.bytes <= c->pin_bytes) {
+            std::memcpy(f.host, c->pin + off, (size_t)f.bytes);
+            off += f.bytes;
         }
-    HIPCHK(c, hipMemcpy(dev, soa.data(), soa.size() * sizeof(double), hipMemcpyHostToDevice));
     return RBSOG_OK;
 }
 
-// device SoA in the current cell order -> host n x 3 in caller order
-rbsog_status download_by_id(rbsog_ctx *c, const double *dev, double *host) {
-    std::vector<int32_t> id;
-    TRY(current_ids(c, id));
-    std::vector<double> soa((size_t)c->N * 3);
-    HIPCHK(c, hipMemcpyAsync(soa.data(), dev, soa.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+// host n x 3 in caller order -> device SoA in the current cell order, through
+// the (idle) gather buffer; a non-finite entry leaves `dev` as it was.
+// `rebuild`: the next evaluation builds the near list.
+rbsog_status upload_by_id(rbsog_ctx *c, const double *host, double *dev, const char *what, bool rebuild) {
+    const int64_t bytes = 3 * c->N * (int64_t)sizeof(double);
+    double *rows = c->buf[1].x;
+    if (bytes <= c->pin_bytes) {
+        // the pinned memory is free: every call that uses it waits for its copies
+        std::memcpy(c->pin, host, (size_t)bytes);
+        HIPCHK(c, hipMemcpyAsync(rows, c->pin, (size_t)bytes, hipMemcpyHostToDevice, c->stream));
+    } else {
+        HIPCHK(c, hipMemcpyAsync(rows, host, (size_t)bytes, hipMemcpyHostToDevice, c->stream));
+    }
+    launch_rows_in(make_args(c, false, 0.0), rows, dev, c->bad, rebuild ? c->rebuild : nullptr, c->stat, c->stream);
+    HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    for (int64_t t = 0; t < c->N; ++t)
-        for (int d = 0; d < 3; ++d) host[3 * (int64_t)id[t] + d] = soa[(size_t)d * c->N + t];
-    return RBSOG_OK;
+    const int32_t bad = c->stat->bad;
+    if (bad == INT32_MAX) return RBSOG_OK;
+    const int32_t none = INT32_MAX;
+    HIPCHK(c, hipMemcpy(c->bad, &none, sizeof none, hipMemcpyHostToDevice));
+    return fail(c, RBSOG_E_NONFINITE, "%s of particle %d is not finite", what, bad);
 }
 
 // Split coefficients of the near kernel for one system.
@@ -1810,6 +1846,14 @@ rbsog_status init_batch(rbsog_ctx **out, int32_t nsys, const int64_t *offsets, c
     ALLOC(flag, 1);
     ALLOC(sys_done, nsys);
     ALLOC(bin_done, 1);
+    ALLOC(bad, 1);
+    c->pin_bytes = std::min<int64_t>(kPinBytes, std::max<int64_t>(4096, 48 * N + 32 * (int64_t)nsys));
+    if (hipHostMalloc((void **)&c->stat, 256 + (size_t)c->pin_bytes, hipHostMallocDefault) != hipSuccess) {
+        c->stat = nullptr;
+        fail(c, RBSOG_E_OOM, "pinned host memory");
+        return bail(RBSOG_E_OOM);
+    }
+    c->pin = (char *)c->stat + 256;
     ALLOC(kin_part, (int64_t)nsys * 2 * kKinBlocks);
     float4 *dtab = nullptr;
     if (o.near_table) {
@@ -1858,7 +1902,7 @@ rbsog_status init_batch(rbsog_ctx **out, int32_t nsys, const int64_t *offsets, c
         for (int32_t s = 0; s < nsys; ++s) sd[s] = sysdev_of(c->sys[s]);
         std::vector<int64_t> zc(nsys, 0);
         std::vector<uint32_t> zu(nsys, 0u);
-        const int32_t zf = 0;
+        const int32_t zf = 0, none = INT32_MAX;
         const StateBufs &b = c->buf[0];
         bool ok = hipMemcpy(b.x, soa.data(), soa.size() * sizeof(double), hipMemcpyHostToDevice) == hipSuccess &&
                   hipMemcpy(b.v, zero.data(), zero.size() * sizeof(double), hipMemcpyHostToDevice) == hipSuccess &&
@@ -1875,6 +1919,7 @@ rbsog_status init_batch(rbsog_ctx **out, int32_t nsys, const int64_t *offsets, c
                   hipMemcpy(c->tstep, zc.data(), sizeof(int64_t), hipMemcpyHostToDevice) == hipSuccess &&
                   hipMemcpy(c->sys_done, zu.data(), nsys * sizeof(uint32_t), hipMemcpyHostToDevice) == hipSuccess &&
                   hipMemset(c->bin_done, 0, sizeof(uint32_t)) == hipSuccess &&
+                  hipMemcpy(c->bad, &none, sizeof none, hipMemcpyHostToDevice) == hipSuccess &&
                   hipMemcpy(c->kin, std::vector<double>(nsys, 0.0).data(), nsys * sizeof(double),
                             hipMemcpyHostToDevice) == hipSuccess &&
                   hipMemcpy(c->nh_xi, std::vector<double>(nsys, 0.0).data(), nsys * sizeof(double),
@@ -2023,32 +2068,31 @@ static rbsog_status check_kseq(rbsog_ctx *c, int64_t evals) {
 rbsog_status rbsog_forces(rbsog_ctx *c, double *F_out, double *E_out) {
     TRY(check_ctx(c));
     TRY(check_kseq(c, 1));
+    c->builds_made = -1;
     TRY(refill_if_due(c));
     TRY(enqueue_eval(c, false, 0.0, true, true));
     account_eval(c);
-    {
-        int32_t flag = 0;
-        HIPCHK(c, hipMemcpyAsync(&flag, c->flag, sizeof flag, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        TRY(check_list(c, flag));
-        TRY(check_flag(c, flag));
+    const EvalArgs a = make_args(c, false, 0.0);
+    double *rows = c->buf[1].x;  // the gather buffer, idle between builds
+    if (F_out) launch_forces_out(a, rows, c->bad, c->stream);
+    launch_status(a, c->bad, c->stat, c->stream);
+    HIPCHK(c, hipGetLastError());
+    const int64_t fb = F_out ? 3 * c->N * (int64_t)sizeof(double) : 0;
+    const int64_t eb = E_out ? 4 * (int64_t)c->nsys * (int64_t)sizeof(double) : 0;
+    TRY(fetch(c, {{c->E, E_out, eb}, {rows, F_out, fb}}));
+    c->builds_made = c->stat->nbuild;
+    TRY(check_list(c, c->stat->flag, c->stat->pmax));
+    const int32_t bad = c->stat->bad;
+    if (bad != INT32_MAX) {
+        const int32_t none = INT32_MAX;
+        HIPCHK(c, hipMemcpy(c->bad, &none, sizeof none, hipMemcpyHostToDevice));
     }
-    if (F_out) {
-        std::vector<double> b((size_t)3 * c->N);
-        TRY(download_by_id(c, c->Fn, F_out));
-        TRY(download_by_id(c, c->Ff, b.data()));
-        for (size_t i = 0; i < b.size(); ++i) F_out[i] += b[i];
-        // without a kick no kernel looks at the sum of the two forces
-        for (size_t i = 0; i < b.size(); ++i)
-            if (!std::isfinite(F_out[i]))
-                return fail(c, RBSOG_E_NONFINITE, "force entry %lld is not finite", (long long)i);
-    }
-    if (E_out) {
-        HIPCHK(c, hipMemcpyAsync(E_out, c->E, 4 * (size_t)c->nsys * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
+    TRY(check_flag(c, c->stat->flag));
+    // without a kick no kernel of the evaluation looks at the sum of the two forces
+    if (bad != INT32_MAX) return fail(c, RBSOG_E_NONFINITE, "force on particle %d is not finite", bad);
+    if (E_out)
         for (int64_t i = 0; i < 4 * (int64_t)c->nsys; ++i)
             if (!std::isfinite(E_out[i])) return fail(c, RBSOG_E_NONFINITE, "energy entry %lld is not finite", (long long)i);
-    }
     return RBSOG_OK;
 }
 
@@ -2056,6 +2100,7 @@ rbsog_status rbsog_step(rbsog_ctx *c, int64_t n_steps, double dt) {
     TRY(check_ctx(c));
     if (n_steps < 0 || !std::isfinite(dt)) return fail(c, RBSOG_E_ARG, "need n_steps >= 0 and finite dt");
     TRY(check_kseq(c, n_steps + (c->forces_valid ? 0 : 1)));
+    c->builds_made = -1;
     if (!c->forces_valid) {
         TRY(refill_if_due(c));
         TRY(enqueue_eval(c, false, 0.0, true, true));
@@ -2112,40 +2157,34 @@ rbsog_status rbsog_step(rbsog_ctx *c, int64_t n_steps, double dt) {
         c->adapt_steps += chunk;
         if (c->adapt_steps >= c->adapt_window) TRY(adapt_skin(c));
     }
-    int32_t flag = 0;
-    HIPCHK(c, hipMemcpyAsync(&flag, c->flag, sizeof flag, hipMemcpyDeviceToHost, c->stream));
+    launch_status(make_args(c, false, 0.0), c->bad, c->stat, c->stream);
+    HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    const int32_t flag = c->stat->flag;
+    c->builds_made = c->stat->nbuild;
     if ((flag & 3) && (flag & 8)) {
         // particles that went non-finite pile into cell 0 and overflow the
         // list: the cause is reported, the list is beyond repair
         c->poisoned = true;
         return fail(c, RBSOG_E_NONFINITE, "non-finite force or energy, and the near list overflowed (flag %d)", flag);
     }
-    TRY(check_list(c, flag));
+    TRY(check_list(c, flag, c->stat->pmax));
     return check_flag(c, flag);
 }
 
-// Kinetic energy of every system from velocities given in the caller's order
-// (n x 3), summed in particle order, uploaded as the systems' current values.
-static rbsog_status upload_kinetic(rbsog_ctx *c, const double *v) {
-    std::vector<double> K((size_t)c->nsys, 0.0);
-    for (int32_t s = 0; s < c->nsys; ++s) {
-        const SysHost &h = c->sys[s];
-        double acc = 0.0;
-        for (int64_t i = h.p0; i < h.p0 + h.n; ++i)
-            acc += (v[3 * i] * v[3 * i] + v[3 * i + 1] * v[3 * i + 1]) + v[3 * i + 2] * v[3 * i + 2];
-        K[s] = 0.5 * c->mass * acc;
-    }
-    HIPCHK(c, hipMemcpy(c->kin, K.data(), K.size() * sizeof(double), hipMemcpyHostToDevice));
+// Kinetic energy of every system from the velocities as they stand (summed on
+// the device in slot order, a fixed order).
+static rbsog_status kinetic_now(rbsog_ctx *c) {
+    launch_kinetic_now(make_args(c, false, 0.0), c->far_items, c->n_far, c->tune.far_block, c->stream);
+    HIPCHK(c, hipGetLastError());
     return RBSOG_OK;
 }
 
 rbsog_status rbsog_set_velocities(rbsog_ctx *c, const double *v, double T, uint64_t seed) {
     TRY(check_ctx(c));
     if (v) {
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        TRY(upload_by_id(c, v, c->buf[0].v, "velocity"));
-        return upload_kinetic(c, v);
+        TRY(upload_by_id(c, v, c->buf[0].v, "velocity", false));
+        return kinetic_now(c);
     }
     if (!(T >= 0.0) || !std::isfinite(T)) return fail(c, RBSOG_E_ARG, "temperature must be >= 0");
     const double sd = std::sqrt(T / c->mass);
@@ -2165,9 +2204,8 @@ rbsog_status rbsog_set_velocities(rbsog_ctx *c, const double *v, double T, uint6
             for (int64_t i = h.p0; i < h.p0 + h.n; ++i) vv[3 * i + d] -= mean[d];
         }
     }
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    TRY(upload_by_id(c, vv.data(), c->buf[0].v, "velocity"));
-    return upload_kinetic(c, vv.data());
+    TRY(upload_by_id(c, vv.data(), c->buf[0].v, "velocity", false));
+    return kinetic_now(c);
 }
 
 rbsog_status rbsog_set_thermostat(rbsog_ctx *c, double gamma, double T, uint64_t seed) {
@@ -2203,9 +2241,7 @@ rbsog_status rbsog_set_nose_hoover(rbsog_ctx *c, double T, double tau) {
     HIPCHK(c, hipMemcpy(c->nh_xi, zero.data(), zero.size() * sizeof(double), hipMemcpyHostToDevice));
     if (c->nh_on) {
         c->gamma = 0.0;  // one thermostat at a time
-        std::vector<double> v((size_t)3 * c->N);
-        TRY(download_by_id(c, c->buf[0].v, v.data()));
-        TRY(upload_kinetic(c, v.data()));
+        TRY(kinetic_now(c));
     }
     drop_graphs(c);  // the graphs hold the step's constants
     return RBSOG_OK;
@@ -2213,10 +2249,8 @@ rbsog_status rbsog_set_nose_hoover(rbsog_ctx *c, double T, double tau) {
 
 rbsog_status rbsog_get_kinetic(rbsog_ctx *c, double *K, double *xi) {
     TRY(check_ctx(c));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    if (K) HIPCHK(c, hipMemcpy(K, c->kin, (size_t)c->nsys * sizeof(double), hipMemcpyDeviceToHost));
-    if (xi) HIPCHK(c, hipMemcpy(xi, c->nh_xi, (size_t)c->nsys * sizeof(double), hipMemcpyDeviceToHost));
-    return RBSOG_OK;
+    const int64_t bytes = (int64_t)c->nsys * (int64_t)sizeof(double);
+    return fetch(c, {{c->kin, K, K ? bytes : 0}, {c->nh_xi, xi, xi ? bytes : 0}});
 }
 
 rbsog_status rbsog_set_msd_origin(rbsog_ctx *c) {
@@ -2245,35 +2279,35 @@ rbsog_status rbsog_get_msd(rbsog_ctx *c, double *msd) {
 rbsog_status rbsog_set_positions(rbsog_ctx *c, const double *pos) {
     TRY(check_ctx(c));
     if (!pos) return fail(c, RBSOG_E_ARG, "pos is null");
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    TRY(upload_by_id(c, pos, c->buf[0].x, "position"));
-    HIPCHK(c, hipMemset(c->buf[0].dsp, 0, (size_t)3 * c->N * sizeof(double)));  // a new origin
+    TRY(upload_by_id(c, pos, c->buf[0].x, "position", true));
+    // a new origin (displacements not tracked yet start with rbsog_set_msd_origin)
+    if (c->msd_on) HIPCHK(c, hipMemsetAsync(c->buf[0].dsp, 0, (size_t)3 * c->N * sizeof(double), c->stream));
     c->forces_valid = false;
-    return request_build(c);
+    return RBSOG_OK;
+}
+
+// Two arrays of the state (either may be null) in the caller's order, through
+// the gather buffers.
+static rbsog_status rows_to_host(rbsog_ctx *c, const double *src0, double *host0, bool wrap0, const double *src1,
+                                 double *host1) {
+    const EvalArgs a = make_args(c, false, 0.0);
+    if (host0) launch_rows_out(a, src0, c->buf[1].x, wrap0, c->stream);
+    if (host1) launch_rows_out(a, src1, c->buf[1].v, false, c->stream);
+    HIPCHK(c, hipGetLastError());
+    const int64_t bytes = 3 * c->N * (int64_t)sizeof(double);
+    return fetch(c, {{c->buf[1].x, host0, host0 ? bytes : 0}, {c->buf[1].v, host1, host1 ? bytes : 0}});
 }
 
 rbsog_status rbsog_get_state(rbsog_ctx *c, double *pos, double *vel) {
     TRY(check_ctx(c));
-    if (pos) {
-        TRY(download_by_id(c, c->buf[0].x, pos));
-        // the stored coordinates are wrapped at each evaluation; wrap here too
-        for (const SysHost &h : c->sys)
-            for (int64_t i = h.p0; i < h.p0 + h.n; ++i)
-                for (int d = 0; d < 3; ++d) {
-                    const double t = pos[3 * i + d] / h.box[d];
-                    pos[3 * i + d] = (t - std::floor(t)) * h.box[d];
-                }
-    }
-    if (vel) TRY(download_by_id(c, c->buf[0].v, vel));
-    return RBSOG_OK;
+    // the stored coordinates are wrapped at each evaluation; wrapped here too
+    return rows_to_host(c, c->buf[0].x, pos, true, c->buf[0].v, vel);
 }
 
 rbsog_status rbsog_get_forces(rbsog_ctx *c, double *F_near, double *F_far) {
     TRY(check_ctx(c));
     if (c->evals == 0) return fail(c, RBSOG_E_STATE, "no force evaluation yet");
-    if (F_near) TRY(download_by_id(c, c->Fn, F_near));
-    if (F_far) TRY(download_by_id(c, c->Ff, F_far));
-    return RBSOG_OK;
+    return rows_to_host(c, c->Fn, F_near, false, c->Ff, F_far);
 }
 
 rbsog_status rbsog_get_forces_subset(rbsog_ctx *c, int64_t m, const int64_t *ids, double *F_near, double *F_far) {
@@ -2317,9 +2351,7 @@ rbsog_status rbsog_get_energy(rbsog_ctx *c, double *E) {
     TRY(check_ctx(c));
     if (c->evals == 0) return fail(c, RBSOG_E_STATE, "no force evaluation yet");
     if (!E) return fail(c, RBSOG_E_ARG, "E is null");
-    HIPCHK(c, hipMemcpyAsync(E, c->E, 4 * (size_t)c->nsys * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    return RBSOG_OK;
+    return fetch(c, {{c->E, E, 4 * (int64_t)c->nsys * (int64_t)sizeof(double)}});
 }
 
 rbsog_status rbsog_get_rho(rbsog_ctx *c, int32_t sys, double *re, double *im) {
@@ -2365,8 +2397,12 @@ rbsog_status rbsog_info(rbsog_ctx *c, int32_t sys, rbsog_info_t *info) {
     info->n_sys = c->nsys;
     info->list_capacity = c->icap;
     info->skin = c->skin_cur;
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    HIPCHK(c, hipMemcpy(&info->list_builds, c->nbuild, sizeof(int64_t), hipMemcpyDeviceToHost));
+    if (c->builds_made >= 0) {
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        info->list_builds = c->builds_made;
+    } else {
+        TRY(fetch(c, {{c->nbuild, &info->list_builds, (int64_t)sizeof(int64_t)}}));
+    }
     info->rho_chunk = c->tune.rho_chunk;
     info->far_block = c->tune.far_block;
     for (const SysHost &h : c->sys) info->rho_ktile = std::max(info->rho_ktile, h.kt);
@@ -2809,6 +2845,7 @@ rbsog_status rbsog_load_state(rbsog_ctx *c, const void *buf, int64_t len) {
         if (!c->lambda) TRY(upload_k(c, s, 0));
         TRY(upload_sysdev(c, s));
     }
+    c->builds_made = -1;
     for (const auto &a : device_state(c)) {
         if (r.pos + a.second > len) return fail(c, RBSOG_E_ARG, "truncated state");
         HIPCHK(c, hipMemcpy(a.first, r.buf + r.pos, (size_t)a.second, hipMemcpyHostToDevice));
@@ -2877,6 +2914,7 @@ void rbsog_destroy(rbsog_ctx *c) {
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     drop_graphs(c);
     for (void *p : c->allocs) (void)hipFree(p);
+    if (c->stat) (void)hipHostFree(c->stat);
     if (c->side) {
         (void)hipStreamSynchronize(c->side);
         (void)hipStreamDestroy(c->side);

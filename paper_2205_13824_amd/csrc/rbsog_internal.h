@@ -343,6 +343,29 @@ constexpr int32_t kKinBlocks = 64;
 void launch_refill(const SampDev *samp, int32_t nsys, int32_t lambda, ChainState *chains, int64_t *kcur,
                    int32_t *flag, hipStream_t s);
 
+// ---- transfers in the caller's order (kernels_io.hip) ------------------------
+// What a call reports to the host, in pinned memory that kernels write.
+struct IoStat {
+    int32_t bad;   // smallest particle index with a non-finite entry, or INT32_MAX
+    int32_t flag;  // EvalArgs::flag
+    int32_t pmax;  // EvalArgs::pmax
+    int32_t pad;
+    int64_t nbuild;  // EvalArgs::nbuild
+};
+// rows (n x 3, caller order) checked for finite entries (the smallest bad
+// index to *bad) and, if all are, put into the slots dst of the current order
+// (*rebuild set, if given); the verdict to st
+void launch_rows_in(const EvalArgs &a, const double *rows, double *dst, int32_t *bad, int32_t *rebuild, IoStat *st,
+                    hipStream_t s);
+// slots src into rows (positions with `wrap`)
+void launch_rows_out(const EvalArgs &a, const double *src, double *rows, bool wrap, hipStream_t s);
+// F_N + F* into rows, the smallest index of a non-finite force to *bad
+void launch_forces_out(const EvalArgs &a, double *rows, int32_t *bad, hipStream_t s);
+// the error flags, the largest list count, the builds made and *bad to st
+void launch_status(const EvalArgs &a, const int32_t *bad, IoStat *st, hipStream_t s);
+// kinetic energy of every system from the velocities as they stand
+void launch_kinetic_now(const EvalArgs &a, const FarItem *items, int32_t nitems, int32_t block_size, hipStream_t s);
+
 // ---- kernel launchers (kernels_md.hip) --------------------------------------
 void launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 // kick dt/2 + drift (if a.kick), wrap, quantise, displacement check against

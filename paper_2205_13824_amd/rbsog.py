@@ -226,8 +226,8 @@ def n_systems(ctx) -> int:
 
 
 def rbsog_forces(ctx, n: int, want_forces: bool = True, want_energy: bool = True):
-    F = np.zeros((n, 3)) if want_forces else None
-    E = np.zeros(4 * n_systems(ctx)) if want_energy else None
+    F = np.empty((n, 3)) if want_forces else None
+    E = np.empty(4 * n_systems(ctx)) if want_energy else None
     _check(lib().rbsog_forces(ctx, _ptr(F), _ptr(E)), ctx)
     return F, E
 
@@ -250,15 +250,15 @@ def rbsog_set_positions(ctx, pos):
 
 
 def rbsog_get_state(ctx, n: int):
-    pos = np.zeros((n, 3))
-    vel = np.zeros((n, 3))
+    pos = np.empty((n, 3))
+    vel = np.empty((n, 3))
     _check(lib().rbsog_get_state(ctx, _ptr(pos), _ptr(vel)), ctx)
     return pos, vel
 
 
 def rbsog_get_forces(ctx, n: int):
-    Fn = np.zeros((n, 3))
-    Ff = np.zeros((n, 3))
+    Fn = np.empty((n, 3))
+    Ff = np.empty((n, 3))
     _check(lib().rbsog_get_forces(ctx, _ptr(Fn), _ptr(Ff)), ctx)
     return Fn, Ff
 
