@@ -368,14 +368,15 @@ rbsog_status rbsog_debug_neighbors(rbsog_ctx *ctx, int32_t sys, int64_t *row_ptr
  *   precision  RBSOG_FP64: FP64 fractional coordinates, FP64 sin/cos of the
  *              phase m.s - rint(m.s), FP64 sums; RBSOG_FP32C: the phase
  *              m.u mod 2^32 on the 32-bit fixed-point coordinates of the
- *              rule above, hardware FP32 sin/cos, FP32 sums over runs of 32
- *              particles added in FP64
+ *              rule above, hardware FP32 sin/cos (two particles of equal
+ *              charge through the half sum and half difference of their
+ *              phases), FP32 sums over runs of 32 particles added in FP64
  *   rho_re, rho_im  device, n_k doubles each, written
  *   stream     hipStream_t to launch on (NULL: the null stream)
  * Asynchronous on `stream`; the result is deterministic (partial sums over
  * particle chunks, added in a fixed order).  Non-finite positions or charges
  * give unspecified values.  The partial sums live in device memory allocated
- * and freed on `stream` for the call.  E_ARG for sizes out of range or a null
+ * and freed on `stream` for the call (none for calls of one chunk).  E_ARG for sizes out of range or a null
  * pointer, E_OOM if the partial sums cannot be allocated, E_DEVICE if a launch
  * fails; the message is at rbsog_last_error(NULL). */
 rbsog_status rbsog_structure_factor(int64_t n, const double *x, const double *q, const double *box, int64_t n_k,

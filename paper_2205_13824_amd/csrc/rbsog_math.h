@@ -140,7 +140,15 @@ __device__ __forceinline__ uint32_t dot3_mod32_s(uint32_t ax, uint32_t ay, uint3
     asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(r), "=s"(c2) : "s"(ax), "v"(bx), "v"(q));
     return (uint32_t)r;
 }
-// c + a.b mod 2^32 for c the low half of the 64-bit addend `c` (its high half
+__device__ __forceinline__ uint32_t dot3_add_mod32_v(uint32_t ax, uint32_t ay, uint32_t az, uint32_t bx, uint32_t by,
+                                                     uint32_t bz, uint64_t c) {
+    uint64_t p, q, r, c0, c1, c2;
+    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(p), "=s"(c0) : "v"(az), "v"(bz), "v"(c));
+    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(q), "=s"(c1) : "v"(ay), "v"(by), "v"(p));
+    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(r), "=s"(c2) : "v"(ax), "v"(bx), "v"(q));
+    return (uint32_t)r;
+}
+// (above and below) c + a.b mod 2^32 for c the low half of the 64-bit addend `c` (its high half
 // is not read into the low half of any product): the same chain with c in
 // place of the constant 0, so a phase offset costs no instruction.  The
 // first factor from scalar registers, the addend from vector registers (one
@@ -191,8 +199,11 @@ __device__ __forceinline__ double exp_nonpos(double y) {
 // (truncation below x^7/5040 < 6e-22 and x^6/720 < 1.2e-18 at |x| <= pi/1024,
 // well under an FP64 ulp of sin x and cos x), then the angle sum with entry
 // j mod kTurnTab.  Callers scale their positions by kTurnTab (a power of 2,
-// so u is exactly kTurnTab times the phase they would form in turns).
+// so u is exactly kTurnTab times the phase they would form in turns).  WIDE
+// takes |u| < 2^51 (else |u| < 2^31): the rounding by adding and subtracting
+// 1.5 2^52, whose sum holds j in its low bits.
 constexpr int kTurnTab = 1024;
+template <bool WIDE = false>
 __device__ __forceinline__ void sincos2pi_tab(double u, const double2 *tab, double *s, double *c) {
     constexpr double T = kTwoPi / kTurnTab;
     constexpr double T2 = T * T;
@@ -200,9 +211,19 @@ __device__ __forceinline__ void sincos2pi_tab(double u, const double2 *tab, doub
     constexpr double S2 = -S1 * T2 / 20.0;
     constexpr double C1 = -T2 / 2.0;
     constexpr double C2 = -C1 * T2 / 12.0;
-    const double jd = rint(u);
+    double jd;
+    int j;
+    if constexpr (WIDE) {
+        constexpr double kRound = 6755399441055744.0;  // 1.5 2^52
+        const double v = u + kRound;
+        jd = v - kRound;
+        j = __double2loint(v);
+    } else {
+        jd = rint(u);
+        j = (int)jd;
+    }
     const double r = u - jd;
-    const double2 e = tab[(int)jd & (kTurnTab - 1)];
+    const double2 e = tab[j & (kTurnTab - 1)];
     const double z = r * r;
     const double sr = r * fma(z, fma(z, S2, S1), T);
     const double cr = fma(z, fma(z, C2, C1), 1.0);
