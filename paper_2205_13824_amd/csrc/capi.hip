@@ -14,6 +14,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "rbsog_internal.h"
@@ -193,6 +194,7 @@ struct rbsog_ctx {
     uint32_t *pairs = nullptr;
     int32_t *pcnt = nullptr, *rebuild = nullptr, *pmax = nullptr;
     int64_t icap = 0;
+    int32_t near_form = kFormExp;  // pair kernel of the list pass
     bool list_hm = false;  // home-major blocks (lists longer than kHomeMajorMin at sizing)
     int64_t *nbuild = nullptr;
     int32_t build_slots = 2;  // candidates per lane and test pass of the build
@@ -603,6 +605,7 @@ EvalArgs make_args(rbsog_ctx *c, bool stepping, double dt) {
     a.pcnt = c->pcnt;
     a.icap = c->icap;
     a.list_hm = c->list_hm ? 1 : 0;
+    a.near_form = c->near_form;
     a.pmax = c->pmax;
     a.nbuild = c->nbuild;
     a.Fn = c->Fn;
@@ -1024,6 +1027,68 @@ rbsog_status upload_by_id(rbsog_ctx *c, const double *host, double *dev, const c
     return fail(c, RBSOG_E_NONFINITE, "%s of particle %d is not finite", what, bad);
 }
 
+// The whole sum of Gaussians and its force weights as polynomials of y = 2 x /
+// r_c^2 - 1 over x in [0, r_c^2]: Chebyshev interpolation at kChebNodes nodes,
+// cut at each form's degree, in powers of y.  A form whose cut exceeds its
+// tolerance of the sum at x = 0 (its largest value) does not hold.
+constexpr int kChebNodes = 40;
+template <class Co>
+bool poly_form(const long double *c, double tol, Co &co, int which) {
+    constexpr int NP = sizeof(co.gp) / sizeof(co.gp[0]);
+    using R = std::remove_reference_t<decltype(co.ys)>;
+    long double cut = 0.0L, top = 0.0L;
+    for (int n = 0; n < kChebNodes; ++n) {
+        top += std::fabs(c[n]);
+        if (n >= NP) cut += std::fabs(c[n]);
+    }
+    // T_n in powers of y, by T_{n+1} = 2 y T_n - T_{n-1}
+    long double t0[NP + 1] = {1.0L}, t1[NP + 1] = {0.0L, 1.0L}, p[NP] = {};
+    for (int n = 0; n < NP; ++n) {
+        for (int k = 0; k < NP; ++k) p[k] += c[n] * t0[k];
+        long double t2[NP + 1];
+        for (int k = 0; k <= NP; ++k) t2[k] = (k ? 2.0L * t1[k - 1] : 0.0L) - t0[k];
+        std::copy(t1, t1 + NP + 1, t0);
+        std::copy(t2, t2 + NP + 1, t1);
+    }
+    for (int k = 0; k < NP; ++k) (which ? co.pp : co.gp)[k] = (R)p[k];
+    return cut <= tol * top;
+}
+
+void build_poly(SysHost &h) {
+    constexpr int NN = kChebNodes;
+    // cos(pi k / (2 NN)), k < 4 NN: the nodes and every T_n at them
+    static const std::vector<long double> cosine = [] {
+        std::vector<long double> t(4 * NN);
+        for (int k = 0; k < 4 * NN; ++k) t[k] = std::cos(3.141592653589793238462643383279502884L * k / (2 * NN));
+        return t;
+    }();
+    const double rc2 = h.rc * h.rc;
+    long double f[2][NN] = {};
+    for (int j = 0; j < NN; ++j) {
+        const long double x = 0.5L * rc2 * (1.0L + cosine[2 * j + 1]);
+        for (size_t l = 0; l < h.s.size(); ++l) {
+            const long double a = 1.0L / ((long double)h.s[l] * h.s[l]);
+            const long double e = h.omega[l] * std::exp((double)(-x * a));
+            f[0][j] += 2.0L * a * e;
+            f[1][j] += e;
+        }
+    }
+    bool ok64 = true, ok32 = true;
+    for (int which = 0; which < 2; ++which) {
+        long double c[NN] = {};
+        for (int n = 0; n < NN; ++n) {
+            for (int j = 0; j < NN; ++j) c[n] += f[which][j] * cosine[n * (2 * j + 1) % (4 * NN)];
+            c[n] *= (n ? 2.0L : 1.0L) / NN;
+        }
+        ok64 = poly_form(c, kPolyTol64, h.co64, which) && ok64;
+        ok32 = poly_form(c, kPolyTol32, h.co32, which) && ok32;
+    }
+    h.co64.poly = ok64 ? 1 : 0;
+    h.co32.poly = ok32 ? 1 : 0;
+    h.co64.ys = 2.0 / rc2;
+    h.co32.ys = (float)(2.0 / rc2);
+}
+
 // Split coefficients of the near kernel for one system.
 void build_split(SysHost &h, int nexp64, int nexp32) {
     // explicit Gaussians and the tail polynomials:
@@ -1069,6 +1134,7 @@ void build_split(SysHost &h, int nexp64, int nexp32) {
         h.co32.pt[k] = (float)pf.first;
         h.co32.ft[k] = (float)pf.second;
     }
+    build_poly(h);
 }
 
 // Cell grid and near-list thresholds of one system for a skin.  skin > 0:
@@ -1088,6 +1154,7 @@ void set_geometry(SysHost &h, double skin) {
     }
     const double rl = h.rc * (1.0 + skin);
     g.rl2_f = (float)(rl * rl * (1.0 + 1e-4) + 1e-30);
+    g.dlist = h.rc * (1.0 + 2.0 * skin) * (1.0 + 1e-3);
     const double dmax = 0.5 * skin * h.rc;
     g.dthr2_f = skin > 0.0 ? (float)(dmax * dmax * (1.0 - 1e-4)) : -1.0f;
     h.ncell = (int64_t)g.nc[0] * g.nc[1] * g.nc[2];
@@ -1752,6 +1819,9 @@ rbsog_status init_batch(rbsog_ctx **out, int32_t nsys, const int64_t *offsets, c
         }
         c->K += P[s];
     }
+    c->near_form = o.near_table ? kFormTable : kFormPoly;
+    for (const SysHost &h : c->sys)
+        if (!o.near_table && !(c->prec == RBSOG_FP64 ? h.co64.poly : h.co32.poly)) c->near_form = kFormExp;
     c->N = offsets[nsys];
     c->q_host.assign(q, q + c->N);
     set_slots(c);
@@ -1811,8 +1881,11 @@ rbsog_status init_batch(rbsog_ctx **out, int32_t nsys, const int64_t *offsets, c
     ALLOC(ksys, K);
     ALLOC(u_tmp, 3 * N);
     ALLOC(u, 3 * N);
-    ALLOC(pk, N);
-    if (c->prec == RBSOG_FP64) ALLOC(pkx, N);
+    if (c->prec == RBSOG_FP64) {
+        ALLOC(pkx, N);
+    } else {
+        ALLOC(pk, N);
+    }
     if (c->prec != RBSOG_FP64) {
         ALLOC(rs_u, 3 * N);
         ALLOC(rs_qf, N);

@@ -292,6 +292,7 @@ __device__ __forceinline__ Geom load_geom(CSys *sp) {
     g.band_hi = sp->g.band_hi;
     g.band_lo_f = sp->g.band_lo_f;
     g.band_hi_f = sp->g.band_hi_f;
+    g.dlist = sp->g.dlist;
     g.rl2_f = sp->g.rl2_f;
     g.dthr2_f = sp->g.dthr2_f;
     return g;
@@ -360,26 +361,6 @@ struct PairData {
     typename std::conditional<F64, double, float>::type q;
     double x[3];
 };
-
-// The candidate's data from its gather records, given the list entry (the
-// byte offset 16 j of candidate slot j's record): one 16-byte load (and one
-// 32-byte record in the FP64 form).
-template <bool F64>
-__device__ __forceinline__ PairData<F64> load_packed(const uint4 *__restrict__ pk, const PosQ64 *__restrict__ pkx,
-                                                     uint32_t off) {
-    PairData<F64> d;
-    // slots below 2^28: 32-bit byte offsets from the arrays' (scalar) bases
-    const uint4 r = *(const uint4 *)((const char *)pk + off);
-    d.u[0] = r.x; d.u[1] = r.y; d.u[2] = r.z;
-    if constexpr (F64) {
-        const PosQ64 w = *(const PosQ64 *)((const char *)pkx + (off << 1));
-        d.x[0] = w.x; d.x[1] = w.y; d.x[2] = w.z;
-        d.q = w.q;
-    } else {
-        d.q = __uint_as_float(r.w);
-    }
-    return d;
-}
 
 template <bool F64>
 __device__ __forceinline__ PairData<F64> load_pair(const uint32_t *__restrict__ su, const double *__restrict__ sx,
@@ -623,7 +604,7 @@ __device__ __forceinline__ void copy_back(const EvalArgs &a, int64_t i0, int64_t
         a.cur.q[i] = a.nxt.q[i];
         a.cur.qf[i] = a.nxt.qf[i];
         a.cur.id[i] = a.nxt.id[i];
-        a.pk[i] = make_uint4(a.u[i], a.u[n + i], a.u[2 * n + i], __float_as_uint(a.nxt.qf[i]));
+        if (a.pk) a.pk[i] = make_uint4(a.u[i], a.u[n + i], a.u[2 * n + i], __float_as_uint(a.nxt.qf[i]));
         if (a.pkx) a.pkx[i] = PosQ64{a.nxt.x[i], a.nxt.x[n + i], a.nxt.x[2 * n + i], a.nxt.q[i]};
     }
 }
@@ -935,13 +916,265 @@ __global__ __launch_bounds__(64 * kNW) void k_list_build(EvalArgs a, const ListI
     }
 }
 
+// ---- list pass ---------------------------------------------------------------
+
+// Constants of the pair kernel, loaded once per block and kept in scalar
+// registers through the list loop (read where used, they cost the loop a
+// scalar load and its wait per pair).
+template <bool F64, int FORM, bool WE>
+struct PairConst {
+    using R = typename std::conditional<F64, double, float>::type;
+    static constexpr int NP = (F64 ? kPolyDeg64 : kPolyDeg32) + 1;
+    R ys, gp[FORM == kFormPoly ? NP : 1], pp[FORM == kFormPoly && WE ? NP : 1];
+    __device__ __forceinline__ void load(typename CoefOf<F64>::type *co) {
+        if constexpr (FORM == kFormPoly) {
+            ys = co->ys;
+            asm volatile("" : "+s"(ys));
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                gp[k] = co->gp[k];
+                asm volatile("" : "+s"(gp[k]));
+                if constexpr (WE) {
+                    pp[k] = co->pp[k];
+                    asm volatile("" : "+s"(pp[k]));
+                }
+            }
+        }
+    }
+};
+
+// 1/sqrt(x) in FP64 for finite x > 0: the hardware estimate (about 2^-23)
+// and one step of third order, y (1 + e/2 + 3 e^2/8) with e = 1 - x y^2.
+__device__ __forceinline__ double rsqrt64(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// Force coefficient 1/r^3 - 2 sum_l omega_l/s_l^2 e^{-r^2/s_l^2} and (WE)
+// potential 1/r - sum_l omega_l e^{-r^2/s_l^2} at x = r^2.
+template <bool F64, int FORM, bool WE, typename R>
+__device__ __forceinline__ void pair_kernel(const PairConst<F64, FORM, WE> &pc, typename CoefOf<F64>::type *co,
+                                            const float4 *__restrict__ tbl, float rin2, CSys *csp, R x, R &gk, R &hk) {
+    auto f = [](R a, R b, R c) {
+        if constexpr (F64) return fma(a, b, c);
+        else return fmaf(a, b, c);
+    };
+    hk = 0;
+    if constexpr (FORM == kFormTable) {
+        if (x >= rin2) {
+            // shell: table point from the FP32 bits of r^2, linear in r^2
+            const uint32_t bits = __float_as_uint(x);
+            const float4 tv = tbl[(bits >> (23 - kTabBman)) & (kTabSize - 1)];
+            const float fr = (float)(bits & ((1u << (23 - kTabBman)) - 1u)) * (1.0f / (1 << (23 - kTabBman)));
+            gk = fmaf(fr, tv.y, tv.x);
+            hk = fmaf(fr, tv.w, tv.z);
+        } else {
+            // core: Taylor terms of the Gaussians, 1/r and 1/r^3 computed
+            const float ri = __builtin_amdgcn_rsqf(x);
+            float pa = csp->ta[kTabQ - 1], pb = csp->tb[kTabQ - 1];
+#pragma unroll
+            for (int t = kTabQ - 2; t >= 0; --t) pa = fmaf(pa, x, csp->ta[t]);
+            if constexpr (WE) {
+#pragma unroll
+                for (int t = kTabQ - 2; t >= 0; --t) pb = fmaf(pb, x, csp->tb[t]);
+            }
+            gk = ri * ri * ri - 2.0f * pa;
+            hk = ri - pb;
+        }
+    } else {
+        R rinv, gs, ph = 0;
+        if constexpr (F64) rinv = rsqrt64(x);
+        else rinv = __builtin_amdgcn_rsqf(x);
+        if constexpr (FORM == kFormPoly) {
+            constexpr int NP = PairConst<F64, FORM, WE>::NP;
+            const R y = f(x, pc.ys, (R)-1);
+            gs = pc.gp[NP - 1];
+#pragma unroll
+            for (int k = NP - 2; k >= 0; --k) gs = f(gs, y, pc.gp[k]);
+            if constexpr (WE) {
+                ph = pc.pp[NP - 1];
+#pragma unroll
+                for (int k = NP - 2; k >= 0; --k) ph = f(ph, y, pc.pp[k]);
+            }
+        } else {
+            constexpr int NT = (F64 ? kTailDeg64 : kTailDeg32) + 1;
+            gs = co->ft[NT - 1];
+#pragma unroll
+            for (int t = NT - 2; t >= 0; --t) gs = f(gs, x, co->ft[t]);
+            if constexpr (WE) {
+                ph = co->pt[NT - 1];
+#pragma unroll
+                for (int t = NT - 2; t >= 0; --t) ph = f(ph, x, co->pt[t]);
+            }
+            // the first terms at fixed indices (the constants past the
+            // count are zero: a term of weight 0 adds exactly 0), then the rest
+            auto term = [&](int l) {
+                R ex;
+                if constexpr (F64) ex = rmath::exp_nonpos(-x * co->a[l]);
+                else ex = __builtin_amdgcn_exp2f(-x * co->a[l]);
+                gs = f(co->cw[l], ex, gs);
+                if constexpr (WE) ph = f(co->w[l], ex, ph);
+            };
+            constexpr int NE = kExpRegs<F64>;
+#pragma unroll
+            for (int l = 0; l < NE; ++l) term(l);
+            for (int l = NE; l < co->nexp; ++l) term(l);
+        }
+        gk = f(rinv, rinv * rinv, -gs);
+        hk = rinv - ph;
+    }
+}
+
+// A home of the list pass in registers, and a listed candidate's gather record.
+template <bool F64>
+struct ListHome {
+    uint32_t u[3];  // FP32C; FP64: only for pairs at the cutoff
+    double x[3];    // FP64
+    typename std::conditional<F64, double, float>::type q;
+};
+template <bool F64>
+struct ListCand;
+template <>
+struct ListCand<false> {
+    uint4 r;  // u_x, u_y, u_z, charge bits
+};
+template <>
+struct ListCand<true> {
+    PosQ64 r;
+};
+
+// The record of a list entry (its byte offset 16 j; slots are below 2^28).
+template <bool F64>
+__device__ __forceinline__ ListCand<F64> load_cand(const EvalArgs &a, uint32_t off) {
+    ListCand<F64> c;
+    if constexpr (F64) c.r = *(const PosQ64 *)((const char *)a.pkx + ((uint64_t)off << 1));
+    else c.r = *(const uint4 *)((const char *)a.pk + off);
+    return c;
+}
+
+// One listed pair: the pair rule at the current positions, then (every lane,
+// no branch) the displacement, the pair force added to (fx, fy, fz) and half
+// the pair energy to e; a select zeroes what a rejected or empty lane
+// produced.  FP32C decides by the FP32 r^2 of the fixed-point differences
+// below its band, FP64 by the FP64 r^2 of the wrapped coordinates below its
+// own (a pair in 10^6 lies in the band), the exact rule on the fixed-point
+// coordinates inside.  WRAP (FP64): take the minimum image; homes farther than
+// dlist from every face need none (the rounded quotient is 0 for every listed
+// pair), which is three subtractions for twelve operations.
+template <bool F64, int FORM, bool WE, bool WRAP, bool DBG>
+__device__ __forceinline__ void list_pair(const EvalArgs &a, const Geom &g, const PairConst<F64, FORM, WE> &pc,
+                                          typename CoefOf<F64>::type *co, const float4 *__restrict__ tbl, float rin2,
+                                          CSys *csp, const ListHome<F64> &h, uint32_t slot, const PairRec *rec,
+                                          uint32_t entry, bool have, const ListCand<F64> &c,
+                                          typename std::conditional<F64, double, float>::type &fx,
+                                          typename std::conditional<F64, double, float>::type &fy,
+                                          typename std::conditional<F64, double, float>::type &fz, double &e) {
+    using R = typename std::conditional<F64, double, float>::type;
+    R dx, dy, dz, r2, qq;
+    bool in;
+    if constexpr (F64) {
+        dx = c.r.x - h.x[0];
+        dy = c.r.y - h.x[1];
+        dz = c.r.z - h.x[2];
+        if constexpr (WRAP) {
+            dx = fma(-g.L[0], rint(dx * g.invL[0]), dx);
+            dy = fma(-g.L[1], rint(dy * g.invL[1]), dy);
+            dz = fma(-g.L[2], rint(dz * g.invL[2]), dz);
+        }
+        r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+        qq = h.q * c.r.q;
+        in = r2 <= g.band_lo;
+        if (have && !in && r2 < g.band_hi) {
+            const uint32_t j = entry >> 4;
+            in = exact_in(g, a.u_tmp[j] - h.u[0], a.u_tmp[a.N + j] - h.u[1], a.u_tmp[2 * a.N + j] - h.u[2]);
+        }
+    } else {
+        const uint32_t dux = c.r.x - h.u[0], duy = c.r.y - h.u[1], duz = c.r.z - h.u[2];
+        dx = (float)(int32_t)dux * g.hf[0];
+        dy = (float)(int32_t)duy * g.hf[1];
+        dz = (float)(int32_t)duz * g.hf[2];
+        r2 = dx * dx + dy * dy + dz * dz;
+        qq = h.q * __uint_as_float(c.r.w);
+        in = r2 <= g.band_lo_f;
+        if (have && !in && r2 < g.band_hi_f) in = exact_in(g, dux, duy, duz);
+    }
+    in = in && have;
+    if constexpr (DBG) {
+        if (in) {
+            const int32_t k = atomicAdd(rec->cnt, 1);
+            if (k < rec->cap) rec->out[k] = make_uint2((uint32_t)rec->id[slot], (uint32_t)rec->id[entry >> 4]);
+        }
+    }
+    R gk, hk;
+    pair_kernel<F64, FORM, WE, R>(pc, co, tbl, rin2, csp, r2, gk, hk);
+    // force on the home along r_i - r_j = -(dx, dy, dz); zero unless accepted
+    const R coef = in ? -(qq * gk) : (R)0;
+    if constexpr (F64) {
+        fx = fma(coef, dx, fx);
+        fy = fma(coef, dy, fy);
+        fz = fma(coef, dz, fz);
+    } else {
+        fx = fmaf(coef, dx, fx);
+        fy = fmaf(coef, dy, fy);
+        fz = fmaf(coef, dz, fz);
+    }
+    if constexpr (WE) e += in ? 0.5 * (double)(qq * hk) : 0.0;
+}
+
+// The passes k = k0, k0 + dk, ... below kend of one home per lane or per wave
+// (entry(k): the lane's list entry of pass k, 0 past its end; have(k): whether
+// it has one): the entries two passes ahead and the candidates' data of the
+// next one are loaded while one is evaluated.  (Three gathers ahead were
+// slower, water-shaped 331,776 sites FP32C 490 against 427 us: the gathers'
+// L1 accesses bound the pass, not their latency.)
+template <bool F64, int FORM, bool WE, bool WRAP, bool DBG, class Entry, class Have>
+__device__ __forceinline__ void list_sweep(const EvalArgs &a, const Geom &g, const PairConst<F64, FORM, WE> &pc,
+                                           typename CoefOf<F64>::type *co, const float4 *__restrict__ tbl, float rin2,
+                                           CSys *csp, const ListHome<F64> &h, uint32_t slot, const PairRec *rec,
+                                           int32_t k0, int32_t dk, int32_t kend, Entry entry, Have have,
+                                           typename std::conditional<F64, double, float>::type &fx,
+                                           typename std::conditional<F64, double, float>::type &fy,
+                                           typename std::conditional<F64, double, float>::type &fz, double &e) {
+    uint32_t e1 = entry(k0), e2 = entry(k0 + dk);
+    ListCand<F64> pd = load_cand<F64>(a, e1);
+    for (int32_t k = k0; k < kend; k += dk) {
+        const ListCand<F64> cur = pd;
+        const uint32_t ce = e1;
+        e1 = e2;
+        e2 = entry(k + 2 * dk);
+        pd = load_cand<F64>(a, e1);
+        list_pair<F64, FORM, WE, WRAP, DBG>(a, g, pc, co, tbl, rin2, csp, h, slot, rec, ce, have(k), cur, fx, fy, fz, e);
+    }
+}
+
+// Total over the wave in lane 63, in a fixed order: DPP moves (row shifts 1,
+// 2, 4, 8, then lane 15 into rows 1 and 3 and lane 31 into rows 2 and 3; a
+// move reads 0 where it has no source lane).
+template <typename R>
+__device__ __forceinline__ R wave_total(R v) {
+    v += dpp<0x111, 0xf>(v);
+    v += dpp<0x112, 0xf>(v);
+    v += dpp<0x114, 0xf>(v);
+    v += dpp<0x118, 0xf>(v);
+    v += dpp<0x142, 0xa>(v);
+    v += dpp<0x143, 0xc>(v);
+    return v;
+}
+
 // List pass: one block per item; runs at every evaluation with the near
 // list, a build's included.  Column blocks: one lane per home (lane h holds
 // home h of the item in registers), wave w evaluating rows w, w + 4, ... of
 // the item's columns (row k holds the k-th listed pair of every home); each
 // lane sums its home's pairs in registers, and the four waves' sums are added
 // in a fixed order.  Home-major blocks: see below.
-template <bool F64, bool HM, bool DBG = false>
+// FP64 was bound by vector issue (about 115 instructions per listed pair with
+// three exponentials, a degree-12 tail, both an FP32 test and minimum images;
+// about 45 with one polynomial of degree 18): 300,000 ions 67 -> 47 us, 98,304
+// water-shaped sites (home-major) 340 -> 248 us.  FP32C (18 of 52 instructions
+// -> 11) is bound by the L1 accesses of its gathers: 20 and 427 us (331,776
+// sites) either way.
+template <bool F64, int FORM, bool HM, bool WE, bool DBG>
 __global__ __launch_bounds__(64 * kNW) void k_near_list(EvalArgs a, const ListItem *__restrict__ items,
                                                         int32_t nitems, int32_t nblk) {
     // the critical path's waves ahead of the structure factor's beside them
@@ -982,14 +1215,31 @@ __global__ __launch_bounds__(64 * kNW) void k_near_list(EvalArgs a, const ListIt
     typename CoefOf<F64>::type *co;
     if constexpr (F64) co = &sp->co64;
     else co = &sp->co32;
-    const float4 *tbl = F64 ? nullptr : sp->tbl;
-    const float rin2 = sp->rin2;
-    CSys *csp = sp;  // the core-shell Taylor constants are read where used
-    const bool we = a.energy != 0;
+    PairConst<F64, FORM, WE> pc;
+    pc.load(co);
+    const float4 *tbl = FORM == kFormTable ? sp->tbl : nullptr;
+    const float rin2 = FORM == kFormTable ? sp->rin2 : 0.f;
     const int64_t t0 = item.t0;
     const int H = (int)(item.t1 - t0);
     const int32_t rlast = (int32_t)(a.icap / kListHomes) - 1;
     double e = 0.0;
+    auto load_home = [&](int64_t t) {
+        ListHome<F64> h;
+        h.u[0] = su[t]; h.u[1] = su[n + t]; h.u[2] = su[2 * n + t];
+        if constexpr (F64) {
+            h.x[0] = sx[t]; h.x[1] = sx[n + t]; h.x[2] = sx[2 * n + t];
+            h.q = sq[t];
+        } else {
+            h.q = sqf[t];
+        }
+        return h;
+    };
+    // whether every listed pair of the home is its own minimum image
+    auto inner = [&](const ListHome<F64> &h) {
+        bool ok = F64;
+        for (int d = 0; d < 3; ++d) ok = ok && h.x[d] >= g.dlist && h.x[d] <= g.L[d] - g.dlist;
+        return ok;
+    };
     if constexpr (HM) {
         // home-major blocks (long lists): wave w takes homes w, w + kNW, ...
         // of the item one at a time, its lanes on 64 consecutive entries of
@@ -998,15 +1248,7 @@ __global__ __launch_bounds__(64 * kNW) void k_near_list(EvalArgs a, const ListIt
         // evaluated; each home's sums close with a fixed-order wave sum
         for (int hh = w; hh < H; hh += kNW) {
             const int64_t th = t0 + hh;
-            HomeData<F64> hd;
-            hd.u[0] = su[th]; hd.u[1] = su[n + th]; hd.u[2] = su[2 * n + th];
-            hd.slot = (uint32_t)th;
-            if constexpr (F64) {
-                hd.q = sq[th];
-                hd.x[0] = sx[th]; hd.x[1] = sx[n + th]; hd.x[2] = sx[2 * n + th];
-            } else {
-                hd.q = sqf[th];
-            }
+            const ListHome<F64> hd = load_home(th);
             const int32_t cnt = ((CI32 *)a.pcnt)[(int64_t)it * kListHomes + hh];
             // the home's block of the list (a uniform base; 32-bit offsets)
             const char *__restrict__ rowp =
@@ -1016,96 +1258,60 @@ __global__ __launch_bounds__(64 * kNW) void k_near_list(EvalArgs a, const ListIt
                 return r < cnt ? v : 0u;
             };
             R fx = 0, fy = 0, fz = 0;
-            // the entries two chunks ahead and the candidates' data of the
-            // next chunk are loaded while one chunk is evaluated
-            uint32_t e1 = entry(lane), e2 = entry(64 + lane);
-            PairData<F64> pd = load_packed<F64>(a.pk, a.pkx, e1);
-            for (int32_t c = 0; c < cnt; c += 64) {
-                const bool have = c + lane < cnt;
-                const uint32_t cj = e1 >> 4;  // the slot (pair records of debug launches)
-                const PairData<F64> cur = pd;
-                e1 = e2;
-                e2 = entry(c + 128 + lane);
-                pd = load_packed<F64>(a.pk, a.pkx, e1);
-                R px, py, pz;
-                double de;
-                pair_force<F64, false, DBG>(g, co, hd, we, DBG ? &rec : nullptr, tbl, rin2, csp, cj, have, cur, px,
-                                            py, pz, de);
-                fx += px; fy += py; fz += pz;
-                if (we) {
-                    asm volatile("");
-                    e += de;
-                }
-            }
-            fx = wave_sum(fx);
-            fy = wave_sum(fy);
-            fz = wave_sum(fz);
-            if (lane == 0) {
+            auto sweep = [&](auto wrapc) {
+                list_sweep<F64, FORM, WE, decltype(wrapc)::value, DBG>(
+                    a, g, pc, co, tbl, rin2, sp, hd, (uint32_t)th, DBG ? &rec : nullptr, 0, 64, cnt,
+                    [&](int32_t c) { return entry(c + lane); }, [&](int32_t c) { return c + lane < cnt; }, fx, fy, fz, e);
+            };
+            if (F64 && !ballot(!inner(hd))) sweep(std::false_type{});
+            else sweep(std::bool_constant<F64>{});
+            fx = wave_total(fx);
+            fy = wave_total(fy);
+            fz = wave_total(fz);
+            if (lane == 63) {
                 a.Fn[th] = (double)fx;
                 a.Fn[n + th] = (double)fy;
                 a.Fn[2 * n + th] = (double)fz;
             }
         }
-        const double es = wave_sum(e);
+        const double es = WE ? wave_sum(e) : 0.0;
         if (lane == 0) es_w[w] = es;
         __syncthreads();
     } else {
-    const bool home = lane < H;
-    const int64_t tt = t0 + (home ? lane : 0);
-    HomeData<F64> hd;
-    hd.u[0] = su[tt]; hd.u[1] = su[n + tt]; hd.u[2] = su[2 * n + tt];
-    hd.slot = (uint32_t)tt;
-    if constexpr (F64) {
-        hd.q = sq[tt];
-        hd.x[0] = sx[tt]; hd.x[1] = sx[n + tt]; hd.x[2] = sx[2 * n + tt];
-    } else {
-        hd.q = sqf[tt];
-    }
-    const int32_t cnt = home ? a.pcnt[(int64_t)it * kListHomes + lane] : 0;
-    int32_t mc = cnt;
-    for (int o = 32; o > 0; o >>= 1) mc = max(mc, __shfl_xor(mc, o, 64));
-    const int32_t maxcnt = rfl(mc);
-    // this lane's column; rows past the stored ones are read as the last
-    // stored row and not used (loads without a branch)
-    const char *__restrict__ blk = (const char *)(a.pairs + (int64_t)it * a.icap);
-    auto entry = [&](int32_t r) -> uint32_t {
-        const uint32_t v = *(const uint32_t *)(blk + (uint32_t)((min(r, rlast) * kListHomes + lane) * 4));
-        return r < cnt ? v : 0u;
-    };
-    R fx = 0, fy = 0, fz = 0;
-    // rows w, w + kNW, ...: the entries two rows ahead and the candidate's
-    // data of the next row are loaded while this one is evaluated
-    int32_t k = w;
-    uint32_t e1 = entry(k), e2 = entry(k + kNW);
-    PairData<F64> pd = load_packed<F64>(a.pk, a.pkx, e1);
-    for (; k < maxcnt; k += kNW) {
-        const bool have = k < cnt;
-        const uint32_t cj = e1 >> 4;  // the slot (pair records of debug launches)
-        const PairData<F64> cur = pd;
-        e1 = e2;
-        e2 = entry(k + 2 * kNW);
-        pd = load_packed<F64>(a.pk, a.pkx, e1);
-        R px, py, pz;
-        double de;
-        pair_force<F64, false, DBG>(g, co, hd, we, DBG ? &rec : nullptr, tbl, rin2, csp, cj, have, cur, px, py, pz,
-                                    de);
-        fx += px; fy += py; fz += pz;
-        if (we) {
-            asm volatile("");
-            e += de;
+        const bool home = lane < H;
+        const int64_t tt = t0 + (home ? lane : 0);
+        const ListHome<F64> hd = load_home(tt);
+        const int32_t cnt = home ? a.pcnt[(int64_t)it * kListHomes + lane] : 0;
+        int32_t mc = cnt;
+        for (int o = 32; o > 0; o >>= 1) mc = max(mc, __shfl_xor(mc, o, 64));
+        const int32_t maxcnt = rfl(mc);
+        // this lane's column; rows past the stored ones are read as the last
+        // stored row and not used (loads without a branch)
+        const char *__restrict__ blk = (const char *)(a.pairs + (int64_t)it * a.icap);
+        auto entry = [&](int32_t r) -> uint32_t {
+            const uint32_t v = *(const uint32_t *)(blk + (uint32_t)((min(r, rlast) * kListHomes + lane) * 4));
+            return r < cnt ? v : 0u;
+        };
+        R fx = 0, fy = 0, fz = 0;
+        // rows w, w + kNW, ...
+        auto sweep = [&](auto wrapc) {
+            list_sweep<F64, FORM, WE, decltype(wrapc)::value, DBG>(
+                a, g, pc, co, tbl, rin2, sp, hd, (uint32_t)tt, DBG ? &rec : nullptr, w, kNW, maxcnt,
+                [&](int32_t k) { return entry(k); }, [&](int32_t k) { return k < cnt; }, fx, fy, fz, e);
+        };
+        if (F64 && !ballot(!inner(hd))) sweep(std::false_type{});
+        else sweep(std::bool_constant<F64>{});
+        pf[w][0][lane] = fx;
+        pf[w][1][lane] = fy;
+        pf[w][2][lane] = fz;
+        const double es = WE ? wave_sum(e) : 0.0;
+        if (lane == 0) es_w[w] = es;
+        __syncthreads();
+        if (w == 0 && home) {
+            for (int d = 0; d < 3; ++d)
+                a.Fn[d * n + tt] = (((double)pf[0][d][lane] + (double)pf[1][d][lane]) + (double)pf[2][d][lane]) +
+                                   (double)pf[3][d][lane];
         }
-    }
-    pf[w][0][lane] = fx;
-    pf[w][1][lane] = fy;
-    pf[w][2][lane] = fz;
-    const double es = wave_sum(e);
-    if (lane == 0) es_w[w] = es;
-    __syncthreads();
-    if (w == 0 && home) {
-        for (int d = 0; d < 3; ++d)
-            a.Fn[d * n + tt] = (((double)pf[0][d][lane] + (double)pf[1][d][lane]) + (double)pf[2][d][lane]) +
-                               (double)pf[3][d][lane];
-    }
     }
     if (threadIdx.x == 0) a.epart[it] = ((es_w[0] + es_w[1]) + es_w[2]) + es_w[3];
 }
@@ -1539,21 +1745,34 @@ void launch_near(const EvalArgs &a, bool f64, const ListItem *items, int32_t nit
     int32_t nblk = (nitems + 7) / 8 * 8;
     if (nblk < 8) nblk = 8;
     dim3 grid((unsigned)nblk), block(64 * kNW);
-    // one instantiation per layout: each keeps its own register budget
-    auto go = [&](auto f64c, auto hmc, auto dbgc) {
-        hipLaunchKernelGGL((k_near_list<decltype(f64c)::value, decltype(hmc)::value, decltype(dbgc)::value>), grid,
-                           block, 0, s, a, items, nitems, nblk);
+    // one instantiation per form, layout and energy flag: each keeps its own
+    // constants in registers, with no test of them in its loop
+    using std::bool_constant;
+    using std::integral_constant;
+    auto go = [&](auto f64c, auto form, auto hmc, auto wec, auto dbgc) {
+        hipLaunchKernelGGL((k_near_list<decltype(f64c)::value, decltype(form)::value, decltype(hmc)::value,
+                                        decltype(wec)::value, decltype(dbgc)::value>),
+                           grid, block, 0, s, a, items, nitems, nblk);
     };
-    auto by_hm = [&](auto f64c, auto dbgc) {
-        if (a.list_hm) go(f64c, std::true_type{}, dbgc);
-        else go(f64c, std::false_type{}, dbgc);
+    auto by_dbg = [&](auto f64c, auto form, auto hmc, auto wec) {
+        if (a.dbg_pairs) go(f64c, form, hmc, wec, bool_constant<true>{});
+        else go(f64c, form, hmc, wec, bool_constant<false>{});
     };
-    auto by_f64 = [&](auto dbgc) {
-        if (f64) by_hm(std::true_type{}, dbgc);
-        else by_hm(std::false_type{}, dbgc);
+    auto by_we = [&](auto f64c, auto form, auto hmc) {
+        if (a.energy) by_dbg(f64c, form, hmc, bool_constant<true>{});
+        else by_dbg(f64c, form, hmc, bool_constant<false>{});
     };
-    if (a.dbg_pairs) by_f64(std::true_type{});
-    else by_f64(std::false_type{});
+    auto by_hm = [&](auto f64c, auto form) {
+        if (a.list_hm) by_we(f64c, form, bool_constant<true>{});
+        else by_we(f64c, form, bool_constant<false>{});
+    };
+    auto by_form = [&](auto f64c) {
+        if (a.near_form == kFormPoly) by_hm(f64c, integral_constant<int, kFormPoly>{});
+        else if (a.near_form == kFormTable && !decltype(f64c)::value) by_hm(bool_constant<false>{}, integral_constant<int, kFormTable>{});
+        else by_hm(f64c, integral_constant<int, kFormExp>{});
+    };
+    if (f64) by_form(bool_constant<true>{});
+    else by_form(bool_constant<false>{});
 }
 
 void launch_neighbor_count(const EvalArgs &a, int32_t sys, int64_t n, int64_t p0, const int32_t *id_cur,

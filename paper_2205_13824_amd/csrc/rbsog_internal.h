@@ -55,6 +55,7 @@ struct Geom {
     float band_lo_f, band_hi_f;  // same for the FP32 fast test
     int32_t nc[3];               // cells per side: floor(L / (r_c (1 + skin))), or 1 below 3
     int32_t reach[3];            // 1 if the stencil spans -1..1 in that dimension, 0 otherwise
+    double dlist;                // no listed pair is farther apart than this before the next build: r_c (1 + 2 skin), widened
     float rl2_f;                 // FP32 r^2 below which a pair enters the Verlet list (r_c (1 + skin))^2, widened
     float dthr2_f;               // FP32 squared displacement beyond which the list is rebuilt (skin r_c / 2)^2, narrowed
 };
@@ -70,7 +71,17 @@ constexpr int kTailDeg64 = 12;
 constexpr int kTailDeg32 = 6;
 constexpr int kMaxExp = 24;  // narrow Gaussians per split (more is rejected)
 
-template <typename R, int NT>
+// List pass, polynomial form: where the whole sum of Gaussians over x in [0,
+// r_c^2] is a polynomial of y = 2 x / r_c^2 - 1 of degree kPolyDeg to below
+// kPolyTol of its value at 0 (Chebyshev coefficients of e^{-a y} fall like
+// (a/2)^n / n!, a = r_c^2 / (2 s_0^2): 1.9 for Table 1 row 2, 0.99 for row 1),
+// it takes the place of the exponentials and the tail; other splits keep them.
+constexpr int kPolyDeg64 = 18;
+constexpr int kPolyDeg32 = 10;
+constexpr double kPolyTol64 = 5e-16;
+constexpr double kPolyTol32 = 1e-8;
+
+template <typename R, int NT, int NP>
 struct SplitCoef {
     R a[kMaxExp];   // 1/s_l^2 (FP32: log2(e)/s_l^2, for exp2)
     R cw[kMaxExp];  // 2 omega_l / s_l^2
@@ -78,9 +89,13 @@ struct SplitCoef {
     R pt[NT];       // sum_{l>=nexp} omega_l e^{-x/s_l^2} = sum_k pt[k] x^k
     R ft[NT];       // sum_{l>=nexp} 2 omega_l/s_l^2 e^{-x/s_l^2} = sum_k ft[k] x^k
     int32_t nexp;
+    int32_t poly;   // the polynomial form holds
+    R ys;           // 2 / r_c^2
+    R gp[NP];       // sum_l 2 omega_l/s_l^2 e^{-x/s_l^2} = sum_k gp[k] y^k
+    R pp[NP];       // sum_l omega_l e^{-x/s_l^2} = sum_k pp[k] y^k
 };
-using SplitCoef64 = SplitCoef<double, kTailDeg64 + 1>;
-using SplitCoef32 = SplitCoef<float, kTailDeg32 + 1>;
+using SplitCoef64 = SplitCoef<double, kTailDeg64 + 1, kPolyDeg64 + 1>;
+using SplitCoef32 = SplitCoef<float, kTailDeg32 + 1, kPolyDeg32 + 1>;
 
 // Core-shell near kernel (Sec. 3.4), an option of the FP32C form: pairs with
 // r < r_in take Q Taylor terms of the Gaussians with 1/r and 1/r^3 computed;
@@ -93,6 +108,10 @@ constexpr int kTabBexp = 3;
 constexpr int kTabBman = 9;
 constexpr int kTabSize = 1 << (kTabBexp + kTabBman);
 constexpr double kTabRin = 0.2;  // r_in / r_c
+
+// Forms of the list pass's pair kernel, the same for every system of a batch:
+// exponentials with the tail polynomial, one polynomial, core-shell table.
+constexpr int32_t kFormExp = 0, kFormPoly = 1, kFormTable = 2;
 
 // Per-system constants, one entry per system in a device array.
 struct SysDev {
@@ -201,7 +220,7 @@ struct EvalArgs {
     // what the list pass gathers of a listed candidate, one record per slot
     // in the current order (written by the kick/drift kernel, and in the new
     // order by a build's copy back): fixed-point coordinates with the FP32
-    // charge's bits; the FP64 position and charge (FP64 form; else null)
+    // charge's bits (FP32C; else null), the FP64 position and charge (FP64)
     uint4 *pk;
     PosQ64 *pkx;
     int32_t *cell_of, *cell_count, *cell_start, *cell_fill, *src, *sorted, *blocksums;
@@ -215,6 +234,7 @@ struct EvalArgs {
     // the near list items state), counts,
     // capacity per item, largest count of the latest build, builds made
     int32_t *rebuild;
+    int32_t near_form;     // how the list pass evaluates the Gaussians (kForm...)
     int32_t list_hm;       // nonzero: home-major blocks of the near list (long lists)
     int32_t always_build;  // nonzero: every evaluation builds (no displacement check, no list kept)
     uint32_t *pairs;
@@ -313,7 +333,7 @@ __device__ __forceinline__ float wrap_store(const EvalArgs &a, int64_t t, bool v
         const double q = a.cur.q[t];
         if (a.rs_qf) a.rs_qf[t] = qf;
         if (a.rs_q) a.rs_q[t] = q;
-        a.pk[t] = make_uint4(uq[0], uq[1], uq[2], __float_as_uint(qf));
+        if (a.pk) a.pk[t] = make_uint4(uq[0], uq[1], uq[2], __float_as_uint(qf));
         if (a.pkx) a.pkx[t] = PosQ64{xw[0], xw[1], xw[2], q};
     }
     return d2;
