@@ -911,7 +911,7 @@ rbsog_status size_list(rbsog_ctx *c, int64_t largest) {
     c->list_hm = largest > kHomeMajorMin;
     HIPCHK(c, hipStreamSynchronize(c->stream));
     uint32_t *np = nullptr;
-    if (hipMalloc((void **)&np, (size_t)c->n_list * (size_t)want * sizeof(uint32_t)) != hipSuccess)
+    if (hipMalloc((void **)&np, ((size_t)c->n_list * (size_t)want + kListPad) * sizeof(uint32_t)) != hipSuccess)
         return fail(c, RBSOG_E_OOM, "pair list of %lld x %lld entries", (long long)c->n_list, (long long)want);
     if (c->pairs) {
         c->allocs.erase(std::remove(c->allocs.begin(), c->allocs.end(), (void *)c->pairs), c->allocs.end());
@@ -2895,7 +2895,7 @@ rbsog_status rbsog_load_state(rbsog_ctx *c, const void *buf, int64_t len) {
     if (skin_cur > 0.0 && icap != c->icap) {
         // a list of the saved capacity
         uint32_t *np = nullptr;
-        if (hipMalloc((void **)&np, (size_t)c->n_list * (size_t)icap * sizeof(uint32_t)) != hipSuccess)
+        if (hipMalloc((void **)&np, ((size_t)c->n_list * (size_t)icap + kListPad) * sizeof(uint32_t)) != hipSuccess)
             return fail(c, RBSOG_E_OOM, "pair list of %lld x %lld entries", (long long)c->n_list, (long long)icap);
         if (c->pairs) {
             c->allocs.erase(std::remove(c->allocs.begin(), c->allocs.end(), (void *)c->pairs), c->allocs.end());

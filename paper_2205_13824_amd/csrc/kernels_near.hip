@@ -1029,9 +1029,10 @@ __device__ __forceinline__ void pair_kernel(const PairConst<F64, FORM, WE> &pc, 
 // A home of the list pass in registers, and a listed candidate's gather record.
 template <bool F64>
 struct ListHome {
-    uint32_t u[3];  // FP32C; FP64: only for pairs at the cutoff
+    uint32_t u[3];  // FP32C
     double x[3];    // FP64
     typename std::conditional<F64, double, float>::type q;
+    uint32_t slot;
 };
 template <bool F64>
 struct ListCand;
@@ -1065,7 +1066,7 @@ __device__ __forceinline__ ListCand<F64> load_cand(const EvalArgs &a, uint32_t o
 template <bool F64, int FORM, bool WE, bool WRAP, bool DBG>
 __device__ __forceinline__ void list_pair(const EvalArgs &a, const Geom &g, const PairConst<F64, FORM, WE> &pc,
                                           typename CoefOf<F64>::type *co, const float4 *__restrict__ tbl, float rin2,
-                                          CSys *csp, const ListHome<F64> &h, uint32_t slot, const PairRec *rec,
+                                          CSys *csp, const ListHome<F64> &h, const PairRec *rec,
                                           uint32_t entry, bool have, const ListCand<F64> &c,
                                           typename std::conditional<F64, double, float>::type &fx,
                                           typename std::conditional<F64, double, float>::type &fy,
@@ -1086,8 +1087,9 @@ __device__ __forceinline__ void list_pair(const EvalArgs &a, const Geom &g, cons
         qq = h.q * c.r.q;
         in = r2 <= g.band_lo;
         if (have && !in && r2 < g.band_hi) {
-            const uint32_t j = entry >> 4;
-            in = exact_in(g, a.u_tmp[j] - h.u[0], a.u_tmp[a.N + j] - h.u[1], a.u_tmp[2 * a.N + j] - h.u[2]);
+            const uint32_t j = entry >> 4, i = h.slot;
+            in = exact_in(g, a.u_tmp[j] - a.u_tmp[i], a.u_tmp[a.N + j] - a.u_tmp[a.N + i],
+                          a.u_tmp[2 * a.N + j] - a.u_tmp[2 * a.N + i]);
         }
     } else {
         const uint32_t dux = c.r.x - h.u[0], duy = c.r.y - h.u[1], duz = c.r.z - h.u[2];
@@ -1103,7 +1105,7 @@ __device__ __forceinline__ void list_pair(const EvalArgs &a, const Geom &g, cons
     if constexpr (DBG) {
         if (in) {
             const int32_t k = atomicAdd(rec->cnt, 1);
-            if (k < rec->cap) rec->out[k] = make_uint2((uint32_t)rec->id[slot], (uint32_t)rec->id[entry >> 4]);
+            if (k < rec->cap) rec->out[k] = make_uint2((uint32_t)rec->id[h.slot], (uint32_t)rec->id[entry >> 4]);
         }
     }
     R gk, hk;
@@ -1122,32 +1124,6 @@ __device__ __forceinline__ void list_pair(const EvalArgs &a, const Geom &g, cons
     if constexpr (WE) e += in ? 0.5 * (double)(qq * hk) : 0.0;
 }
 
-// The passes k = k0, k0 + dk, ... below kend of one home per lane or per wave
-// (entry(k): the lane's list entry of pass k, 0 past its end; have(k): whether
-// it has one): the entries two passes ahead and the candidates' data of the
-// next one are loaded while one is evaluated.  (Three gathers ahead were
-// slower, water-shaped 331,776 sites FP32C 490 against 427 us: the gathers'
-// L1 accesses bound the pass, not their latency.)
-template <bool F64, int FORM, bool WE, bool WRAP, bool DBG, class Entry, class Have>
-__device__ __forceinline__ void list_sweep(const EvalArgs &a, const Geom &g, const PairConst<F64, FORM, WE> &pc,
-                                           typename CoefOf<F64>::type *co, const float4 *__restrict__ tbl, float rin2,
-                                           CSys *csp, const ListHome<F64> &h, uint32_t slot, const PairRec *rec,
-                                           int32_t k0, int32_t dk, int32_t kend, Entry entry, Have have,
-                                           typename std::conditional<F64, double, float>::type &fx,
-                                           typename std::conditional<F64, double, float>::type &fy,
-                                           typename std::conditional<F64, double, float>::type &fz, double &e) {
-    uint32_t e1 = entry(k0), e2 = entry(k0 + dk);
-    ListCand<F64> pd = load_cand<F64>(a, e1);
-    for (int32_t k = k0; k < kend; k += dk) {
-        const ListCand<F64> cur = pd;
-        const uint32_t ce = e1;
-        e1 = e2;
-        e2 = entry(k + 2 * dk);
-        pd = load_cand<F64>(a, e1);
-        list_pair<F64, FORM, WE, WRAP, DBG>(a, g, pc, co, tbl, rin2, csp, h, slot, rec, ce, have(k), cur, fx, fy, fz, e);
-    }
-}
-
 // Total over the wave in lane 63, in a fixed order: DPP moves (row shifts 1,
 // 2, 4, 8, then lane 15 into rows 1 and 3 and lane 31 into rows 2 and 3; a
 // move reads 0 where it has no source lane).
@@ -1162,26 +1138,44 @@ __device__ __forceinline__ R wave_total(R v) {
     return v;
 }
 
-// List pass: one block per item; runs at every evaluation with the near
-// list, a build's included.  Column blocks: one lane per home (lane h holds
-// home h of the item in registers), wave w evaluating rows w, w + 4, ... of
-// the item's columns (row k holds the k-th listed pair of every home); each
-// lane sums its home's pairs in registers, and the four waves' sums are added
-// in a fixed order.  Home-major blocks: see below.
-// FP64 was bound by vector issue (about 115 instructions per listed pair with
-// three exponentials, a degree-12 tail, both an FP32 test and minimum images;
-// about 45 with one polynomial of degree 18): 300,000 ions 67 -> 47 us, 98,304
-// water-shaped sites (home-major) 340 -> 248 us.  FP32C (18 of 52 instructions
-// -> 11) is bound by the L1 accesses of its gathers: 20 and 427 us (331,776
-// sites) either way.
+// List pass: one block per item; runs at every evaluation with the near list,
+// a build's included.  Column blocks: one lane per home (lane h holds home h
+// of the item in registers), wave w evaluating rows w, w + 4, ... of the
+// item's columns (row k holds the k-th listed pair of every home); each lane
+// sums its home's pairs in registers, and the four waves' sums are added in a
+// fixed order.  Home-major blocks (HM): see below.
+//
+// A pass over 64 pairs takes about 45 vector instructions and two dependent
+// loads (the list entries, then the candidates' records), so the loop keeps
+// list entries kE and records kG passes ahead and looks at an entry only when
+// its record is requested: one entry and one record ahead, with the entry
+// tested in the pass of its load, each pass waited for a load.
+// 300,000 ions FP32C 20 -> 16 us, FP64 67 -> 38; 2,097,152 ions FP32C (beside
+// the structure factor) 219 -> 163; water-shaped 331,776 sites FP32C 429 ->
+// 336, 98,304 sites FP64 340 -> 178.
+constexpr int kE = 4;
+template <bool F64>
+constexpr int kG = F64 ? 1 : 2;
+static_assert(kG<false> < kE && kE % kG<false> == 0, "records are requested from loaded entries");
+
+// Waves of a home-major block: 16 (FP64 8, whose 80 registers leave a SIMD six
+// waves), so that the waves of a CU work on few places of the box and the
+// gathers of homes that share their candidates meet in L1.  331,776
+// water-shaped sites FP32C: 4 waves 407 us (34 million L1 misses, 11 TB/s
+// from L2), 8 waves 375, 16 waves 336, 16 waves on two items 366; 98,304
+// sites FP64: 4 waves 192, 8 waves 178, 16 waves 188.
+template <bool F64>
+constexpr int kHmWaves = F64 ? 8 : 16;
+
 template <bool F64, int FORM, bool HM, bool WE, bool DBG>
-__global__ __launch_bounds__(64 * kNW) void k_near_list(EvalArgs a, const ListItem *__restrict__ items,
+__global__ __launch_bounds__(64 * (HM ? kHmWaves<F64> : kNW), HM ? (F64 ? 6 : 8) : 1) void k_near_list(EvalArgs a, const ListItem *__restrict__ items,
                                                         int32_t nitems, int32_t nblk) {
     // the critical path's waves ahead of the structure factor's beside them
     __builtin_amdgcn_s_setprio(2);
     using R = typename std::conditional<F64, double, float>::type;
-    __shared__ R pf[kNW][3][kListHomes];
-    __shared__ double es_w[kNW];
+    constexpr int W = HM ? kHmWaves<F64> : kNW;
+    __shared__ R pf[HM ? 1 : kNW][3][kListHomes];
+    __shared__ double es_w[W];
     __shared__ PairRec rec;
     if constexpr (DBG) {
         if (threadIdx.x == 0) {
@@ -1193,85 +1187,126 @@ __global__ __launch_bounds__(64 * kNW) void k_near_list(EvalArgs a, const ListIt
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
     const int64_t n = a.N;
-    const uint32_t *__restrict__ su = a.u_tmp;
-    const double *__restrict__ sx = a.cur.x;
-    const double *__restrict__ sq = a.cur.q;
-    const float *__restrict__ sqf = a.cur.qf;
-    // one item per block, dealt to the XCDs as in the build
+    // items dealt to the XCDs as in the build
     const int32_t b = blockIdx.x;
     const int32_t it = (b % 8) * (nblk / 8) + b / 8;
     // the far kernel that follows opens the next step and sets the flag: the
     // list build, its last reader in this evaluation, has run
     if (a.fuse && b == 0 && threadIdx.x == 0) *a.rebuild = 0;
     if (it >= nitems) return;
+    const int64_t rows = a.icap / kListHomes;
+    const char *__restrict__ blk = (const char *)(a.pairs + (int64_t)it * a.icap);
     const __attribute__((address_space(4))) ListItem *ip = (const __attribute__((address_space(4))) ListItem *)(items + it);
     ListItem item;
     item.sys = ip->sys;
     item.t0 = ip->t0;
     item.t1 = ip->t1;
-    const int32_t sys = rfl(item.sys);
-    CSys *sp = (CSys *)(a.sys + sys);
-    const Geom g = load_geom(sp);
-    typename CoefOf<F64>::type *co;
-    if constexpr (F64) co = &sp->co64;
-    else co = &sp->co32;
-    PairConst<F64, FORM, WE> pc;
-    pc.load(co);
-    const float4 *tbl = FORM == kFormTable ? sp->tbl : nullptr;
-    const float rin2 = FORM == kFormTable ? sp->rin2 : 0.f;
+    CSys *sp = (CSys *)(a.sys + rfl(item.sys));
     const int64_t t0 = item.t0;
     const int H = (int)(item.t1 - t0);
-    const int32_t rlast = (int32_t)(a.icap / kListHomes) - 1;
     double e = 0.0;
-    auto load_home = [&](int64_t t) {
+    auto home_of = [&](const ListCand<F64> &c, int64_t t) {
         ListHome<F64> h;
-        h.u[0] = su[t]; h.u[1] = su[n + t]; h.u[2] = su[2 * n + t];
         if constexpr (F64) {
-            h.x[0] = sx[t]; h.x[1] = sx[n + t]; h.x[2] = sx[2 * n + t];
-            h.q = sq[t];
+            h.x[0] = c.r.x; h.x[1] = c.r.y; h.x[2] = c.r.z;
+            h.q = c.r.q;
         } else {
-            h.q = sqf[t];
+            h.u[0] = c.r.x; h.u[1] = c.r.y; h.u[2] = c.r.z;
+            h.q = __uint_as_float(c.r.w);
         }
+        h.slot = (uint32_t)t;
         return h;
     };
+    auto constants = [&](PairConst<F64, FORM, WE> &pc, typename CoefOf<F64>::type *&co) {
+        if constexpr (F64) co = &sp->co64;
+        else co = &sp->co32;
+        pc.load(co);
+    };
     // whether every listed pair of the home is its own minimum image
-    auto inner = [&](const ListHome<F64> &h) {
+    auto inner = [&](const Geom &g, const ListHome<F64> &h) {
         bool ok = F64;
         for (int d = 0; d < 3; ++d) ok = ok && h.x[d] >= g.dlist && h.x[d] <= g.L[d] - g.dlist;
         return ok;
     };
     if constexpr (HM) {
-        // home-major blocks (long lists): wave w takes homes w, w + kNW, ...
-        // of the item one at a time, its lanes on 64 consecutive entries of
-        // the home's list (neighbouring candidates: the gathers stay local);
-        // the next chunk's entries and data are loaded while one is
-        // evaluated; each home's sums close with a fixed-order wave sum
-        for (int hh = w; hh < H; hh += kNW) {
-            const int64_t th = t0 + hh;
-            const ListHome<F64> hd = load_home(th);
-            const int32_t cnt = ((CI32 *)a.pcnt)[(int64_t)it * kListHomes + hh];
-            // the home's block of the list (a uniform base; 32-bit offsets)
-            const char *__restrict__ rowp =
-                (const char *)(a.pairs + (int64_t)it * a.icap + (int64_t)hh * (rlast + 1));
-            auto entry = [&](int32_t r) -> uint32_t {
-                const uint32_t v = *(const uint32_t *)(rowp + (uint32_t)(min(r, rlast) * 4));
-                return r < cnt ? v : 0u;
-            };
+        // home-major blocks (long lists): wave w takes homes w, w + W, ...
+        // of the item, its lanes on 64 consecutive entries of the home's list
+        // (neighbouring candidates: the gathers stay local); each home's sums
+        // close with a fixed-order wave sum.  The chunks of all its homes are
+        // one stream: entries are loaded kE chunks ahead (the list comes from
+        // HBM), records gathered kG<F64> ahead, across the homes' ends.
+        auto count = [&](int hh) { return ((CI32 *)a.pcnt)[(int64_t)it * kListHomes + hh]; };
+        uint32_t en[kE];
+        int32_t rem[kE];  // entries of a chunk's home from the chunk on
+        ListCand<F64> pd[kG<F64>];
+        // the load cursor: home, its list, its count, the chunk's first entry
+        int lh = w;
+        int32_t lcnt = lh < H ? count(lh) : 0, lc = 0;
+        const char *lp = blk + (int64_t)lh * rows * 4;
+        auto load_entry = [&](int s) {
+            rem[s] = lcnt - lc;
+            en[s] = *(const uint32_t *)(lp + (int64_t)lc * 4 + (uint32_t)(lane * 4));
+            lc += 64;
+            if (lc >= lcnt) {
+                // the next home (past the last one: chunks that nothing uses)
+                lh += W;
+                lc = 0;
+                if (lh < H) {
+                    lcnt = count(lh);
+                    lp = blk + (int64_t)lh * rows * 4;
+                } else {
+                    lcnt = 0;
+                }
+            }
+        };
+        int hh = w;
+        if (hh < H) {
+#pragma unroll
+            for (int s = 0; s < kE; ++s) load_entry(s);
+            const Geom g = load_geom(sp);
+            PairConst<F64, FORM, WE> pc;
+            typename CoefOf<F64>::type *co;
+            constants(pc, co);
+            const float4 *tbl = FORM == kFormTable ? sp->tbl : nullptr;
+            const float rin2 = FORM == kFormTable ? sp->rin2 : 0.f;
+#pragma unroll
+            for (int s = 0; s < kG<F64>; ++s) pd[s] = load_cand<F64>(a, lane < rem[s] ? en[s] : 0u);
+            ListHome<F64> hd = home_of(load_cand<F64>(a, (uint32_t)(t0 + hh) << 4), t0 + hh);
+            bool wrap = F64 && ballot(!inner(g, hd)) != 0;
             R fx = 0, fy = 0, fz = 0;
-            auto sweep = [&](auto wrapc) {
-                list_sweep<F64, FORM, WE, decltype(wrapc)::value, DBG>(
-                    a, g, pc, co, tbl, rin2, sp, hd, (uint32_t)th, DBG ? &rec : nullptr, 0, 64, cnt,
-                    [&](int32_t c) { return entry(c + lane); }, [&](int32_t c) { return c + lane < cnt; }, fx, fy, fz, e);
-            };
-            if (F64 && !ballot(!inner(hd))) sweep(std::false_type{});
-            else sweep(std::bool_constant<F64>{});
-            fx = wave_total(fx);
-            fy = wave_total(fy);
-            fz = wave_total(fz);
-            if (lane == 63) {
-                a.Fn[th] = (double)fx;
-                a.Fn[n + th] = (double)fy;
-                a.Fn[2 * n + th] = (double)fz;
+            while (hh < H) {
+#pragma unroll
+                for (int s = 0; s < kE; ++s) {
+                    const ListCand<F64> cur = pd[s % kG<F64>];
+                    const uint32_t ce = en[s];
+                    const int32_t rc = rem[s];
+                    const int sg = (s + kG<F64>) % kE;
+                    pd[s % kG<F64>] = load_cand<F64>(a, lane < rem[sg] ? en[sg] : 0u);
+                    load_entry(s);
+                    if (F64 && !wrap)
+                        list_pair<F64, FORM, WE, false, DBG>(a, g, pc, co, tbl, rin2, sp, hd, DBG ? &rec : nullptr, ce,
+                                                             lane < rc, cur, fx, fy, fz, e);
+                    else
+                        list_pair<F64, FORM, WE, F64, DBG>(a, g, pc, co, tbl, rin2, sp, hd, DBG ? &rec : nullptr, ce,
+                                                           lane < rc, cur, fx, fy, fz, e);
+                    if (rc <= 64) {
+                        // the home's last chunk
+                        fx = wave_total(fx);
+                        fy = wave_total(fy);
+                        fz = wave_total(fz);
+                        if (lane == 63) {
+                            const int64_t th = t0 + hh;
+                            a.Fn[th] = (double)fx;
+                            a.Fn[n + th] = (double)fy;
+                            a.Fn[2 * n + th] = (double)fz;
+                        }
+                        hh += W;
+                        if (hh >= H) break;
+                        hd = home_of(load_cand<F64>(a, (uint32_t)(t0 + hh) << 4), t0 + hh);
+                        wrap = F64 && ballot(!inner(g, hd)) != 0;
+                        fx = fy = fz = 0;
+                    }
+                }
             }
         }
         const double es = WE ? wave_sum(e) : 0.0;
@@ -1280,31 +1315,51 @@ __global__ __launch_bounds__(64 * kNW) void k_near_list(EvalArgs a, const ListIt
     } else {
         const bool home = lane < H;
         const int64_t tt = t0 + (home ? lane : 0);
-        const ListHome<F64> hd = load_home(tt);
+        // this lane's column (rows past the stored ones, at most kListPad
+        // entries on, are read and not used)
+        auto entry = [&](int32_t r) {
+            return *(const uint32_t *)(blk + (int64_t)r * (kListHomes * 4) + (uint32_t)(lane * 4));
+        };
+        uint32_t en[kE];
+#pragma unroll
+        for (int s = 0; s < kE; ++s) en[s] = entry(w + s * W);
         const int32_t cnt = home ? a.pcnt[(int64_t)it * kListHomes + lane] : 0;
-        int32_t mc = cnt;
-        for (int o = 32; o > 0; o >>= 1) mc = max(mc, __shfl_xor(mc, o, 64));
-        const int32_t maxcnt = rfl(mc);
-        // this lane's column; rows past the stored ones are read as the last
-        // stored row and not used (loads without a branch)
-        const char *__restrict__ blk = (const char *)(a.pairs + (int64_t)it * a.icap);
-        auto entry = [&](int32_t r) -> uint32_t {
-            const uint32_t v = *(const uint32_t *)(blk + (uint32_t)((min(r, rlast) * kListHomes + lane) * 4));
-            return r < cnt ? v : 0u;
-        };
+        const ListHome<F64> hd = home_of(load_cand<F64>(a, (uint32_t)tt << 4), tt);
+        const Geom g = load_geom(sp);
+        PairConst<F64, FORM, WE> pc;
+        typename CoefOf<F64>::type *co;
+        constants(pc, co);
+        const float4 *tbl = FORM == kFormTable ? sp->tbl : nullptr;
+        const float rin2 = FORM == kFormTable ? sp->rin2 : 0.f;
         R fx = 0, fy = 0, fz = 0;
-        // rows w, w + kNW, ...
         auto sweep = [&](auto wrapc) {
-            list_sweep<F64, FORM, WE, decltype(wrapc)::value, DBG>(
-                a, g, pc, co, tbl, rin2, sp, hd, (uint32_t)tt, DBG ? &rec : nullptr, w, kNW, maxcnt,
-                [&](int32_t k) { return entry(k); }, [&](int32_t k) { return k < cnt; }, fx, fy, fz, e);
+            ListCand<F64> pd[kG<F64>];
+#pragma unroll
+            for (int s = 0; s < kG<F64>; ++s) pd[s] = load_cand<F64>(a, w + s * W < cnt ? en[s] : 0u);
+            // rows while some home of the wave has a pair in them
+            bool have = w < cnt;
+            for (int32_t k = w; ballot(have);) {
+#pragma unroll
+                for (int s = 0; s < kE; ++s) {
+                    const ListCand<F64> cur = pd[s % kG<F64>];
+                    const uint32_t ce = en[s];
+                    pd[s % kG<F64>] = load_cand<F64>(a, k + kG<F64> * W < cnt ? en[(s + kG<F64>) % kE] : 0u);
+                    en[s] = entry(k + kE * W);
+                    list_pair<F64, FORM, WE, decltype(wrapc)::value, DBG>(a, g, pc, co, tbl, rin2, sp, hd,
+                                                                         DBG ? &rec : nullptr, ce, have, cur, fx, fy,
+                                                                         fz, e);
+                    k += W;
+                    have = k < cnt;
+                    if (!ballot(have)) break;
+                }
+            }
         };
-        if (F64 && !ballot(!inner(hd))) sweep(std::false_type{});
+        if (F64 && !ballot(!inner(g, hd))) sweep(std::false_type{});
         else sweep(std::bool_constant<F64>{});
+        const double es = WE ? wave_sum(e) : 0.0;
         pf[w][0][lane] = fx;
         pf[w][1][lane] = fy;
         pf[w][2][lane] = fz;
-        const double es = WE ? wave_sum(e) : 0.0;
         if (lane == 0) es_w[w] = es;
         __syncthreads();
         if (w == 0 && home) {
@@ -1313,7 +1368,11 @@ __global__ __launch_bounds__(64 * kNW) void k_near_list(EvalArgs a, const ListIt
                                    (double)pf[3][d][lane];
         }
     }
-    if (threadIdx.x == 0) a.epart[it] = ((es_w[0] + es_w[1]) + es_w[2]) + es_w[3];
+    if (threadIdx.x == 0) {
+        double es = es_w[0];
+        for (int v = 1; v < W; ++v) es += es_w[v];
+        a.epart[it] = es;
+    }
 }
 
 template <bool F64>
@@ -1742,9 +1801,8 @@ void launch_near_cells(const EvalArgs &a, bool f64, const NearItem *items, int32
 
 void launch_near(const EvalArgs &a, bool f64, const ListItem *items, int32_t nitems, hipStream_t s) {
     // one item per block
-    int32_t nblk = (nitems + 7) / 8 * 8;
-    if (nblk < 8) nblk = 8;
-    dim3 grid((unsigned)nblk), block(64 * kNW);
+    const int32_t nblk = std::max((nitems + 7) / 8 * 8, 8);
+    const dim3 grid((unsigned)nblk), block(64 * (!a.list_hm ? kNW : f64 ? kHmWaves<true> : kHmWaves<false>));
     // one instantiation per form, layout and energy flag: each keeps its own
     // constants in registers, with no test of them in its loop
     using std::bool_constant;

@@ -162,6 +162,7 @@ struct NearItem {
 // wave each.
 constexpr int kListHomes = 64;
 constexpr int kListWaves = 4;
+constexpr int64_t kListPad = 32 * kListHomes;  // entries allocated past the last item (the list pass reads ahead)
 struct ListItem {
     int32_t sys;
     int32_t pad;
