@@ -233,7 +233,6 @@ struct rbsog_ctx {
     ChainState *chains = nullptr;
     int32_t *flag = nullptr;
     uint32_t *sys_done = nullptr;
-    uint32_t *bin_done = nullptr;
     // transfers: first non-finite particle of one (device), and pinned host
     // memory: the status block that kernels write, then kPinBytes at most of
     // staging for small transfers
@@ -624,7 +623,6 @@ EvalArgs make_args(rbsog_ctx *c, bool stepping, double dt) {
     a.dipole = c->dipole;
     a.flag = c->flag;
     a.sys_done = c->sys_done;
-    a.bin_done = c->bin_done;
     a.kick = stepping ? 1 : 0;
     a.energy = 1;
     a.hdm = 0.5 * dt / c->mass;
@@ -705,14 +703,22 @@ rbsog_status enqueue_eval(rbsog_ctx *c, bool stepping, double dt, bool kinetic, 
             TRY(timed_on(c, K_FARSIDE, c->side, [&] { launch_far_side(a, f64, c->far_items, c->n_far, fb, c->side); }));
         HIPCHK(c, hipEventRecord(c->ev_join, c->side));
     }
-    if (!a.always_build) TRY(timed(c, K_BIN, [&] { launch_bin_scan(a, s); }));
-    else TRY(timed(c, K_SCAN, [&] { launch_scan(a, s); }));
-    TRY(timed(c, K_SCATTER, [&] { launch_cell_scatter(a, s); }));
-    TRY(timed(c, K_SORTG, [&] { launch_sort_gather(a, s); }));
+    // steps of a small batch on a kept list re-sort in one kernel (few of them
+    // build); an evaluation that the host has asked to build takes the kernels
+    // that use the whole device
+    const bool one = stepping && !a.always_build && resort_in_one(a);
+    if (one) {
+        TRY(timed(c, K_SORTG, [&] { launch_resort_one(a, s); }));
+    } else {
+        if (!a.always_build) TRY(timed(c, K_BIN, [&] { launch_bin(a, s); }));
+        if (scan_apart(a)) TRY(timed(c, K_SCAN, [&] { launch_scan(a, s); }));
+        TRY(timed(c, K_SCATTER, [&] { launch_cell_scatter(a, s); }));
+        TRY(timed(c, K_SORTG, [&] { launch_sort_gather(a, s); }));
+    }
     if (a.always_build) {
         TRY(timed(c, K_NEARC, [&] { launch_near_cells(a, f64, c->near_items, c->n_near, c->cell_slots, s); }));
     } else {
-        TRY(timed(c, K_LIST, [&] { launch_list_build(a, f64, c->list_items, c->n_list, c->build_slots, s); }));
+        TRY(timed(c, K_LIST, [&] { launch_list_build(a, f64, c->list_items, c->n_list, c->build_slots, s, !one); }));
         TRY(timed(c, K_NEAR, [&] { launch_near(a, f64, c->list_items, c->n_list, s); }));
     }
     if (fork) {
@@ -1507,7 +1513,8 @@ rbsog_status autotune_now(rbsog_ctx *c, int32_t reps) {
     // already, so the re-sort is the identity), its near kernel with `slots`
     auto build = [&]() {
         EvalArgs a = make_args(c, false, 0.0);
-        launch_bin_scan(a, st);
+        launch_bin(a, st);
+        if (scan_apart(a)) launch_scan(a, st);
         launch_cell_scatter(a, st);
         launch_sort_gather(a, st);
         return a;
@@ -1738,7 +1745,8 @@ rbsog_status first_build(rbsog_ctx *c) {
     a.icap = 0;
     hipStream_t s = c->stream;
     launch_kdq(a, s);
-    launch_bin_scan(a, s);
+    launch_bin(a, s);
+    if (scan_apart(a)) launch_scan(a, s);
     launch_cell_scatter(a, s);
     launch_sort_gather(a, s);
     launch_list_build(a, c->prec == RBSOG_FP64, c->list_items, c->n_list, c->build_slots, s);
@@ -1918,7 +1926,6 @@ rbsog_status init_batch(rbsog_ctx **out, int32_t nsys, const int64_t *offsets, c
     ALLOC(dipole, 3 * (int64_t)nsys);
     ALLOC(flag, 1);
     ALLOC(sys_done, nsys);
-    ALLOC(bin_done, 1);
     ALLOC(bad, 1);
     c->pin_bytes = std::min<int64_t>(kPinBytes, std::max<int64_t>(4096, 48 * N + 32 * (int64_t)nsys));
     if (hipHostMalloc((void **)&c->stat, 256 + (size_t)c->pin_bytes, hipHostMallocDefault) != hipSuccess) {
@@ -1991,14 +1998,14 @@ rbsog_status init_batch(rbsog_ctx **out, int32_t nsys, const int64_t *offsets, c
                   hipMemcpy(c->kcur, zc.data(), nsys * sizeof(int64_t), hipMemcpyHostToDevice) == hipSuccess &&
                   hipMemcpy(c->tstep, zc.data(), sizeof(int64_t), hipMemcpyHostToDevice) == hipSuccess &&
                   hipMemcpy(c->sys_done, zu.data(), nsys * sizeof(uint32_t), hipMemcpyHostToDevice) == hipSuccess &&
-                  hipMemset(c->bin_done, 0, sizeof(uint32_t)) == hipSuccess &&
                   hipMemcpy(c->bad, &none, sizeof none, hipMemcpyHostToDevice) == hipSuccess &&
                   hipMemcpy(c->kin, std::vector<double>(nsys, 0.0).data(), nsys * sizeof(double),
                             hipMemcpyHostToDevice) == hipSuccess &&
                   hipMemcpy(c->nh_xi, std::vector<double>(nsys, 0.0).data(), nsys * sizeof(double),
                             hipMemcpyHostToDevice) == hipSuccess &&
                   hipMemcpy(c->flag, &zf, sizeof zf, hipMemcpyHostToDevice) == hipSuccess &&
-                  hipMemset(c->cell_count, 0, (size_t)C * sizeof(int32_t)) == hipSuccess;
+                  hipMemset(c->cell_count, 0, (size_t)C * sizeof(int32_t)) == hipSuccess &&
+                  hipMemset(c->cell_fill, 0, (size_t)C * sizeof(int32_t)) == hipSuccess;
         if (!ok) {
             fail(c, RBSOG_E_DEVICE, "initial upload failed");
             return bail(RBSOG_E_DEVICE);

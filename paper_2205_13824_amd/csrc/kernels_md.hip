@@ -140,8 +140,9 @@ __global__ __launch_bounds__(kBlock) void k_kdq(EvalArgs a) {
 
 // ---- exclusive scan of int32 counts: 1024 elements per block --------------
 
+template <int BLOCK = kBlock>
 __device__ int32_t block_exclusive_scan(int32_t v, int32_t *total) {
-    __shared__ int32_t wsum[kBlock / 64];
+    __shared__ int32_t wsum[BLOCK / 64];
     int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     int32_t incl = v;
     for (int o = 1; o < 64; o <<= 1) {
@@ -151,7 +152,7 @@ __device__ int32_t block_exclusive_scan(int32_t v, int32_t *total) {
     if (lane == 63) wsum[wid] = incl;
     __syncthreads();
     int32_t base = 0, tot = 0;
-    for (int w = 0; w < kBlock / 64; ++w) {
+    for (int w = 0; w < BLOCK / 64; ++w) {
         if (w < wid) base += wsum[w];
         tot += wsum[w];
     }
@@ -160,68 +161,70 @@ __device__ int32_t block_exclusive_scan(int32_t v, int32_t *total) {
     return base + incl - v;
 }
 
-// Exclusive scan of the counts of n cells by one block (few cells): each
-// thread sums a contiguous run, the block scans the run totals, each thread
-// writes its run's starts (cell_start, and the scatter's fill counters), and
-// out[n] = the total.
-__device__ void scan_counts_block(const int32_t *in, int64_t n, int32_t *out, int32_t *fill) {
-    const int64_t per = (n + kBlock - 1) / kBlock;
-    const int64_t b = (int64_t)threadIdx.x * per;
-    const int64_t e = b + per < n ? b + per : n;
-    int32_t sum = 0;
-    for (int64_t c = b; c < e; ++c) sum += in[c];
-    int32_t tot;
-    int32_t off = block_exclusive_scan(sum, &tot);
-    for (int64_t c = b; c < e; ++c) {
-        const int32_t v = in[c];
-        out[c] = off;
-        fill[c] = off;
-        off += v;
+// The kernels of a list build run at every evaluation with a kept list and
+// return at once unless a build is due, so their blocks are large and few:
+// kBuildThreads threads, at most kBuildGrid blocks (two per CU) that stride.
+constexpr int kBuildThreads = 1024;
+constexpr int64_t kBuildGrid = 512;
+
+// Exclusive scan of the counts of n cells by one block, tile after tile of four
+// counts per thread: the cells' starts, the scatter's fill counters, and
+// out[n] = the total.  (The last block of the bin pass did this before, after a
+// device-scope fence in every block; each fence writes back its XCD's L2:
+// 77,781 ions 55 us, 331,776 sites 350 us a build.)
+__global__ __launch_bounds__(kBuildThreads) void k_scan_one(const int32_t *__restrict__ in, int64_t n,
+                                                            int32_t *__restrict__ out, int32_t *__restrict__ fill,
+                                                            const int32_t *__restrict__ cond) {
+    __builtin_amdgcn_s_setprio(2);
+    if (!*cond) return;
+    int32_t before = 0;
+    for (int64_t c0 = 0; c0 < n; c0 += 4 * kBuildThreads) {
+        const int64_t c = c0 + 4 * (int64_t)threadIdx.x;
+        int32_t v[4], sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = c + k < n ? in[c + k] : 0;
+            sum += v[k];
+        }
+        int32_t tot;
+        int32_t off = before + block_exclusive_scan<kBuildThreads>(sum, &tot);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (c + k < n) {
+                out[c + k] = off;
+                fill[c + k] = off;
+                off += v[k];
+            }
+        before += tot;
     }
-    if (threadIdx.x == 0) out[n] = tot;
+    if (threadIdx.x == 0) out[n] = before;
 }
 
-// Cell c_d = (u n_d) >> 32 of each particle and the cell histogram.  SCAN
-// (few cells): the last block to finish also scans the counts (the scan
-// kernels are not launched).
-template <bool SCAN>
-__global__ __launch_bounds__(kBlock) void k_bin(EvalArgs a) {
+// Cell c_d = (u n_d) >> 32 of slot t.
+__device__ __forceinline__ int64_t cell_at(const EvalArgs &a, int64_t t) {
+    const SysDev &sd = a.sys[a.sys_of[t]];
+    int64_t c[3];
+    int32_t nc[3];
+    for (int d = 0; d < 3; ++d) {
+        nc[d] = sd.g.nc[d];
+        c[d] = (int64_t)(((uint64_t)a.u_tmp[d * a.N + t] * (uint64_t)nc[d]) >> 32);
+    }
+    return sd.c0 + c[0] + (int64_t)nc[0] * (c[1] + (int64_t)nc[1] * c[2]);
+}
+
+// Cell of each particle and the cell histogram.
+__global__ __launch_bounds__(kBuildThreads) void k_bin(EvalArgs a) {
     // the critical path's waves ahead of the structure factor's beside them
     __builtin_amdgcn_s_setprio(2);
     if (!*a.rebuild) return;
     const int64_t N = a.N;
-    // grid-stride over blocks of kBlock slots (the grid is capped: on the
-    // steps that do not build, few blocks return at once)
-    for (int64_t base = (int64_t)blockIdx.x * kBlock; base < N; base += (int64_t)gridDim.x * kBlock) {
+    for (int64_t base = (int64_t)blockIdx.x * kBuildThreads; base < N; base += (int64_t)gridDim.x * kBuildThreads) {
         const int64_t t0 = base + threadIdx.x;
         const bool valid = t0 < N;
         const int64_t t = valid ? t0 : N - 1;
-        const SysDev &sd = a.sys[a.sys_of[t]];
-        int64_t c[3];
-        int32_t nc[3];
-        for (int d = 0; d < 3; ++d) {
-            nc[d] = sd.g.nc[d];
-            c[d] = (int64_t)(((uint64_t)a.u_tmp[d * N + t] * (uint64_t)nc[d]) >> 32);
-        }
-        const int64_t cell = sd.c0 + c[0] + (int64_t)nc[0] * (c[1] + (int64_t)nc[1] * c[2]);
+        const int64_t cell = cell_at(a, t);
         if (valid) a.cell_of[t] = (int32_t)cell;
         run_atomic_add(a.cell_count, cell, valid);
-    }
-    if constexpr (SCAN) {
-        // one device-scope fence per block (it writes the XCD's L2 back),
-        // after the block's barrier
-        __shared__ int32_t last;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            __threadfence();
-            last = atomicAdd(a.bin_done, 1u) == gridDim.x - 1 ? 1 : 0;
-        }
-        __syncthreads();
-        if (!last) return;
-        // every block's counts are in: scan them, then re-arm the counter
-        __threadfence();
-        scan_counts_block(a.cell_count, a.C, a.cell_start, a.cell_fill);
-        if (threadIdx.x == 0) *a.bin_done = 0u;
     }
 }
 
@@ -278,136 +281,328 @@ __global__ void k_scan_apply(const int32_t *__restrict__ in, int64_t n, const in
 }
 
 // Each particle to a slot of its cell (atomic order), with its id beside it
-// for the per-cell sort.
-__global__ __launch_bounds__(kBlock) void k_cell_scatter(int64_t N, const int32_t *__restrict__ cell_of,
-                                                         const int32_t *__restrict__ id, int32_t *__restrict__ fill,
-                                                         int32_t *__restrict__ src, int32_t *__restrict__ skey,
-                                                         const int32_t *__restrict__ cond) {
+// for the per-cell sort.  With SCAN each block scans the cell counts for itself
+// (up to kScanLds of them, kept in LDS: a launch less, 27,000 ions 43.6 us a step
+// against 47) and the fill counters start at zero; otherwise they start at the
+// scan kernels' cell starts.
+constexpr int kScanLds = 12 * kBuildThreads;
+template <bool SCAN>
+__global__ __launch_bounds__(kBuildThreads) void k_cell_scatter(EvalArgs a) {
     // the critical path's waves ahead of the structure factor's beside them
     __builtin_amdgcn_s_setprio(2);
-    if (!*cond) return;
+    if (!*a.rebuild) return;
+    __shared__ int32_t start[SCAN ? kScanLds : 1];
+    const int64_t N = a.N;
+    if constexpr (SCAN) {
+        const int32_t C = (int32_t)a.C;
+        for (int32_t c = threadIdx.x; c < C; c += kBuildThreads) start[c] = a.cell_count[c];
+        __syncthreads();
+        const int32_t per = (C + kBuildThreads - 1) / kBuildThreads, at = (int32_t)threadIdx.x * per;
+        const int32_t b = at < C ? at : C, e = b + per < C ? b + per : C;
+        int32_t sum = 0, tot;
+        for (int32_t c = b; c < e; ++c) sum += start[c];
+        int32_t off = block_exclusive_scan<kBuildThreads>(sum, &tot);
+        for (int32_t c = b; c < e; ++c) {
+            const int32_t v = start[c];
+            start[c] = off;
+            off += v;
+        }
+        __syncthreads();
+        if (blockIdx.x == 0) {
+            for (int32_t c = threadIdx.x; c < C; c += kBuildThreads) a.cell_start[c] = start[c];
+            if (threadIdx.x == 0) a.cell_start[C] = tot;
+        }
+    }
     // grid-stride as in k_bin (the order of the atomics within a cell is
     // undone by the per-cell id sort)
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < N; base += (int64_t)gridDim.x * blockDim.x) {
         const int64_t t = base + threadIdx.x;
         const bool valid = t < N;
-        const int32_t cell = valid ? cell_of[t] : 0;
-        const int32_t key = valid ? id[t] : 0;
-        const int32_t dst = run_atomic_add(fill, cell, valid);
+        const int32_t cell = valid ? a.cell_of[t] : 0;
+        const int32_t key = valid ? a.cur.id[t] : 0;
+        int32_t dst = run_atomic_add(a.cell_fill, cell, valid);
         if (valid) {
-            src[dst] = (int32_t)t;
-            skey[dst] = key;
+            if constexpr (SCAN) dst += start[cell];
+            a.src[dst] = (int32_t)t;
+            a.skey[dst] = key;
         }
     }
 }
 
 // Per cell: order of its slots by particle id (the order becomes (cell, id),
-// independent of the scatter's atomic order), and reset of its histogram
-// count for the next evaluation; then the block gathers the state of its
+// independent of the scatter's atomic order), and reset of its histogram and
+// fill counts for the next evaluation; then the block gathers the state of its
 // cells' slots into `nxt` in the new order, one thread per slot (writes are
 // coalesced, reads stay close: particles move little between builds).  The
-// positions become the new list reference `u`.  Cells of up to kRankMax
-// particles load their keys at once and rank them in registers; larger cells
-// take an insertion sort in memory.
+// positions become the new list reference `u`.  A slot's place is the number
+// of smaller ids in its cell.  Up to kRankMax particles: one thread per cell,
+// its keys in registers.  More (water-shaped sites at r_c = 10: about 150 a
+// cell): one wave per cell, a slot per lane, every key broadcast; an insertion
+// sort by one thread took 2 ms a build there.
+// CELLS: cells per block, 256 (one thread each, larger ones left to the
+// waves) or 16 (one wave each).
 constexpr int kRankMax = 16;
 
-constexpr int kSortCells = 64;  // cells per block of the sort and gather
+// Slots [lo, hi) of one cell ordered by a wave.
+__device__ __forceinline__ void sort_cell_wave(const int32_t *__restrict__ src, const int32_t *__restrict__ skey,
+                                               int32_t *__restrict__ out, int32_t lo, int32_t hi, int lane) {
+    for (int32_t i0 = lo; i0 < hi; i0 += 64) {
+        const int32_t i = i0 + lane;
+        const int32_t key = i < hi ? skey[i] : INT32_MAX, v = i < hi ? src[i] : 0;
+        int32_t rank = 0;
+        for (int32_t j0 = lo; j0 < hi; j0 += 64) {
+            const int32_t kj = j0 + lane < hi ? skey[j0 + lane] : INT32_MAX;
+            const int m = hi - j0 < 64 ? hi - j0 : 64;
+            for (int j = 0; j < m; ++j) rank += __builtin_amdgcn_readlane(kj, j) < key ? 1 : 0;
+        }
+        if (i < hi) out[lo + rank] = v;
+    }
+}
 
-__global__ __launch_bounds__(kBlock) void k_sort_gather(EvalArgs a) {
+// Slots [lo, lo + cnt) of one cell, cnt <= kRankMax, ordered by a thread.
+__device__ __forceinline__ void sort_cell_thread(const int32_t *__restrict__ src, const int32_t *__restrict__ skey,
+                                                 int32_t *__restrict__ out, int32_t lo, int32_t cnt) {
+    int32_t sv[kRankMax], key[kRankMax];
+#pragma unroll
+    for (int i = 0; i < kRankMax; ++i) {
+        sv[i] = i < cnt ? src[lo + i] : 0;
+        key[i] = i < cnt ? skey[lo + i] : INT32_MAX;
+    }
+#pragma unroll
+    for (int i = 0; i < kRankMax; ++i) {
+        int32_t rank = 0;
+#pragma unroll
+        for (int j = 0; j < kRankMax; ++j) rank += key[j] < key[i] ? 1 : 0;
+        if (i < cnt) out[lo + rank] = sv[i];
+    }
+}
+
+// Slots [k0, k1) of the new order gathered from the state by a block: two
+// slots per thread and pass, all loads issued before the stores.
+__device__ __forceinline__ void gather_slots(const EvalArgs &a, const int32_t *out, int64_t k0, int64_t k1) {
+    const int64_t N = a.N;
+    constexpr int U = 2;
+    for (int64_t kb = k0 + threadIdx.x; kb < k1; kb += U * kBuildThreads) {
+        int64_t tt[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) tt[j] = kb + j * kBuildThreads < k1 ? out[kb + j * kBuildThreads] : -1;
+        double xv[U][3], vv[U][3], qv[U];
+        uint32_t uv[U][3];
+        float qfv[U];
+        int32_t idv[U], cv[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int64_t t = tt[j] < 0 ? 0 : tt[j];
+            for (int d = 0; d < 3; ++d) {
+                xv[j][d] = a.cur.x[d * N + t];
+                vv[j][d] = a.cur.v[d * N + t];
+                uv[j][d] = a.u_tmp[d * N + t];
+            }
+            qv[j] = a.cur.q[t];
+            qfv[j] = a.cur.qf[t];
+            idv[j] = a.cur.id[t];
+            cv[j] = a.cell_of[t];
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int64_t k = kb + j * kBuildThreads;
+            if (tt[j] < 0) continue;
+            for (int d = 0; d < 3; ++d) {
+                a.nxt.x[d * N + k] = xv[j][d];
+                a.nxt.v[d * N + k] = vv[j][d];
+                a.u[d * N + k] = uv[j][d];
+            }
+            a.nxt.q[k] = qv[j];
+            a.nxt.qf[k] = qfv[j];
+            a.nxt.id[k] = idv[j];
+            a.cell_sorted[k] = cv[j];
+        }
+        if (a.cur.dsp) {
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                if (tt[j] < 0) continue;
+                for (int d = 0; d < 3; ++d) a.nxt.dsp[d * N + kb + j * kBuildThreads] = a.cur.dsp[d * N + tt[j]];
+            }
+        }
+    }
+}
+
+template <int CELLS>
+__global__ __launch_bounds__(kBuildThreads) void k_sort_gather(EvalArgs a) {
     // the critical path's waves ahead of the structure factor's beside them
     __builtin_amdgcn_s_setprio(2);
     if (!*a.rebuild) return;
+    __shared__ int32_t nbig, big[CELLS];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     int32_t *out = a.sorted;
-    // grid-stride over groups of kSortCells cells (the grid is capped)
-    for (int64_t c0 = (int64_t)blockIdx.x * kSortCells; c0 < a.C; c0 += (int64_t)gridDim.x * kSortCells) {
-        const int64_t c = c0 + threadIdx.x;
-        if (threadIdx.x < kSortCells && c < a.C) {
-            const int32_t lo = a.cell_start[c], hi = a.cell_start[c + 1];
-            const int32_t cnt = hi - lo;
-            const int32_t *src = a.src;
-            const int32_t *idc = a.cur.id;
-            if (cnt <= kRankMax) {
-                int32_t sv[kRankMax], key[kRankMax];
-#pragma unroll
-                for (int i = 0; i < kRankMax; ++i) {
-                    sv[i] = i < cnt ? src[lo + i] : 0;
-                    key[i] = i < cnt ? a.skey[lo + i] : INT32_MAX;
-                }
-#pragma unroll
-                for (int i = 0; i < kRankMax; ++i) {
-                    int32_t rank = 0;
-#pragma unroll
-                    for (int j = 0; j < kRankMax; ++j) rank += key[j] < key[i] ? 1 : 0;
-                    if (i < cnt) out[lo + rank] = sv[i];
-                }
-            } else {
-                for (int32_t i = lo; i < hi; ++i) out[i] = src[i];
-                for (int32_t i = lo + 1; i < hi; ++i) {
-                    const int32_t v = out[i];
-                    const int32_t kv = idc[v];
-                    int32_t j = i - 1;
-                    while (j >= lo && idc[out[j]] > kv) {
-                        out[j + 1] = out[j];
-                        --j;
-                    }
-                    out[j + 1] = v;
-                }
+    for (int64_t c0 = (int64_t)blockIdx.x * CELLS; c0 < a.C; c0 += (int64_t)gridDim.x * CELLS) {
+        if constexpr (CELLS == kBuildThreads / 64) {
+            const int64_t c = c0 + wave;
+            if (c < a.C) {
+                sort_cell_wave(a.src, a.skey, out, a.cell_start[c], a.cell_start[c + 1], lane);
+                if (lane == 0) a.cell_count[c] = a.cell_fill[c] = 0;
             }
-            a.cell_count[c] = 0;
+        } else {
+            if (threadIdx.x == 0) nbig = 0;
+            __syncthreads();
+            const int64_t c = c0 + threadIdx.x;
+            if (threadIdx.x < CELLS && c < a.C) {
+                const int32_t lo = a.cell_start[c], cnt = a.cell_start[c + 1] - lo;
+                if (cnt <= kRankMax) {
+                    sort_cell_thread(a.src, a.skey, out, lo, cnt);
+                } else {
+                    big[atomicAdd(&nbig, 1)] = (int32_t)threadIdx.x;
+                }
+                a.cell_count[c] = a.cell_fill[c] = 0;
+            }
+            __syncthreads();
+            for (int k = wave; k < nbig; k += kBuildThreads / 64) {
+                const int64_t cb = c0 + big[k];
+                sort_cell_wave(a.src, a.skey, out, a.cell_start[cb], a.cell_start[cb + 1], lane);
+            }
         }
         // the block's permutation entries are visible to the whole block here
         __syncthreads();
-        const int64_t c1 = c0 + kSortCells < a.C ? c0 + kSortCells : a.C;
-        const int64_t k0 = a.cell_start[c0], k1 = a.cell_start[c1];
-        const int64_t N = a.N;
-        // two slots per thread and pass, all loads issued before the stores
-        constexpr int U = 2;
-        for (int64_t kb = k0 + threadIdx.x; kb < k1; kb += U * kBlock) {
-            int64_t tt[U];
-#pragma unroll
-            for (int j = 0; j < U; ++j) tt[j] = kb + j * kBlock < k1 ? out[kb + j * kBlock] : -1;
-            double xv[U][3], vv[U][3], qv[U];
-            uint32_t uv[U][3];
-            float qfv[U];
-            int32_t idv[U], cv[U];
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const int64_t t = tt[j] < 0 ? 0 : tt[j];
-                for (int d = 0; d < 3; ++d) {
-                    xv[j][d] = a.cur.x[d * N + t];
-                    vv[j][d] = a.cur.v[d * N + t];
-                    uv[j][d] = a.u_tmp[d * N + t];
-                }
-                qv[j] = a.cur.q[t];
-                qfv[j] = a.cur.qf[t];
-                idv[j] = a.cur.id[t];
-                cv[j] = a.cell_of[t];
-            }
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const int64_t k = kb + j * kBlock;
-                if (tt[j] < 0) continue;
-                for (int d = 0; d < 3; ++d) {
-                    a.nxt.x[d * N + k] = xv[j][d];
-                    a.nxt.v[d * N + k] = vv[j][d];
-                    a.u[d * N + k] = uv[j][d];
-                }
-                a.nxt.q[k] = qv[j];
-                a.nxt.qf[k] = qfv[j];
-                a.nxt.id[k] = idv[j];
-                a.cell_sorted[k] = cv[j];
-            }
-            if (a.cur.dsp) {
-#pragma unroll
-                for (int j = 0; j < U; ++j) {
-                    if (tt[j] < 0) continue;
-                    for (int d = 0; d < 3; ++d) a.nxt.dsp[d * N + kb + j * kBlock] = a.cur.dsp[d * N + tt[j]];
-                }
-            }
-        }
+        const int64_t c1 = c0 + CELLS < a.C ? c0 + CELLS : a.C;
+        gather_slots(a, out, a.cell_start[c0], a.cell_start[c1]);
         // the next group's permutation entries are written after every
         // thread has read this group's
         __syncthreads();
+    }
+}
+
+// The whole re-sort of a small batch by one block, in steps on a kept list,
+// where most launches find nothing to do: one launch (some 3 us of a step) in
+// place of four.  Histogram, order and sort stay in LDS, each thread holds its
+// slots' values of an array across a barrier and stores them back in place, and
+// the gather records follow, so that no copy back remains.  Per step of 200
+// (5 builds | 40 builds), one launch against three: 1,000 ions 37.8 | 44 us
+// against 47 | 49, 8,000 ions 38.8 | 48.9 against 44.5 | 50; with twice the slots
+// and the state gathered through memory it lost (16,000 ions 41 | 66 us).
+constexpr int kResortSlots = 8;
+constexpr int kResortMax = kResortSlots * kBuildThreads;
+constexpr int kResortCells = 3072;
+__global__ __launch_bounds__(kBuildThreads) void k_resort_one(EvalArgs a) {
+    __shared__ uint32_t ent[kResortMax];  // (id, slot) by cell
+    __shared__ uint16_t ord[kResortMax];
+    __shared__ int32_t cnt[kResortCells], nbig;
+    __shared__ uint16_t big[kResortMax / kRankMax];
+    static_assert(kResortMax <= 1 << 16 && kResortMax % kRankMax == 0, "ids and slots are packed in 16 bits");
+    __builtin_amdgcn_s_setprio(2);
+    if (!*a.rebuild) return;
+    const int32_t N = (int32_t)a.N, C = (int32_t)a.C, tid = threadIdx.x;
+    for (int32_t c = tid; c < C; c += kBuildThreads) cnt[c] = 0;
+    if (tid == 0) nbig = 0;
+    __syncthreads();
+    int32_t cell[kResortSlots], at[kResortSlots], src[kResortSlots];
+    uint32_t key[kResortSlots];
+#pragma unroll
+    for (int i = 0; i < kResortSlots; ++i) {
+        const int32_t t = tid + i * kBuildThreads, tc = t < N ? t : 0;
+        cell[i] = (int32_t)cell_at(a, tc);
+        key[i] = (uint32_t)a.cur.id[tc] << 16 | (uint32_t)t;
+    }
+#pragma unroll
+    for (int i = 0; i < kResortSlots; ++i) {
+        const int32_t t = tid + i * kBuildThreads;
+        if (t >= N) continue;
+        at[i] = atomicAdd(&cnt[cell[i]], 1);
+        a.cell_of[t] = cell[i];
+    }
+    __syncthreads();
+    {  // each thread scans a run of cells
+        const int32_t per = (C + kBuildThreads - 1) / kBuildThreads;
+        const int32_t b = tid * per < C ? tid * per : C, e = b + per < C ? b + per : C;
+        int32_t sum = 0, tot;
+        for (int32_t c = b; c < e; ++c) sum += cnt[c];
+        int32_t off = block_exclusive_scan<kBuildThreads>(sum, &tot);
+        for (int32_t c = b; c < e; ++c) {
+            const int32_t v = cnt[c];
+            cnt[c] = off;
+            a.cell_start[c] = off;
+            off += v;
+        }
+        if (tid == 0) a.cell_start[C] = N;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kResortSlots; ++i)
+        if (tid + i * kBuildThreads < N) ent[cnt[cell[i]] + at[i]] = key[i];
+    __syncthreads();
+    for (int32_t c = tid; c < C; c += kBuildThreads) {
+        const int32_t lo = cnt[c], n = (c + 1 < C ? cnt[c + 1] : N) - lo;
+        if (n > kRankMax) {
+            big[atomicAdd(&nbig, 1)] = (uint16_t)c;
+            continue;
+        }
+        uint32_t v[kRankMax];
+#pragma unroll
+        for (int i = 0; i < kRankMax; ++i) v[i] = i < n ? ent[lo + i] : UINT32_MAX;
+#pragma unroll
+        for (int i = 0; i < kRankMax; ++i) {
+            int32_t rank = 0;
+#pragma unroll
+            for (int j = 0; j < kRankMax; ++j) rank += v[j] < v[i] ? 1 : 0;
+            if (i < n) ord[lo + rank] = (uint16_t)v[i];
+        }
+    }
+    __syncthreads();
+    for (int32_t k = tid >> 6; k < nbig; k += kBuildThreads / 64) {
+        const int32_t c = big[k], lo = cnt[c], hi = c + 1 < C ? cnt[c + 1] : N;
+        for (int32_t i = lo + (tid & 63); i < hi; i += 64) {
+            const uint32_t v = ent[i];
+            int32_t rank = 0;
+            for (int32_t j = lo; j < hi; ++j) rank += ent[j] < v ? 1 : 0;
+            ord[lo + rank] = (uint16_t)v;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kResortSlots; ++i) src[i] = tid + i * kBuildThreads < N ? ord[tid + i * kBuildThreads] : 0;
+    // charges, ids, cells and quantised coordinates, then the FP64 vectors one by one
+    {
+        double q[kResortSlots];
+        float qf[kResortSlots];
+        int32_t id[kResortSlots], cs[kResortSlots];
+        uint32_t u[kResortSlots][3];
+#pragma unroll
+        for (int i = 0; i < kResortSlots; ++i) {
+            q[i] = a.cur.q[src[i]];
+            qf[i] = a.cur.qf[src[i]];
+            id[i] = a.cur.id[src[i]];
+            cs[i] = a.cell_of[src[i]];
+            for (int d = 0; d < 3; ++d) u[i][d] = a.u_tmp[(int64_t)d * N + src[i]];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kResortSlots; ++i) {
+            const int32_t k = tid + i * kBuildThreads;
+            if (k >= N) continue;
+            a.cur.q[k] = q[i];
+            a.cur.qf[k] = qf[i];
+            a.cur.id[k] = id[i];
+            a.cell_sorted[k] = cs[i];
+            for (int d = 0; d < 3; ++d) a.u[(int64_t)d * N + k] = a.u_tmp[(int64_t)d * N + k] = u[i][d];
+            if (a.pk) a.pk[k] = make_uint4(u[i][0], u[i][1], u[i][2], __float_as_uint(qf[i]));
+        }
+    }
+    double *const rows[3] = {a.cur.x, a.cur.v, a.cur.dsp};
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+        double *__restrict__ p = rows[f];
+        if (!p) continue;
+        double r[kResortSlots][3];
+#pragma unroll
+        for (int i = 0; i < kResortSlots; ++i)
+            for (int d = 0; d < 3; ++d) r[i][d] = p[(int64_t)d * N + src[i]];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kResortSlots; ++i) {
+            const int32_t k = tid + i * kBuildThreads;
+            if (k >= N) continue;
+            for (int d = 0; d < 3; ++d) p[(int64_t)d * N + k] = r[i][d];
+            if (f == 0 && a.pkx) a.pkx[k] = PosQ64{r[i][0], r[i][1], r[i][2], a.cur.q[k]};
+        }
     }
 }
 
@@ -452,27 +647,29 @@ void launch_kdq(const EvalArgs &a, hipStream_t s) {
 
 int64_t scan_blocksums_size(int64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
 
-// Grids of the list-build kernels that stride: a step without a build
-// dispatches this many blocks at most, each returning at once.
-constexpr int64_t kBuildGrid = 2048;
-inline unsigned capped(int64_t blocks) { return (unsigned)(blocks < kBuildGrid ? (blocks < 1 ? 1 : blocks) : kBuildGrid); }
-
-// Cell counts scanned by the last block of the bin pass up to this many
-// cells (one block reads them twice); above, by the two scan kernels.
-constexpr int64_t kScanInBin = 65536;
-
-void launch_bin_scan(const EvalArgs &a, hipStream_t s) {
-    const dim3 grid(capped(grid_for(a.N, kBlock)));
-    if (a.C <= kScanInBin) {
-        hipLaunchKernelGGL(k_bin<true>, grid, dim3(kBlock), 0, s, a);
-    } else {
-        hipLaunchKernelGGL(k_bin<false>, grid, dim3(kBlock), 0, s, a);
-        launch_scan(a, s);
-    }
+inline unsigned build_grid(int64_t blocks) {
+    return (unsigned)(blocks < kBuildGrid ? (blocks < 1 ? 1 : blocks) : kBuildGrid);
 }
+
+// More cells than the scatter scans for itself: scanned by one block up to this
+// many (its 17 tiles at 68,921 cells take about 20 us of the one evaluation in
+// some thirty that builds, and one launch instead of two on all others), by two
+// kernels above and where every evaluation builds.
+constexpr int64_t kScanOne = 131072;
+
+void launch_bin(const EvalArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL(k_bin, dim3(build_grid(grid_for(a.N, kBuildThreads))), dim3(kBuildThreads), 0, s, a);
+}
+
+bool scan_apart(const EvalArgs &a) { return a.C > kScanLds; }
 
 void launch_scan(const EvalArgs &a, hipStream_t s) {
     const int64_t n = a.C;
+    if (n <= kScanOne && !a.always_build) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kBuildThreads), 0, s, a.cell_count, n, a.cell_start, a.cell_fill,
+                           (const int32_t *)a.rebuild);
+        return;
+    }
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
     hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(kBlock), 0, s, a.cell_count, n, a.blocksums,
                        (const int32_t *)a.rebuild);
@@ -481,12 +678,24 @@ void launch_scan(const EvalArgs &a, hipStream_t s) {
 }
 
 void launch_cell_scatter(const EvalArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(k_cell_scatter, dim3(capped(grid_for(a.N, kBlock))), dim3(kBlock), 0, s, a.N, a.cell_of, a.cur.id,
-                       a.cell_fill, a.src, a.skey, (const int32_t *)a.rebuild);
+    const dim3 grid(build_grid(grid_for(a.N, kBuildThreads))), block(kBuildThreads);
+    if (scan_apart(a)) hipLaunchKernelGGL(k_cell_scatter<false>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(k_cell_scatter<true>, grid, block, 0, s, a);
+}
+
+// Batches that k_resort_one takes.
+bool resort_in_one(const EvalArgs &a) { return a.N <= kResortMax && a.C <= kResortCells; }
+
+void launch_resort_one(const EvalArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL(k_resort_one, dim3(1), dim3(kBuildThreads), 0, s, a);
 }
 
 void launch_sort_gather(const EvalArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(k_sort_gather, dim3(capped(grid_for(a.C, kSortCells))), dim3(kBlock), 0, s, a);
+    // one wave per cell where cells hold more than a thread ranks
+    if (a.N > kRankMax * a.C)
+        hipLaunchKernelGGL(k_sort_gather<16>, dim3(build_grid(grid_for(a.C, 16))), dim3(kBuildThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_sort_gather<256>, dim3(build_grid(grid_for(a.C, 256))), dim3(kBuildThreads), 0, s, a);
 }
 
 }  // namespace rbsog

@@ -262,7 +262,6 @@ struct EvalArgs {
     int32_t dbg_cap;
     int32_t *dbg_kind;
     uint32_t *sys_done;    // per-system counters of the energy sums' blocks (re-armed to 0)
-    uint32_t *bin_done;    // blocks of the bin pass done (its last block scans the counts; re-armed to 0)
     // velocity-Verlet
     int32_t kick;          // nonzero: kick + drift before, kick after
     double hdm, dt;
@@ -394,15 +393,20 @@ void launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 void launch_kdq(const EvalArgs &a, hipStream_t s);
 // The list build: each of these returns at once unless *a.rebuild is set.
 // Cell of each particle and the histogram, then the exclusive scan of the
-// counts (by the bin pass's last block when the cells are few, else by the
-// scan kernels); the scan alone (the kick/drift kernel made the histogram);
+// counts (by one block, or two kernels where there are many cells); the scan
+// alone (the kick/drift kernel made the histogram);
 // scatter into cells; per cell: id sort of its segment, reset of its count,
 // gather of the state into `nxt` in the new order
-void launch_bin_scan(const EvalArgs &a, hipStream_t s);
+void launch_bin(const EvalArgs &a, hipStream_t s);
+// the cell counts scanned ahead of the scatter (where it does not scan them itself)
+bool scan_apart(const EvalArgs &a);
 void launch_scan(const EvalArgs &a, hipStream_t s);
 int64_t scan_blocksums_size(int64_t n);
 void launch_cell_scatter(const EvalArgs &a, hipStream_t s);
 void launch_sort_gather(const EvalArgs &a, hipStream_t s);
+// all of the above and the copy back by one block, for small batches
+bool resort_in_one(const EvalArgs &a);
+void launch_resort_one(const EvalArgs &a, hipStream_t s);
 // near and far forces (6 doubles each) of the caller indices ids[0..m) from
 // the current order (slot_of: N int32 of scratch for the inverse permutation)
 void launch_subset_forces(const EvalArgs &a, int64_t m, const int64_t *ids, int32_t *slot_of, double *out,
