@@ -67,9 +67,10 @@ __device__ __forceinline__ int64_t rfl64(int64_t v) {
 // wave vector per lane) for particle stream (w / kt); kt * streams <= 16
 // waves per block.  The block stages kStage particles at a time in LDS (one
 // coalesced load per thread) and sums them (rho_core.h); the streams' sums
-// are added in a fixed order.
+// are added in a fixed order.  Two blocks per CU (64 VGPRs; FP64 at 77 and one
+// block: 300,000 ions x 200 62.7 us against 59.8).
 template <bool F64>
-__global__ __launch_bounds__(1024, F64 ? 1 : 8) void k_rho(EvalArgs a, const RhoItem *__restrict__ items, int32_t nitems) {
+__global__ __launch_bounds__(1024, 8) void k_rho(EvalArgs a, const RhoItem *__restrict__ items, int32_t nitems) {
     __shared__ double2 red[1024];
     __shared__ uint4 st32[F64 ? 1 : kStage];
     __shared__ int2 wcnt[F64 ? 1 : 16];
@@ -190,18 +191,25 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// Record r of system sys (its k-th wave vector) from its rho: rho and the
-// per-k energy stored, and the amplitude-phase records of both forms
-// written.  The cursor still points at the batch.
-__device__ __forceinline__ void write_record(const EvalArgs &a, const SysDev &sd, int32_t sys, int64_t r, int32_t k,
-                                             double re, double im) {
+// A system's k-th wave vector of the batch and its weight (the cursor still
+// points at the batch), requested ahead of the sums.
+struct KVec {
+    int32_t m[3];
+    double w;
+};
+__device__ __forceinline__ KVec batch_vector(const EvalArgs &a, const SysDev &sd, int32_t sys, int32_t k) {
+    const int64_t e = a.kcur[sys] + k;
+    return KVec{{sd.kseq[3 * e], sd.kseq[3 * e + 1], sd.kseq[3 * e + 2]}, sd.kw ? sd.kw[e] : sd.w_rb};
+}
+
+// Record r from its wave vector and rho: rho and the per-k energy stored, and
+// the amplitude-phase records of both forms written.
+__device__ __forceinline__ void write_record(const EvalArgs &a, const SysDev &sd, int64_t r, const KVec &kv, double re,
+                                             double im) {
     a.rho[r] = re;
     a.rho[a.K + r] = im;
-    // the batch's k-th vector of the sequence and its weight (the
-    // cursor moves once every record of the system is reduced)
-    const int64_t e = a.kcur[sys] + k;
-    const int32_t m[3] = {sd.kseq[3 * e], sd.kseq[3 * e + 1], sd.kseq[3 * e + 2]};
-    const double w = sd.kw ? sd.kw[e] : sd.w_rb;
+    const int32_t *m = kv.m;
+    const double w = kv.w;
     a.ek[r] = 0.5 * w * (re * re + im * im);
     // amplitude-phase record: phi = arg(rho) / (2 pi), a = w |rho| k
     const double phi = atan2(im, re) * (1.0 / rmath::kTwoPi);
@@ -235,9 +243,8 @@ __device__ __forceinline__ void write_record(const EvalArgs &a, const SysDev &sd
 
 // The structure factor's reduction.  Per k record r: rho = sum over the
 // system's chunks of the partials (fixed order), the per-k energy
-// 1/2 w |rho|^2, and rho written into the records; then k_rho_finish sums
-// each system's far energy.  U_N and U follow in k_kinetic, after the near
-// part.  Nothing here waits for the near part.  (A last-block finish inside
+// 1/2 w |rho|^2, and rho written into the records.  The energies follow in
+// k_kinetic, after the near part.  Nothing here waits for the near part.  (A last-block finish inside
 // the reduction would need a device-scope fence in every block, a writeback
 // of the XCD's L2 each: 0.3 ms for the 6,400 blocks of a 256-system batch.)
 // k_rho_reduce: one wave per record, four records per block (systems of few
@@ -252,6 +259,7 @@ __global__ __launch_bounds__(256) void k_rho_reduce(EvalArgs a) {
         const int32_t k = (int32_t)(r - sd.k0);
         const double2 *pk = reinterpret_cast<const double2 *>(a.partial) + sd.pofs + (int64_t)k * sd.nch;
         const int32_t nch = sd.nch;
+        const KVec kv = batch_vector(a, sd, sys, k);
         // four independent loads in flight per lane, summed in a fixed order
         double2 v0 = make_double2(0.0, 0.0), v1 = v0, v2 = v0, v3 = v0;
         int32_t c = lane;
@@ -267,7 +275,7 @@ __global__ __launch_bounds__(256) void k_rho_reduce(EvalArgs a) {
         double re = (v0.x + v1.x) + (v2.x + v3.x), im = (v0.y + v1.y) + (v2.y + v3.y);
         re = wave_sum(re);
         im = wave_sum(im);
-        if (lane == 0) write_record(a, sd, sys, r, k, re, im);
+        if (lane == 0) write_record(a, sd, r, kv, re, im);
     }
 }
 
@@ -283,6 +291,7 @@ __global__ __launch_bounds__(256) void k_rho_reduce_block(EvalArgs a) {
     const int32_t k = (int32_t)(r - sd.k0);
     const double2 *pk = reinterpret_cast<const double2 *>(a.partial) + sd.pofs + (int64_t)k * sd.nch;
     const int32_t nch = sd.nch;
+    const KVec kv = batch_vector(a, sd, sys, k);
     double2 v[8];
 #pragma unroll
     for (int h = 0; h < 8; ++h) v[h] = make_double2(0.0, 0.0);
@@ -311,48 +320,38 @@ __global__ __launch_bounds__(256) void k_rho_reduce_block(EvalArgs a) {
     if (threadIdx.x == 0) {
         re = (red[0].x + red[1].x) + (red[2].x + red[3].x);
         im = (red[0].y + red[1].y) + (red[2].y + red[3].y);
-        write_record(a, sd, sys, r, k, re, im);
+        write_record(a, sd, r, kv, re, im);
     }
 }
 
-// Per system, one block, after the reduction: the far energy U* = sum_e
-// ek_e (strided sums, then a fixed tree) with the zero-frequency mode term
-// and its dipole (the chunks' dipole partials, the same way), U_self, and
-// the sequence cursor moved on by P.  A kernel of its own: the records'
-// writes are visible to it without fences.
-__global__ __launch_bounds__(256) void k_rho_finish(EvalArgs a) {
-    __shared__ double si[4][256];
+// Batches with a zero-frequency mode term: per system, one block, the dipole
+// from the chunks' partials (strided sums, then a fixed tree).  A kernel of its
+// own: the chunks' writes are visible to it without fences.
+__global__ __launch_bounds__(256) void k_dipole(EvalArgs a) {
+    __shared__ double si[3][256];
     const int32_t s = blockIdx.x;
     const SysDev &sd = a.sys[s];
-    double us = 0.0;
-    for (int64_t e = threadIdx.x; e < sd.P; e += 256) us += a.ek[sd.k0 + e];
+    if (sd.zmode == 0) return;
     double m[3] = {0.0, 0.0, 0.0};
-    if (sd.zmode != 0)
-        for (int32_t ch = threadIdx.x; ch < sd.nch; ch += 256)
-            for (int d = 0; d < 3; ++d) m[d] += a.dip_part[3 * (sd.choff + ch) + d];
-    si[0][threadIdx.x] = us;
-    si[1][threadIdx.x] = m[0];
-    si[2][threadIdx.x] = m[1];
-    si[3][threadIdx.x] = m[2];
+    for (int32_t ch = threadIdx.x; ch < sd.nch; ch += 256)
+        for (int d = 0; d < 3; ++d) m[d] += a.dip_part[3 * (sd.choff + ch) + d];
+    for (int d = 0; d < 3; ++d) si[d][threadIdx.x] = m[d];
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
         if ((int)threadIdx.x < o)
-            for (int j = 0; j < 4; ++j) si[j][threadIdx.x] += si[j][threadIdx.x + o];
+            for (int d = 0; d < 3; ++d) si[d][threadIdx.x] += si[d][threadIdx.x + o];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        double u0 = 0.0;
-        if (sd.zmode != 0) {
-            const double M[3] = {si[1][0], si[2][0], si[3][0]};
-            for (int d = 0; d < 3; ++d) a.dipole[3 * s + d] = M[d];
-            u0 = sd.zmode == 1 ? sd.zu * (M[0] * M[0] + M[1] * M[1] + M[2] * M[2]) : sd.zu * M[2] * M[2];
-        }
-        // U* holds the far part with the zero-frequency mode term
-        a.E[4 * s + 1] = si[0][0] + u0;
-        a.E[4 * s + 2] = sd.uself;
-        a.kcur[s] += sd.P;
-        if (s == 0 && a.kick && a.thermo) *a.tstep += 1;
-    }
+    if (threadIdx.x < 3) a.dipole[3 * s + threadIdx.x] = si[threadIdx.x][0];
+}
+
+// The last kernel of an evaluation (nothing in it or after it reads the
+// batch's place in the sequence): every system's sequence cursor moved on by P,
+// and the thermostat's noise counter by one step.
+__device__ __forceinline__ void advance_cursors(const EvalArgs &a) {
+    if (!a.advance || blockIdx.x != 0) return;
+    for (int32_t s = threadIdx.x; s < a.nsys; s += blockDim.x) a.kcur[s] += a.sys[s].P;
+    if (threadIdx.x == 0 && a.kick && a.thermo) *a.tstep += 1;
 }
 
 // Records whose phases a wave stages at once in the FP32C far sum.
@@ -360,8 +359,8 @@ constexpr int kFarStage = 256;
 // s_waitcnt lgkmcnt(0) with the other counters left alone (gfx9 encoding)
 constexpr int kWaitLgkm0 = 0xC07F;
 
-// Far force on particle i (the factor -q_i included) from its system's P
-// amplitude-phase records, streamed as uniform loads: one sine per record,
+// Far force on particle i (the factor -q_i included) from `P` amplitude-phase
+// records of its system, streamed as uniform loads: one sine per record,
 // F_i = -q_i sum_e a_e sin(2 pi (phi_e - m_e.s_i)).  Positions and charges
 // from (u, qf) in FP32C (the phase phi - m.u mod 2^32), (x, q) in FP64.
 template <bool F64>
@@ -471,7 +470,30 @@ __device__ __forceinline__ void far_sum(CSys *sp, CRec64 *kb64, CRec32 *kb32, in
                         }
                     }
                 } else {
-                    for (int h = 0; h < cnt; ++h) rec(ld(kb32 + e + h), ph[h], fx, fy, fz);
+                    // a short run: the same, group by group, with the rest
+                    // of up to three records one by one
+                    const int full = cnt & ~(G - 1);
+                    KFar32 r[G];
+                    if (full) {
+#pragma unroll
+                        for (int h = 0; h < G; ++h) r[h] = ld(kb32 + e + h);
+                    }
+                    for (int h4 = 0; h4 < full; h4 += G) {
+                        const ulonglong2 w0 = *(const ulonglong2 *)(ph + h4), w1 = *(const ulonglong2 *)(ph + h4 + 2);
+                        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        const int nx = h4 + G < full ? h4 + G : h4;
+                        KFar32 rn[G];
+#pragma unroll
+                        for (int h = 0; h < G; ++h) rn[h] = ld(kb32 + e + nx + h);
+                        rec(r[0], w0.x, fx, fy, fz);
+                        rec(r[1], w0.y, fx, fy, fz);
+                        rec(r[2], w1.x, fx, fy, fz);
+                        rec(r[3], w1.y, fx, fy, fz);
+#pragma unroll
+                        for (int h = 0; h < G; ++h) r[h] = rn[h];
+                    }
+                    for (int h = full; h < cnt; ++h) rec(ld(kb32 + e + h), ph[h], fx, fy, fz);
                 }
                 Fx += fx; Fy += fy; Fz += fz;
             }
@@ -485,31 +507,38 @@ __device__ __forceinline__ void far_sum(CSys *sp, CRec64 *kb64, CRec32 *kb32, in
 // the zero-frequency mode term, the far force stored, the closing half kick
 // (and the second Nose-Hoover scaling) when stepping, and the kinetic energy
 // of each wave's particles summed across the wave in a fixed order into
-// partial [item * 4 + wave] (k_kinetic adds them up).  FUSE: the next step
+// partial `part` (k_kinetic adds them up).  FUSE: the next step
 // starts here, as the kick/drift kernel would start it: its opening half kick
 // with the same force, its drift, wrap and quantisation, and its
 // displacement check.  Lanes past the item (valid false) hold slot i = t0 and
 // store nothing.
 template <bool FUSE>
-__device__ __forceinline__ void far_finish(const EvalArgs &a, CSys *sp, int32_t sys, int64_t i, bool valid,
-                                           double Fx, double Fy, double Fz, int32_t itx) {
+struct FarEnd {
+    // loaded before the far force is stored (the stores could alias them for
+    // the compiler), or before the far sum
+    double vv[3], fn[3], xs[FUSE ? 3 : 1];
+    uint32_t uref[FUSE ? 3 : 1];
+};
+template <bool FUSE>
+__device__ __forceinline__ FarEnd<FUSE> far_operands(const EvalArgs &a, int64_t i) {
     const int64_t n = a.N;
-    // the velocity and the near force are loaded before the far force is
-    // stored (the stores could alias them for the compiler), so that their
-    // loads overlap the ones before
-    double vv[3] = {a.cur.v[i], a.cur.v[n + i], a.cur.v[2 * n + i]};
-    const double fn[3] = {a.Fn[i], a.Fn[n + i], a.Fn[2 * n + i]};
-    double xs[3], L[3];
-    float hf[3];
-    uint32_t uref[3];
-    if constexpr (FUSE) {
-        for (int d = 0; d < 3; ++d) {
-            xs[d] = a.cur.x[d * n + i];
-            uref[d] = a.u[d * n + i];
-            L[d] = sp->g.L[d];
-            hf[d] = sp->g.hf[d];
+    FarEnd<FUSE> o;
+    for (int d = 0; d < 3; ++d) {
+        o.vv[d] = a.cur.v[d * n + i];
+        o.fn[d] = a.Fn[d * n + i];
+        if constexpr (FUSE) {
+            o.xs[d] = a.cur.x[d * n + i];
+            o.uref[d] = a.u[d * n + i];
         }
     }
+    return o;
+}
+template <bool FUSE>
+__device__ __forceinline__ void far_finish(const EvalArgs &a, CSys *sp, int32_t sys, int64_t i, bool valid,
+                                           double Fx, double Fy, double Fz, int32_t part, const FarEnd<FUSE> &o) {
+    const int64_t n = a.N;
+    double vv[3] = {o.vv[0], o.vv[1], o.vv[2]};
+    const double *fn = o.fn;
     if (sp->zmode != 0) {
         const double qi = a.cur.q[i], c = sp->zf * qi;
         const double *M = a.dipole + 3 * sys;
@@ -546,11 +575,17 @@ __device__ __forceinline__ void far_finish(const EvalArgs &a, CSys *sp, int32_t 
     double ke = valid ? 0.5 * a.mass * ((vv[0] * vv[0] + vv[1] * vv[1]) + vv[2] * vv[2]) : 0.0;
     // the wave's kinetic energy (a fixed butterfly), one partial per wave
     for (int o = 32; o > 0; o >>= 1) ke += __shfl_xor(ke, o, 64);
-    if ((threadIdx.x & 63) == 0) a.kpart[(int64_t)itx * 4 + (threadIdx.x >> 6)] = ke;
+    if ((threadIdx.x & 63) == 0) a.kpart[part] = ke;
     if constexpr (FUSE) {
         // the next step: half kick and drift, the drift kept for the
         // mean-square displacement, then wrap and quantise
-        const double xs0[3] = {xs[0], xs[1], xs[2]};
+        const double xs0[3] = {o.xs[0], o.xs[1], o.xs[2]};
+        double xs[3] = {o.xs[0], o.xs[1], o.xs[2]}, L[3];
+        float hf[3];
+        for (int d = 0; d < 3; ++d) {
+            L[d] = sp->g.L[d];
+            hf[d] = sp->g.hf[d];
+        }
         for (int d = 0; d < 3; ++d) {
             vv[d] += a.hdm * f[d];
             xs[d] += a.dt * vv[d];
@@ -559,7 +594,7 @@ __device__ __forceinline__ void far_finish(const EvalArgs &a, CSys *sp, int32_t 
         if (valid && a.cur.dsp)
             for (int d = 0; d < 3; ++d) a.cur.dsp[d * n + i] += xs[d] - xs0[d];
         uint32_t uq[3];
-        const float d2 = wrap_store(a, i, valid, xs, L, hf, uref, uq);
+        const float d2 = wrap_store(a, i, valid, xs, L, hf, o.uref, uq);
         // one atomic per wave that found a particle past the threshold
         const bool far_ = valid && !(d2 <= sp->g.dthr2_f);
         if (__ballot(far_) != 0ull && (threadIdx.x & 63) == 0) atomicOr(a.rebuild, 1);
@@ -567,28 +602,65 @@ __device__ __forceinline__ void far_finish(const EvalArgs &a, CSys *sp, int32_t 
 }
 
 // Far force and the end of the evaluation, one particle per lane; items are
-// runs of up to 256 slots of one system (grid-stride).  The near-list
-// rebuild flag is cleared here (every kernel of the evaluation that reads it
-// has run), unless the kernel opens the next step (FUSE), whose displacement
-// check sets it: the list pass has cleared it then.
-template <bool F64, bool FUSE>
-__global__ __launch_bounds__(256) void k_far(EvalArgs a, const FarItem *__restrict__ items, int32_t nitems) {
+// runs of up to 256 slots of one system, in groups of 64.  W = 1: a block per
+// item, a wave per group.  W > 1: a block per group, whose W waves share the
+// records (in order; the partial forces meet in LDS, added in wave order) and
+// whose first wave ends the evaluation, its operands requested before the sum:
+// for systems with too few groups to fill the device.
+// The near-list rebuild flag is cleared here (every kernel of the evaluation
+// that reads it has run), unless the kernel opens the next step (FUSE), whose
+// displacement check sets it: the list pass has cleared it then.
+template <bool F64, bool FUSE, int W>
+__global__ __launch_bounds__(W == 1 ? 256 : 64 * W) void k_far(EvalArgs a, const FarItem *__restrict__ items, int32_t nitems,
+                                                               int32_t groups) {
+    constexpr int kWaves = W == 1 ? 4 : W;
     __shared__ double2 turn[F64 ? rmath::kTurnTab : 1];
-    __shared__ uint64_t phs[F64 ? 1 : 4 * kFarStage];  // FP32C: record phases, per wave
+    __shared__ uint64_t phs[F64 ? 1 : kWaves * kFarStage];  // FP32C: record phases, per wave
+    __shared__ double part[W == 1 ? 1 : W][3][W == 1 ? 1 : 64];
     if constexpr (F64) fill_turns(turn);
     if (!FUSE && blockIdx.x == 0 && threadIdx.x == 0 && a.rebuild) *a.rebuild = 0;
-    for (int32_t itx = blockIdx.x; itx < nitems; itx += gridDim.x) {
-        const FarItem item = items[itx];
-        const int32_t sys = rfl(item.sys);
-        CSys *sp = (CSys *)(a.sys + sys);
-        const int64_t t0 = rfl64(item.t0), t1 = rfl64(item.t1);
-        const int64_t i0 = t0 + threadIdx.x;
-        const bool valid = i0 < t1;
-        const int64_t i = valid ? i0 : t0;
-        double Fx, Fy, Fz;
+    advance_cursors(a);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    // W = 1: item = block, group = wave; W > 1: `groups` groups per item
+    const int32_t itx = W == 1 ? (int32_t)blockIdx.x : (int32_t)blockIdx.x / groups;
+    const int32_t grp = W == 1 ? wave : (int32_t)blockIdx.x % groups;
+    if (itx >= nitems) return;
+    const FarItem item = items[itx];
+    const int32_t sys = rfl(item.sys);
+    CSys *sp = (CSys *)(a.sys + sys);
+    const int64_t t0 = rfl64(item.t0), t1 = rfl64(item.t1);
+    const int64_t i0 = t0 + 64 * grp + lane;
+    const bool valid = i0 < t1;
+    const int64_t i = valid ? i0 : t0;
+    uint64_t *ph = phs + (F64 ? 0 : wave * kFarStage);
+    double Fx, Fy, Fz;
+    if constexpr (W == 1) {
         far_sum<F64>(sp, (CRec64 *)(a.kb64 + sp->k0), (CRec32 *)(a.kb32 + sp->k0), sp->P, a.N, i, a.u_tmp,
-                     a.cur.qf, a.cur.x, a.cur.q, turn, phs + (F64 ? 0 : (threadIdx.x >> 6) * kFarStage), Fx, Fy, Fz);
-        far_finish<FUSE>(a, sp, sys, i, valid, Fx, Fy, Fz, itx);
+                     a.cur.qf, a.cur.x, a.cur.q, turn, ph, Fx, Fy, Fz);
+        const FarEnd<FUSE> o = far_operands<FUSE>(a, i);
+        far_finish<FUSE>(a, sp, sys, i, valid, Fx, Fy, Fz, itx * 4 + grp, o);
+    } else {
+        FarEnd<FUSE> o;
+        if (wave == 0) o = far_operands<FUSE>(a, i);
+        // the wave's share of the records, in groups of four
+        const int32_t P = sp->P, per = ((P + 4 * W - 1) / (4 * W)) * 4;
+        const int32_t e0 = wave * per < P ? wave * per : P, cnt = P - e0 < per ? P - e0 : per;
+        Fx = Fy = Fz = 0.0;
+        if (cnt > 0)
+            far_sum<F64>(sp, (CRec64 *)(a.kb64 + sp->k0 + e0), (CRec32 *)(a.kb32 + sp->k0 + e0), cnt, a.N, i, a.u_tmp,
+                         a.cur.qf, a.cur.x, a.cur.q, turn, ph, Fx, Fy, Fz);
+        part[wave][0][lane] = Fx;
+        part[wave][1][lane] = Fy;
+        part[wave][2][lane] = Fz;
+        __syncthreads();
+        if (wave != 0) return;
+#pragma unroll
+        for (int w = 1; w < W; ++w) {
+            Fx += part[w][0][lane];
+            Fy += part[w][1][lane];
+            Fz += part[w][2][lane];
+        }
+        far_finish<FUSE>(a, sp, sys, i, valid, Fx, Fy, Fz, itx * 4 + grp, o);
     }
 }
 
@@ -627,6 +699,7 @@ __global__ __launch_bounds__(256) void k_far_side(EvalArgs a, const FarItem *__r
 __global__ __launch_bounds__(256) void k_far_finish(EvalArgs a, const FarItem *__restrict__ items, int32_t nitems) {
     const int64_t n = a.N;
     if (blockIdx.x == 0 && threadIdx.x == 0 && a.rebuild) *a.rebuild = 0;
+    advance_cursors(a);
     for (int32_t itx = blockIdx.x; itx < nitems; itx += gridDim.x) {
         const FarItem item = items[itx];
         const int32_t sys = rfl(item.sys);
@@ -637,20 +710,22 @@ __global__ __launch_bounds__(256) void k_far_finish(EvalArgs a, const FarItem *_
         const int64_t i = valid ? i0 : t0;
         const int64_t o = a.sorted[i];
         const double Fx = a.Ff_side[o], Fy = a.Ff_side[n + o], Fz = a.Ff_side[2 * n + o];
-        far_finish<false>(a, sp, sys, i, valid, Fx, Fy, Fz, itx);
+        far_finish<false>(a, sp, sys, i, valid, Fx, Fy, Fz, itx * 4 + (int32_t)(threadIdx.x >> 6),
+                          far_operands<false>(a, i));
     }
 }
 
 // Per system, gridDim.x blocks: each sums a contiguous share of the far
 // items' wave partials of the kinetic energy and of the near items' energy
 // partials of the mode in use (eight loads in flight per thread, a fixed
-// tree across the block); with one block it finishes alone, else the last
+// tree across the block), the first one also the far energies of the records;
+// with one block it finishes alone, else the last
 // block of the system (per-system counter, re-armed) adds the blocks' sums in
 // block order.  The finish: U_N and the total U = U_N + U* - U_self, the
 // kinetic energy after the evaluation, and for a Nose-Hoover step xi's
 // second half step with it.
 __global__ __launch_bounds__(256) void k_kinetic(EvalArgs a) {
-    __shared__ double kw[256], ew[256];
+    __shared__ double kw[256], ew[256], uw[256];
     const int32_t s = blockIdx.y, g = blockIdx.x, G = gridDim.x;
     const SysDev &sp = a.sys[s];
     // the block's share [lo, hi) of the partials [b0, b1)
@@ -676,16 +751,32 @@ __global__ __launch_bounds__(256) void k_kinetic(EvalArgs a) {
     const double *ep = a.always_build ? a.epart_cells : a.epart;
     share(a.always_build ? sp.jt0 : sp.it0, a.always_build ? sp.jt1 : sp.it1, lo, hi);
     ew[threadIdx.x] = sum8(ep, lo, hi);
+    // the far energy of the system, summed by its first block
+    double us = 0.0;
+    if (g == 0)
+        for (int32_t e = threadIdx.x; e < sp.P; e += 256) us += a.ek[sp.k0 + e];
+    uw[threadIdx.x] = us;
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
         if ((int)threadIdx.x < o) {
             kw[threadIdx.x] += kw[threadIdx.x + o];
             ew[threadIdx.x] += ew[threadIdx.x + o];
+            uw[threadIdx.x] += uw[threadIdx.x + o];
         }
         __syncthreads();
     }
     if (threadIdx.x != 0) return;
     double K = kw[0], un = ew[0];
+    if (g == 0) {
+        // U* holds the far part with the zero-frequency mode term
+        double u0 = 0.0;
+        if (sp.zmode != 0) {
+            const double M[3] = {a.dipole[3 * s], a.dipole[3 * s + 1], a.dipole[3 * s + 2]};
+            u0 = sp.zmode == 1 ? sp.zu * (M[0] * M[0] + M[1] * M[1] + M[2] * M[2]) : sp.zu * M[2] * M[2];
+        }
+        a.E[4 * s + 1] = uw[0] + u0;
+        a.E[4 * s + 2] = sp.uself;
+    }
     if (G > 1) {
         double *part = a.kin_part + (int64_t)s * 2 * G;
         part[2 * g] = K;
@@ -751,18 +842,40 @@ void launch_rho_reduce(const EvalArgs &a, hipStream_t s) {
     if (a.K <= 0) return;
     if (a.red_waves == 4) hipLaunchKernelGGL(k_rho_reduce_block, dim3((unsigned)a.K), dim3(256), 0, s, a);
     else hipLaunchKernelGGL(k_rho_reduce, dim3((unsigned)((a.K + 3) / 4)), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_rho_finish, dim3((unsigned)a.nsys), dim3(256), 0, s, a);
+    if (a.zmode) hipLaunchKernelGGL(k_dipole, dim3((unsigned)a.nsys), dim3(256), 0, s, a);
+}
+
+// Waves per group of 64 particles: as many as keep the launch within 4 (FP32C) or
+// 8 (FP64) waves per SIMD and leave each wave a few groups of records.  k_far at
+// W = 1 and at the W taken: 1,000 ions x 100 FP32C 10.1 -> 5.8 us (16), FP64 21 ->
+// 5.8; 26,998 ions x 130 11.3 -> 7.2 (8; 16: 9.4); 77,781 x 150 13.2 -> 10.5 (2);
+// 98,304 x 211 FP64 40.7 -> 21.2 (4; 2: 25.8); 300,000 x 200 FP64 54 (2: 62).
+template <bool F64, bool FUSE>
+static void far_split(const EvalArgs &a, const FarItem *items, int32_t nitems, int32_t block_size, hipStream_t s) {
+    const int32_t groups = block_size / 64;
+    const int64_t all = (a.N + 63) / 64, per = a.nsys ? a.K / a.nsys : 0;
+    int w = 16;
+    while (w > 1 && (all * w > (F64 ? 8192 : 4096) || per < 4 * w)) w >>= 1;
+    const dim3 grid((unsigned)(nitems * groups)), block((unsigned)(64 * w));
+    switch (w) {
+        case 16: hipLaunchKernelGGL((k_far<F64, FUSE, 16>), grid, block, 0, s, a, items, nitems, groups); break;
+        case 8: hipLaunchKernelGGL((k_far<F64, FUSE, 8>), grid, block, 0, s, a, items, nitems, groups); break;
+        case 4: hipLaunchKernelGGL((k_far<F64, FUSE, 4>), grid, block, 0, s, a, items, nitems, groups); break;
+        case 2: hipLaunchKernelGGL((k_far<F64, FUSE, 2>), grid, block, 0, s, a, items, nitems, groups); break;
+        default:
+            hipLaunchKernelGGL((k_far<F64, FUSE, 1>), dim3((unsigned)nitems), dim3((unsigned)block_size), 0, s, a, items,
+                               nitems, groups);
+    }
 }
 
 void launch_far(const EvalArgs &a, bool f64, const FarItem *items, int32_t nitems, int32_t block_size,
                 hipStream_t s) {
-    dim3 grid((unsigned)nitems), block((unsigned)block_size);
     if (a.fuse) {
-        if (f64) hipLaunchKernelGGL((k_far<true, true>), grid, block, 0, s, a, items, nitems);
-        else hipLaunchKernelGGL((k_far<false, true>), grid, block, 0, s, a, items, nitems);
+        if (f64) far_split<true, true>(a, items, nitems, block_size, s);
+        else far_split<false, true>(a, items, nitems, block_size, s);
     } else {
-        if (f64) hipLaunchKernelGGL((k_far<true, false>), grid, block, 0, s, a, items, nitems);
-        else hipLaunchKernelGGL((k_far<false, false>), grid, block, 0, s, a, items, nitems);
+        if (f64) far_split<true, false>(a, items, nitems, block_size, s);
+        else far_split<false, false>(a, items, nitems, block_size, s);
     }
 }
 

@@ -281,6 +281,8 @@ struct EvalArgs {
     double c1, c2;
     uint64_t tseed;
     int64_t *tstep;        // thermostatted steps taken (noise counter)
+    int32_t advance;       // 1: the evaluation's last far kernel moves the sequence cursors on
+    int32_t zmode;         // 1: some system has a zero-frequency mode term
     // nonzero (plain velocity Verlet on a kept near list): the far kernel
     // also opens the next step (its half kick with the same force, its drift
     // and quantisation, its displacement check), the near list pass clears
