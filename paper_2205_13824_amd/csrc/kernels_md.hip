@@ -163,9 +163,12 @@ __device__ int32_t block_exclusive_scan(int32_t v, int32_t *total) {
 
 // The kernels of a list build run at every evaluation with a kept list and
 // return at once unless a build is due, so their blocks are large and few:
-// kBuildThreads threads, at most kBuildGrid blocks (two per CU) that stride.
+// kBuildThreads threads, at most kBuildGrid blocks that stride, so that they pass
+// the few wave slots that the structure factor leaves free (512 blocks: 300,000
+// ions 84.8 us a step against 83.7; 64: 84.0; a build's own time is the same
+// within 2 %).
 constexpr int kBuildThreads = 1024;
-constexpr int64_t kBuildGrid = 512;
+constexpr int64_t kBuildGrid = 128;
 
 // Exclusive scan of the counts of n cells by one block, tile after tile of four
 // counts per thread: the cells' starts, the scatter's fill counters, and
