@@ -671,7 +671,7 @@ EvalArgs make_args(rbsog_ctx *c, bool stepping, double dt) {
 // the near kernels sum the pair energies.  Steps without the Nose-Hoover
 // thermostat leave both to the last step of their run (nothing reads the
 // values in between).
-// Fused steps (plain velocity Verlet on a kept list, fusable(c)): `fuse`
+// Fused steps (velocity Verlet, plain or Langevin, on a kept list, fusable(c)): `fuse`
 // has the far kernel open the next step, whose enqueue then passes `head`
 // false: it starts with the structure factor.  Every value is computed as in
 // the unfused steps, in the same order.
@@ -773,11 +773,11 @@ void drop_graphs(rbsog_ctx *c) {
 
 int graph_mode(const rbsog_ctx *c) { return c->skin_cur > 0.0 ? 0 : 1; }
 
-// Steps whose far kernel may open the next step: plain velocity Verlet (no
-// thermostat) on a kept near list, without kernel timing or pair records.
+// Steps whose far kernel may open the next step: velocity Verlet, plain or with
+// the Langevin thermostat, on a kept near list, without kernel timing or pair
+// records.
 bool fusable(const rbsog_ctx *c) {
-    return c->skin_cur > 0.0 && !c->nh_on && !(c->gamma > 0.0) && !c->prof_on && !c->dbg_pairs && c->n_list > 0 &&
-           c->n_far > 0;
+    return c->skin_cur > 0.0 && !c->nh_on && !c->prof_on && !c->dbg_pairs && c->n_list > 0 && c->n_far > 0;
 }
 
 // A step graph captures the kernel arguments; it is rebuilt when dt or a

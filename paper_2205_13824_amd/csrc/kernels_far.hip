@@ -247,11 +247,19 @@ __device__ __forceinline__ void write_record(const EvalArgs &a, const SysDev &sd
 // k_kinetic, after the near part.  Nothing here waits for the near part.  (A last-block finish inside
 // the reduction would need a device-scope fence in every block, a writeback
 // of the XCD's L2 each: 0.3 ms for the 6,400 blocks of a 256-system batch.)
+// The reduction also moves the thermostat's noise counter on: the kernel that
+// drew this step's noise ran before it, the one that draws the next step's (the
+// far kernel, or the next kick/drift) runs after it.
+__device__ __forceinline__ void advance_noise(const EvalArgs &a) {
+    if (a.advance && a.kick && a.thermo && blockIdx.x == 0 && threadIdx.x == 0) *a.tstep += 1;
+}
+
 // k_rho_reduce: one wave per record, four records per block (systems of few
 // chunks, many of them in a batch).
 __global__ __launch_bounds__(256) void k_rho_reduce(EvalArgs a) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t r = (int64_t)blockIdx.x * 4 + wave;
+    advance_noise(a);
     int32_t sys = -1;
     if (r < a.K) {
         sys = a.ksys[r];
@@ -286,6 +294,7 @@ __global__ __launch_bounds__(256) void k_rho_reduce_block(EvalArgs a) {
     __shared__ double2 red[4];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t r = blockIdx.x;
+    advance_noise(a);
     const int32_t sys = a.ksys[r];
     const SysDev &sd = a.sys[sys];
     const int32_t k = (int32_t)(r - sd.k0);
@@ -346,12 +355,10 @@ __global__ __launch_bounds__(256) void k_dipole(EvalArgs a) {
 }
 
 // The last kernel of an evaluation (nothing in it or after it reads the
-// batch's place in the sequence): every system's sequence cursor moved on by P,
-// and the thermostat's noise counter by one step.
+// batch's place in the sequence): every system's sequence cursor moved on by P.
 __device__ __forceinline__ void advance_cursors(const EvalArgs &a) {
     if (!a.advance || blockIdx.x != 0) return;
     for (int32_t s = threadIdx.x; s < a.nsys; s += blockDim.x) a.kcur[s] += a.sys[s].P;
-    if (threadIdx.x == 0 && a.kick && a.thermo) *a.tstep += 1;
 }
 
 // Records whose phases a wave stages at once in the FP32C far sum.
@@ -509,20 +516,23 @@ __device__ __forceinline__ void far_sum(CSys *sp, CRec64 *kb64, CRec32 *kb32, in
 // of each wave's particles summed across the wave in a fixed order into
 // partial `part` (k_kinetic adds them up).  FUSE: the next step
 // starts here, as the kick/drift kernel would start it: its opening half kick
-// with the same force, its drift, wrap and quantisation, and its
-// displacement check.  Lanes past the item (valid false) hold slot i = t0 and
+// with the same force, its drift (Langevin: with the noise xi between two half
+// drifts), wrap and quantisation, and its displacement check.  Lanes past the item (valid false) hold slot i = t0 and
 // store nothing.
-template <bool FUSE>
+constexpr int kFusePlain = 1, kFuseLangevin = 2;
+template <int FUSE>
 struct FarEnd {
     // loaded before the far force is stored (the stores could alias them for
     // the compiler), or before the far sum
     double vv[3], fn[3], xs[FUSE ? 3 : 1];
     uint32_t uref[FUSE ? 3 : 1];
+    int32_t id;
 };
-template <bool FUSE>
+template <int FUSE>
 __device__ __forceinline__ FarEnd<FUSE> far_operands(const EvalArgs &a, int64_t i) {
     const int64_t n = a.N;
     FarEnd<FUSE> o;
+    if constexpr (FUSE == kFuseLangevin) o.id = a.cur.id[i];
     for (int d = 0; d < 3; ++d) {
         o.vv[d] = a.cur.v[d * n + i];
         o.fn[d] = a.Fn[d * n + i];
@@ -533,9 +543,10 @@ __device__ __forceinline__ FarEnd<FUSE> far_operands(const EvalArgs &a, int64_t 
     }
     return o;
 }
-template <bool FUSE>
+template <int FUSE>
 __device__ __forceinline__ void far_finish(const EvalArgs &a, CSys *sp, int32_t sys, int64_t i, bool valid,
-                                           double Fx, double Fy, double Fz, int32_t part, const FarEnd<FUSE> &o) {
+                                           double Fx, double Fy, double Fz, int32_t part, const FarEnd<FUSE> &o,
+                                           const double *xi = nullptr) {
     const int64_t n = a.N;
     double vv[3] = {o.vv[0], o.vv[1], o.vv[2]};
     const double *fn = o.fn;
@@ -588,7 +599,14 @@ __device__ __forceinline__ void far_finish(const EvalArgs &a, CSys *sp, int32_t 
         }
         for (int d = 0; d < 3; ++d) {
             vv[d] += a.hdm * f[d];
-            xs[d] += a.dt * vv[d];
+            if constexpr (FUSE == kFuseLangevin) {
+                // half drift, Ornstein-Uhlenbeck, half drift
+                xs[d] += 0.5 * a.dt * vv[d];
+                vv[d] = fma(a.c1, vv[d], a.c2 * xi[d]);
+                xs[d] += 0.5 * a.dt * vv[d];
+            } else {
+                xs[d] += a.dt * vv[d];
+            }
             if (valid) a.cur.v[d * n + i] = vv[d];
         }
         if (valid && a.cur.dsp)
@@ -610,13 +628,14 @@ __device__ __forceinline__ void far_finish(const EvalArgs &a, CSys *sp, int32_t 
 // The near-list rebuild flag is cleared here (every kernel of the evaluation
 // that reads it has run), unless the kernel opens the next step (FUSE), whose
 // displacement check sets it: the list pass has cleared it then.
-template <bool F64, bool FUSE, int W>
+template <bool F64, int FUSE, int W>
 __global__ __launch_bounds__(W == 1 ? 256 : 64 * W) void k_far(EvalArgs a, const FarItem *__restrict__ items, int32_t nitems,
                                                                int32_t groups) {
     constexpr int kWaves = W == 1 ? 4 : W;
     __shared__ double2 turn[F64 ? rmath::kTurnTab : 1];
     __shared__ uint64_t phs[F64 ? 1 : kWaves * kFarStage];  // FP32C: record phases, per wave
     __shared__ double part[W == 1 ? 1 : W][3][W == 1 ? 1 : 64];
+    __shared__ double noise[W > 1 && FUSE == kFuseLangevin ? 3 : 1][W > 1 && FUSE == kFuseLangevin ? 64 : 1];
     if constexpr (F64) fill_turns(turn);
     if (!FUSE && blockIdx.x == 0 && threadIdx.x == 0 && a.rebuild) *a.rebuild = 0;
     advance_cursors(a);
@@ -638,7 +657,9 @@ __global__ __launch_bounds__(W == 1 ? 256 : 64 * W) void k_far(EvalArgs a, const
         far_sum<F64>(sp, (CRec64 *)(a.kb64 + sp->k0), (CRec32 *)(a.kb32 + sp->k0), sp->P, a.N, i, a.u_tmp,
                      a.cur.qf, a.cur.x, a.cur.q, turn, ph, Fx, Fy, Fz);
         const FarEnd<FUSE> o = far_operands<FUSE>(a, i);
-        far_finish<FUSE>(a, sp, sys, i, valid, Fx, Fy, Fz, itx * 4 + grp, o);
+        double xi[3];
+        if constexpr (FUSE == kFuseLangevin) rmath::thermo_normals(a.tseed, *a.tstep, o.id, xi);
+        far_finish<FUSE>(a, sp, sys, i, valid, Fx, Fy, Fz, itx * 4 + grp, o, xi);
     } else {
         FarEnd<FUSE> o;
         if (wave == 0) o = far_operands<FUSE>(a, i);
@@ -652,6 +673,14 @@ __global__ __launch_bounds__(W == 1 ? 256 : 64 * W) void k_far(EvalArgs a, const
         part[wave][0][lane] = Fx;
         part[wave][1][lane] = Fy;
         part[wave][2][lane] = Fz;
+        if constexpr (FUSE == kFuseLangevin) {
+            // the last wave, whose share of the records is the smallest, draws the noise
+            if (wave == W - 1) {
+                double xi[3];
+                rmath::thermo_normals(a.tseed, *a.tstep, a.cur.id[i], xi);
+                for (int d = 0; d < 3; ++d) noise[d][lane] = xi[d];
+            }
+        }
         __syncthreads();
         if (wave != 0) return;
 #pragma unroll
@@ -660,7 +689,10 @@ __global__ __launch_bounds__(W == 1 ? 256 : 64 * W) void k_far(EvalArgs a, const
             Fy += part[w][1][lane];
             Fz += part[w][2][lane];
         }
-        far_finish<FUSE>(a, sp, sys, i, valid, Fx, Fy, Fz, itx * 4 + grp, o);
+        double xi[3];
+        if constexpr (FUSE == kFuseLangevin)
+            for (int d = 0; d < 3; ++d) xi[d] = noise[d][lane];
+        far_finish<FUSE>(a, sp, sys, i, valid, Fx, Fy, Fz, itx * 4 + grp, o, xi);
     }
 }
 
@@ -710,8 +742,8 @@ __global__ __launch_bounds__(256) void k_far_finish(EvalArgs a, const FarItem *_
         const int64_t i = valid ? i0 : t0;
         const int64_t o = a.sorted[i];
         const double Fx = a.Ff_side[o], Fy = a.Ff_side[n + o], Fz = a.Ff_side[2 * n + o];
-        far_finish<false>(a, sp, sys, i, valid, Fx, Fy, Fz, itx * 4 + (int32_t)(threadIdx.x >> 6),
-                          far_operands<false>(a, i));
+        far_finish<0>(a, sp, sys, i, valid, Fx, Fy, Fz, itx * 4 + (int32_t)(threadIdx.x >> 6),
+                          far_operands<0>(a, i));
     }
 }
 
@@ -850,7 +882,7 @@ void launch_rho_reduce(const EvalArgs &a, hipStream_t s) {
 // W = 1 and at the W taken: 1,000 ions x 100 FP32C 10.1 -> 5.8 us (16), FP64 21 ->
 // 5.8; 26,998 ions x 130 11.3 -> 7.2 (8; 16: 9.4); 77,781 x 150 13.2 -> 10.5 (2);
 // 98,304 x 211 FP64 40.7 -> 21.2 (4; 2: 25.8); 300,000 x 200 FP64 54 (2: 62).
-template <bool F64, bool FUSE>
+template <bool F64, int FUSE>
 static void far_split(const EvalArgs &a, const FarItem *items, int32_t nitems, int32_t block_size, hipStream_t s) {
     const int32_t groups = block_size / 64;
     const int64_t all = (a.N + 63) / 64, per = a.nsys ? a.K / a.nsys : 0;
@@ -870,12 +902,15 @@ static void far_split(const EvalArgs &a, const FarItem *items, int32_t nitems, i
 
 void launch_far(const EvalArgs &a, bool f64, const FarItem *items, int32_t nitems, int32_t block_size,
                 hipStream_t s) {
-    if (a.fuse) {
-        if (f64) far_split<true, true>(a, items, nitems, block_size, s);
-        else far_split<false, true>(a, items, nitems, block_size, s);
+    if (a.fuse && a.thermo) {
+        if (f64) far_split<true, kFuseLangevin>(a, items, nitems, block_size, s);
+        else far_split<false, kFuseLangevin>(a, items, nitems, block_size, s);
+    } else if (a.fuse) {
+        if (f64) far_split<true, kFusePlain>(a, items, nitems, block_size, s);
+        else far_split<false, kFusePlain>(a, items, nitems, block_size, s);
     } else {
-        if (f64) far_split<true, false>(a, items, nitems, block_size, s);
-        else far_split<false, false>(a, items, nitems, block_size, s);
+        if (f64) far_split<true, 0>(a, items, nitems, block_size, s);
+        else far_split<false, 0>(a, items, nitems, block_size, s);
     }
 }
 

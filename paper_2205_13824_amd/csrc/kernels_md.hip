@@ -28,13 +28,6 @@ __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v) {
     if (i < n) p[i] = v;
 }
 
-// Three standard normals for particle `id` at thermostat step `step`
-// (Box-Muller on lanes 0 and 1 of Philox stream 2, counter (id, step)).
-__device__ __forceinline__ void thermo_normals(uint64_t seed, int64_t step, int32_t id, double xi[3]) {
-    const uint64_t idx = ((uint64_t)step << 32) | (uint32_t)id;
-    rmath::normals3(seed, 2, idx, xi);
-}
-
 // Lanes holding the same cell in a run of consecutive lanes (the state is in
 // cell order, so runs are the rule) share one atomic: the run's first lane
 // adds the run length and the others take their offset in the run.  Returns
@@ -99,12 +92,12 @@ __global__ __launch_bounds__(kBlock) void k_kdq(EvalArgs a) {
         if (a.thermo) {
             // BAOAB: half kick, half drift, Ornstein-Uhlenbeck, half drift
             double xi[3];
-            thermo_normals(a.tseed, *a.tstep, a.cur.id[t], xi);
+            rmath::thermo_normals(a.tseed, *a.tstep, a.cur.id[t], xi);
             for (int d = 0; d < 3; ++d) {
                 bad |= !isfinite(f[d]);
                 vs[d] += a.hdm * f[d];
                 xs[d] += 0.5 * a.dt * vs[d];
-                vs[d] = a.c1 * vs[d] + a.c2 * xi[d];
+                vs[d] = fma(a.c1, vs[d], a.c2 * xi[d]);  // (rounded as where the far kernel opens the step)
                 xs[d] += 0.5 * a.dt * vs[d];
                 if (valid) v[d * N + t] = vs[d];
             }

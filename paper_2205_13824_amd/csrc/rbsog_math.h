@@ -61,6 +61,12 @@ __host__ __device__ inline void normals3(uint64_t seed, uint32_t stream, uint64_
     z[2] = r2 * cos(kTwoPi * u4);
 }
 
+// Thermostat noise of particle `id` at thermostat step `step`: stream 2,
+// counter (id, step).
+__host__ __device__ inline void thermo_normals(uint64_t seed, int64_t step, int32_t id, double xi[3]) {
+    normals3(seed, 2, ((uint64_t)step << 32) | (uint32_t)id, xi);
+}
+
 // Unnormalised target of the sampler, p(m) ~ F~(2 pi m / L) =
 // pi^{3/2} sum_l omega_l s_l^3 exp(-pi^2 s_l^2 |m/L|^2) without the pi^{3/2}
 // (Sec. 3.3, eq. "distribution"; G = M + 1 Gaussians).
