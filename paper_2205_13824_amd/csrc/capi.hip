@@ -148,6 +148,17 @@ rbsog_status fail_noctx(rbsog_status st, const char *fmt, ...) {
 }
 }  // namespace rbsog
 
+// (particle, k) pairs of one evaluation up to which the structure factor runs
+// beside the near part on the second stream
+constexpr double kSideMaxWork = 4e9;
+// and from which it does on a kept list.  An edge between two queues of a step
+// graph costs some 5 us; below, the kernels beside the structure factor take no
+// longer than that.  Us per step on one stream | on two: FP32C 1,000 ions x 100
+// wave vectors 27 | 34, 26,998 x 130 40 | 45, 78,000 x 150 60 | 62, 150,000 x 100
+// 77 | 78, 100,000 x 300 80 | 77, 300,000 x 200 107 | 84; FP64 26,998 x 130 48 | 52,
+// 60,000 x 150 70 | 68, 110,000 x 150 96 | 86.
+constexpr double side_min_work(int prec) { return prec == RBSOG_FP64 ? 6e6 : 2e7; }
+
 struct rbsog_ctx {
     int32_t nsys = 0;
     std::vector<SysHost> sys;
@@ -259,11 +270,13 @@ struct rbsog_ctx {
     // variant (GV_*)
     bool use_graphs = true;
     // the structure factor on a second stream beside the re-sort and the near
-    // part: when its (particle, k) work is small enough that the two do not
-    // each fill the device (sum of n P <= kSideMaxWork); larger systems run
-    // the kernels one after the other (both are bound by vector issue there,
-    // and the overlap only shares the same units)
-    bool use_side = true;
+    // part: when its (particle, k) work, sum of n P, is small enough that the two
+    // do not each fill the device (<= kSideMaxWork; larger systems run the kernels
+    // one after the other: both are bound by vector issue there, and the overlap
+    // only shares the same units) and, on a kept list, large enough to pay for the
+    // two edges between the queues (> side_min_work)
+    double work = 0.0;
+    bool use_side() const { return work <= kSideMaxWork && (!(skin_cur > 0.0) || work > side_min_work(prec)); }
     hipGraph_t graph[2][GV_COUNT] = {};
     hipGraphExec_t graph_exec[2][GV_COUNT] = {};
     double graph_dt_m[2][GV_COUNT] = {};
@@ -693,7 +706,7 @@ rbsog_status enqueue_eval(rbsog_ctx *c, bool stepping, double dt, bool kinetic, 
     // taken by the kick/drift (or the previous far) kernel only: they run on the
     // side stream beside the re-sort and the near part (one stream while
     // profiling kernels alone, and for systems with a lot of far work)
-    const bool fork = c->prof_on != 1 && c->use_side;
+    const bool fork = c->prof_on != 1 && c->use_side();
     // building at every step, the far force joins them there (the near part
     // is long enough to hide it); it is then read back in the new order
     const bool far_side = a.always_build != 0;
@@ -899,10 +912,6 @@ rbsog_status request_build(rbsog_ctx *c) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return RBSOG_OK;
 }
-
-// (particle, k) pairs of one evaluation up to which the structure factor runs
-// beside the near part on the second stream
-constexpr double kSideMaxWork = 4e9;
 
 // Lists longer than this (pairs of one home at the sizing build) are kept in
 // home-major blocks, evaluated one home per wave; shorter ones in columns, one
@@ -1824,9 +1833,7 @@ rbsog_status init_batch(rbsog_ctx **out, int32_t nsys, const int64_t *offsets, c
     c->skin = o.skin;
     c->skin_cur = o.skin;
     {
-        double work = 0.0;
-        for (int32_t s = 0; s < nsys; ++s) work += (double)(offsets[s + 1] - offsets[s]) * (double)P[s];
-        c->use_side = work <= kSideMaxWork;
+        for (int32_t s = 0; s < nsys; ++s) c->work += (double)(offsets[s + 1] - offsets[s]) * (double)P[s];
     }
     for (int k = 0; k < K_COUNT; ++k) c->prof[k].name = kKernelNames[k];
     for (int32_t s = 0; s < nsys; ++s) {
