@@ -711,6 +711,11 @@ rbsog_status enqueue_eval(rbsog_ctx *c, bool stepping, double dt, bool kinetic, 
     // is long enough to hide it); it is then read back in the new order
     const bool far_side = a.always_build != 0;
     const int32_t fb = c->tune.far_block;
+    // small evaluations on one stream: the list pass's launch reduces the structure
+    // factor's partial sums too
+    const bool carry = !fork && !c->prof_on && !a.always_build && !c->dbg_pairs && c->work <= kSideMaxWork &&
+                       a.K > 0 && !a.zmode && a.red_waves == 1;
+    if (carry) launch_rho(a, f64, c->rho_items, c->n_rho, s);
     if (fork) {
         HIPCHK(c, hipEventRecord(c->ev_fork, s));
         HIPCHK(c, hipStreamWaitEvent(c->side, c->ev_fork, 0));
@@ -736,11 +741,11 @@ rbsog_status enqueue_eval(rbsog_ctx *c, bool stepping, double dt, bool kinetic, 
         TRY(timed(c, K_NEARC, [&] { launch_near_cells(a, f64, c->near_items, c->n_near, c->cell_slots, s); }));
     } else {
         TRY(timed(c, K_LIST, [&] { launch_list_build(a, f64, c->list_items, c->n_list, c->build_slots, s, !one); }));
-        TRY(timed(c, K_NEAR, [&] { launch_near(a, f64, c->list_items, c->n_list, s); }));
+        TRY(timed(c, K_NEAR, [&] { launch_near(a, f64, c->list_items, c->n_list, s, carry); }));
     }
     if (fork) {
         HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));
-    } else {
+    } else if (!carry) {
         TRY(timed(c, K_RHO, [&] { launch_rho(a, f64, c->rho_items, c->n_rho, s); }));
         TRY(timed(c, K_RHORED, [&] { launch_rho_reduce(a, s); }));
         if (far_side) TRY(timed(c, K_FARSIDE, [&] { launch_far_side(a, f64, c->far_items, c->n_far, fb, s); }));
@@ -1665,7 +1670,7 @@ rbsog_status autotune_now(rbsog_ctx *c, int32_t reps) {
             launch_near_cells(a, f64, c->near_items, c->n_near, c->cell_slots, st);
         } else {
             launch_list_build(a, f64, c->list_items, c->n_list, c->build_slots, st);
-            launch_near(a, f64, c->list_items, c->n_list, st);
+            launch_near(a, f64, c->list_items, c->n_list, st, false);
         }
         // the far force of the current order (the re-sorts above left the
         // side copy of the positions out of step with the permutation)

@@ -19,6 +19,7 @@
 #include "rbsog_internal.h"
 #include "rbsog_math.h"
 #include "rho_core.h"
+#include "rho_reduce.h"
 
 namespace rbsog {
 
@@ -185,106 +186,12 @@ __global__ __launch_bounds__(1024, 8) void k_rho(EvalArgs a, const RhoItem *__re
     }
 }
 
-// Sum over the wave in a fixed order (the same on every run).
-__device__ __forceinline__ double wave_sum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// A system's k-th wave vector of the batch and its weight (the cursor still
-// points at the batch), requested ahead of the sums.
-struct KVec {
-    int32_t m[3];
-    double w;
-};
-__device__ __forceinline__ KVec batch_vector(const EvalArgs &a, const SysDev &sd, int32_t sys, int32_t k) {
-    const int64_t e = a.kcur[sys] + k;
-    return KVec{{sd.kseq[3 * e], sd.kseq[3 * e + 1], sd.kseq[3 * e + 2]}, sd.kw ? sd.kw[e] : sd.w_rb};
-}
-
-// Record r from its wave vector and rho: rho and the per-k energy stored, and
-// the amplitude-phase records of both forms written.
-__device__ __forceinline__ void write_record(const EvalArgs &a, const SysDev &sd, int64_t r, const KVec &kv, double re,
-                                             double im) {
-    a.rho[r] = re;
-    a.rho[a.K + r] = im;
-    const int32_t *m = kv.m;
-    const double w = kv.w;
-    a.ek[r] = 0.5 * w * (re * re + im * im);
-    // amplitude-phase record: phi = arg(rho) / (2 pi), a = w |rho| k
-    const double phi = atan2(im, re) * (1.0 / rmath::kTwoPi);
-    const double mag = hypot(re, im);
-    const double c = w * mag * rmath::kTwoPi;
-    KRec64 h;
-    h.mx = m[0];
-    h.my = m[1];
-    h.mz = m[2];
-    h.phi = phi * rmath::kTurnTab;
-    h.ax = c * h.mx * sd.g.invL[0];
-    h.ay = c * h.my * sd.g.invL[1];
-    h.az = c * h.mz * sd.g.invL[2];
-    h.pad = 0.0;
-    a.kb64[r] = h;
-    // FP32 form: phi in 2^-32 turns, plus 2^9 units: the FP32 phases of
-    // the structure factor and of the far force are each truncated
-    // to 2^-23 turns (half a unit of it low on average), which this
-    // offset takes back
-    KRec32 f;
-    f.nmx = -m[0];
-    f.nmy = -m[1];
-    f.nmz = -m[2];
-    f.phi = (uint32_t)(int64_t)rint(phi * 4294967296.0) + 512u;
-    f.ax = (float)h.ax;
-    f.ay = (float)h.ay;
-    f.az = (float)h.az;
-    f.pad = 0.f;
-    a.kb32[r] = f;
-}
-
-// The structure factor's reduction.  Per k record r: rho = sum over the
-// system's chunks of the partials (fixed order), the per-k energy
-// 1/2 w |rho|^2, and rho written into the records.  The energies follow in
-// k_kinetic, after the near part.  Nothing here waits for the near part.  (A last-block finish inside
-// the reduction would need a device-scope fence in every block, a writeback
-// of the XCD's L2 each: 0.3 ms for the 6,400 blocks of a 256-system batch.)
-// The reduction also moves the thermostat's noise counter on: the kernel that
-// drew this step's noise ran before it, the one that draws the next step's (the
-// far kernel, or the next kick/drift) runs after it.
-__device__ __forceinline__ void advance_noise(const EvalArgs &a) {
-    if (a.advance && a.kick && a.thermo && blockIdx.x == 0 && threadIdx.x == 0) *a.tstep += 1;
-}
-
 // k_rho_reduce: one wave per record, four records per block (systems of few
 // chunks, many of them in a batch).
 __global__ __launch_bounds__(256) void k_rho_reduce(EvalArgs a) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t r = (int64_t)blockIdx.x * 4 + wave;
-    advance_noise(a);
-    int32_t sys = -1;
-    if (r < a.K) {
-        sys = a.ksys[r];
-        const SysDev &sd = a.sys[sys];
-        const int32_t k = (int32_t)(r - sd.k0);
-        const double2 *pk = reinterpret_cast<const double2 *>(a.partial) + sd.pofs + (int64_t)k * sd.nch;
-        const int32_t nch = sd.nch;
-        const KVec kv = batch_vector(a, sd, sys, k);
-        // four independent loads in flight per lane, summed in a fixed order
-        double2 v0 = make_double2(0.0, 0.0), v1 = v0, v2 = v0, v3 = v0;
-        int32_t c = lane;
-        for (; c + 192 < nch; c += 256) {
-            const double2 a0 = pk[c], a1 = pk[c + 64], a2 = pk[c + 128], a3 = pk[c + 192];
-            v0.x += a0.x; v0.y += a0.y; v1.x += a1.x; v1.y += a1.y;
-            v2.x += a2.x; v2.y += a2.y; v3.x += a3.x; v3.y += a3.y;
-        }
-        for (; c < nch; c += 64) {
-            const double2 a0 = pk[c];
-            v0.x += a0.x; v0.y += a0.y;
-        }
-        double re = (v0.x + v1.x) + (v2.x + v3.x), im = (v0.y + v1.y) + (v2.y + v3.y);
-        re = wave_sum(re);
-        im = wave_sum(im);
-        if (lane == 0) write_record(a, sd, r, kv, re, im);
-    }
+    const int64_t r = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (blockIdx.x == 0) advance_noise(a);
+    if (r < a.K) reduce_record(a, r);
 }
 
 // k_rho_reduce_block: one block per record (systems of many chunks): each
@@ -294,7 +201,7 @@ __global__ __launch_bounds__(256) void k_rho_reduce_block(EvalArgs a) {
     __shared__ double2 red[4];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t r = blockIdx.x;
-    advance_noise(a);
+    if (blockIdx.x == 0) advance_noise(a);
     const int32_t sys = a.ksys[r];
     const SysDev &sd = a.sys[sys];
     const int32_t k = (int32_t)(r - sd.k0);
@@ -322,8 +229,8 @@ __global__ __launch_bounds__(256) void k_rho_reduce_block(EvalArgs a) {
     }
     double re = ((v[0].x + v[1].x) + (v[2].x + v[3].x)) + ((v[4].x + v[5].x) + (v[6].x + v[7].x));
     double im = ((v[0].y + v[1].y) + (v[2].y + v[3].y)) + ((v[4].y + v[5].y) + (v[6].y + v[7].y));
-    re = wave_sum(re);
-    im = wave_sum(im);
+    re = record_sum(re);
+    im = record_sum(im);
     if (lane == 0) red[wave] = make_double2(re, im);
     __syncthreads();
     if (threadIdx.x == 0) {

@@ -428,9 +428,10 @@ void launch_list_build(const EvalArgs &a, bool f64, const ListItem *items, int32
 // slots (2 or 3): candidates per lane and test pass
 void launch_near_cells(const EvalArgs &a, bool f64, const NearItem *items, int32_t nitems, int32_t slots,
                        hipStream_t s);
-// near forces and energies from the list; returns at once if *a.rebuild is
-// set (the build has evaluated them)
-void launch_near(const EvalArgs &a, bool f64, const ListItem *items, int32_t nitems, hipStream_t s);
+// near forces and energies from the list; `reduce`: also the structure factor's
+// reduction (launch_rho_reduce where a.red_waves is 1 and no system has a
+// zero-frequency mode term)
+void launch_near(const EvalArgs &a, bool f64, const ListItem *items, int32_t nitems, hipStream_t s, bool reduce);
 // neighbour list of one system (debug export): counts per local id, then fill
 void launch_neighbor_count(const EvalArgs &a, int32_t sys, int64_t n, int64_t p0, const int32_t *id_cur,
                            int64_t *counts, hipStream_t s);
