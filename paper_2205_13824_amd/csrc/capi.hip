@@ -711,11 +711,10 @@ rbsog_status enqueue_eval(rbsog_ctx *c, bool stepping, double dt, bool kinetic, 
     // is long enough to hide it); it is then read back in the new order
     const bool far_side = a.always_build != 0;
     const int32_t fb = c->tune.far_block;
-    // small evaluations on one stream: the list pass's launch reduces the structure
-    // factor's partial sums too
+    // small evaluations on one stream: the structure factor shares a launch with the
+    // build's first kernel, its reduction one with the list pass
     const bool carry = !fork && !c->prof_on && !a.always_build && !c->dbg_pairs && c->work <= kSideMaxWork &&
                        a.K > 0 && !a.zmode && a.red_waves == 1;
-    if (carry) launch_rho(a, f64, c->rho_items, c->n_rho, s);
     if (fork) {
         HIPCHK(c, hipEventRecord(c->ev_fork, s));
         HIPCHK(c, hipStreamWaitEvent(c->side, c->ev_fork, 0));
@@ -729,10 +728,11 @@ rbsog_status enqueue_eval(rbsog_ctx *c, bool stepping, double dt, bool kinetic, 
     // build); an evaluation that the host has asked to build takes the kernels
     // that use the whole device
     const bool one = stepping && !a.always_build && resort_in_one(a);
-    if (one) {
+    if (carry) launch_rho_build(a, f64, c->rho_items, c->n_rho, one, s);
+    if (one && !carry) {
         TRY(timed(c, K_SORTG, [&] { launch_resort_one(a, s); }));
-    } else {
-        if (!a.always_build) TRY(timed(c, K_BIN, [&] { launch_bin(a, s); }));
+    } else if (!one) {
+        if (!a.always_build && !carry) TRY(timed(c, K_BIN, [&] { launch_bin(a, s); }));
         if (scan_apart(a)) TRY(timed(c, K_SCAN, [&] { launch_scan(a, s); }));
         TRY(timed(c, K_SCATTER, [&] { launch_cell_scatter(a, s); }));
         TRY(timed(c, K_SORTG, [&] { launch_sort_gather(a, s); }));

@@ -409,6 +409,8 @@ void launch_sort_gather(const EvalArgs &a, hipStream_t s);
 // all of the above and the copy back by one block, for small batches
 bool resort_in_one(const EvalArgs &a);
 void launch_resort_one(const EvalArgs &a, hipStream_t s);
+// launch_rho and launch_resort_one (one) or launch_bin in one launch
+void launch_rho_build(const EvalArgs &a, bool f64, const RhoItem *items, int32_t nitems, bool one, hipStream_t s);
 // near and far forces (6 doubles each) of the caller indices ids[0..m) from
 // the current order (slot_of: N int32 of scratch for the inverse permutation)
 void launch_subset_forces(const EvalArgs &a, int64_t m, const int64_t *ids, int32_t *slot_of, double *out,
