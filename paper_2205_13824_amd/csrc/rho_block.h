@@ -18,20 +18,50 @@ __device__ __forceinline__ int64_t rfl64(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// read-only within the kernels that read them uniformly: scalar loads
+typedef const double __attribute__((address_space(4))) CF64;
+// Particles [ja, jb) of a wave in FP64, four read at once, then used.
+__device__ __forceinline__ void sum_uniform64(CF64 *x, CF64 *q, int64_t n, int64_t ja, int64_t jb, const double2 *turn,
+                                              double mx, double my, double mz, double &re, double &im) {
+    auto add = [&](double px, double py, double pz, double pq) {
+        const double t = mx * px + my * py + mz * pz;
+        double sn, cs;
+        rmath::sincos2pi_tab(t, turn, &sn, &cs);
+        re = fma(pq, cs, re);
+        im = fma(pq, sn, im);
+    };
+    int64_t j = ja;
+    for (; j + 4 <= jb; j += 4) {
+        double p[4][4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            p[0][g] = x[j + g];
+            p[1][g] = x[n + j + g];
+            p[2][g] = x[2 * n + j + g];
+            p[3][g] = q[j + g];
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) add(p[0][g], p[1][g], p[2][g], p[3][g]);
+    }
+    for (; j < jb; ++j) add(x[j], x[n + j], x[2 * n + j], q[j]);
+}
+
 // Structure factor partial sums over the work items (grid-stride).  Item
 // (s, kg, chunk, [j0, j1)): wave w handles k tile (w % kt) of group kg (one
 // wave vector per lane) for particle stream (w / kt); kt * streams <= 16
-// waves per block.  The block stages kStage particles at a time in LDS (one
-// coalesced load per thread) and sums them (rho_core.h); the streams' sums
-// are added in a fixed order.  Two blocks per CU (64 VGPRs; FP64 at 77 and one
-// block: 300,000 ions x 200 62.7 us against 59.8).
+// waves per block.  FP32C: the block stages kStage particles at a time in LDS (one
+// coalesced load per thread) and sums them (rho_core.h).  FP64: a stream is a run
+// of the chunk, its particles read as uniform (scalar) loads: the LDS, which the
+// 16-byte reads of the turn table at a lane's own phase keep busy, carries nothing
+// else (staged there, a particle's 32 bytes for each lane cost it as much again:
+// 300,000 ions x 200 76 us against 68, 98,304 sites x 211 33 against 24).  The
+// streams' sums are added in a fixed order.  Two blocks per CU (64 VGPRs).
 template <bool F64>
 __device__ __forceinline__ void rho_items(const EvalArgs &a, const RhoItem *__restrict__ items, int32_t nitems,
                                           int32_t block, int32_t blocks) {
     __shared__ double2 red[1024];
     __shared__ uint4 st32[F64 ? 1 : kStage];
     __shared__ int2 wcnt[F64 ? 1 : 16];
-    __shared__ Stage64 st64[F64 ? kStage : 1];
     // FP64: cos and sin of the kTurnTab turns (sincos2pi_tab)
     __shared__ double2 turn[F64 ? rmath::kTurnTab : 1];
     if constexpr (F64) fill_turns(turn);
@@ -57,19 +87,14 @@ __device__ __forceinline__ void rho_items(const EvalArgs &a, const RhoItem *__re
         const int64_t j0 = rfl64(item.j0), j1 = rfl64(item.j1);
         double re = 0.0, im = 0.0;
         if constexpr (F64) {
-            const double mx = mk[0], my = mk[1], mz = mk[2];
-            // fractional coordinates in table units (kTurnTab per box length)
-            const double ix = sp->g.invL[0] * rmath::kTurnTab, iy = sp->g.invL[1] * rmath::kTurnTab,
-                         iz = sp->g.invL[2] * rmath::kTurnTab;
-            for (int64_t jb = j0; jb < j1; jb += kStage) {
-                const int cnt = (int)(j1 - jb < kStage ? j1 - jb : kStage);
-                if ((int)threadIdx.x < cnt) {
-                    const int64_t j = jb + threadIdx.x;
-                    st64[threadIdx.x] = Stage64{x[j] * ix, x[n + j] * iy, x[2 * n + j] * iz, q[j]};
-                }
-                __syncthreads();
-                if (st < streams) sum_staged64(st64, cnt, turn, mx, my, mz, st, streams, re, im);
-                __syncthreads();
+            // the wave vectors in table units per length
+            const double mx = mk[0] * (sp->g.invL[0] * rmath::kTurnTab), my = mk[1] * (sp->g.invL[1] * rmath::kTurnTab),
+                         mz = mk[2] * (sp->g.invL[2] * rmath::kTurnTab);
+            if (st < streams) {
+                // the stream's particles, a run of the chunk
+                const int64_t per = (j1 - j0 + streams - 1) / streams;
+                const int64_t ja = j0 + st * per < j1 ? j0 + st * per : j1, jb = ja + per < j1 ? ja + per : j1;
+                sum_uniform64((CF64 *)x, (CF64 *)q, n, ja, jb, turn, mx, my, mz, re, im);
             }
         } else {
             const uint32_t mx = (uint32_t)mk[0], my = (uint32_t)mk[1], mz = (uint32_t)mk[2];

@@ -1,6 +1,6 @@
 // Sums of the structure factor over particles staged in LDS (Sec. 3.1:
-// rho(k) = sum_j q_j e^{i k.r_j}), shared by the batch's structure factor
-// (kernels_far.hip) and the context-free one (structure_factor.hip).  Blocks
+// rho(k) = sum_j q_j e^{i k.r_j}), shared by the batch's structure factor in FP32C
+// (rho_block.h) and the context-free one (structure_factor.hip).  Blocks
 // of 1024 threads, 16 waves: a wave holds one wave vector per lane and sums
 // every streams-th staged particle from its stream's on, each read an LDS
 // broadcast to the wave.
@@ -156,14 +156,13 @@ __device__ __forceinline__ void sum_staged32(const uint4 *st32, int np, int ns, 
 }
 
 // The staged particles of stream st in FP64: four read at once, then used.
-// WIDE: phases m.s of any int32 m (else m.s within 2^21 turns).
-template <bool WIDE = false>
+// Phases m.s of any int32 m.
 __device__ __forceinline__ void sum_staged64(const Stage64 *st64, int cnt, const double2 *turn, double mx, double my,
                                              double mz, int st, int streams, double &re, double &im) {
     auto add = [&](const Stage64 &p) {
         const double t = mx * p.sx + my * p.sy + mz * p.sz;
         double sn, cs;
-        rmath::sincos2pi_tab<WIDE>(t, turn, &sn, &cs);
+        rmath::sincos2pi_tab<true>(t, turn, &sn, &cs);
         re = fma(p.q, cs, re);
         im = fma(p.q, sn, im);
     };

@@ -122,7 +122,7 @@ __global__ __launch_bounds__(1024, F64 ? 1 : 8) void k_sf_partial(int64_t n, con
             constexpr double tu = rmath::kTurnTab;
             if (have) st64[threadIdx.x] = Stage64{s[0] * tu, s[1] * tu, s[2] * tu, qj};
             __syncthreads();
-            if (st < streams) sum_staged64<true>(st64, cnt, turn, mx, my, mz, st, streams, re, im);
+            if (st < streams) sum_staged64(st64, cnt, turn, mx, my, mz, st, streams, re, im);
         } else {
             // fixed-point rule of the library: u = min(2^32 - 1, floor(frac(x/L) 2^32))
             uint32_t u[3];
