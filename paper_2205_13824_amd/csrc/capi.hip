@@ -151,13 +151,14 @@ rbsog_status fail_noctx(rbsog_status st, const char *fmt, ...) {
 // (particle, k) pairs of one evaluation up to which the structure factor runs
 // beside the near part on the second stream
 constexpr double kSideMaxWork = 4e9;
-// and from which it does on a kept list.  An edge between two queues of a step
-// graph costs some 5 us; below, the kernels beside the structure factor take no
-// longer than that.  Us per step on one stream | on two: FP32C 1,000 ions x 100
-// wave vectors 27 | 34, 26,998 x 130 40 | 45, 78,000 x 150 60 | 62, 150,000 x 100
-// 77 | 78, 100,000 x 300 80 | 77, 300,000 x 200 107 | 84; FP64 26,998 x 130 48 | 52,
-// 60,000 x 150 70 | 68, 110,000 x 150 96 | 86.
-constexpr double side_min_work(int prec) { return prec == RBSOG_FP64 ? 6e6 : 2e7; }
+// and above which it does on a kept list.  An edge between two queues of a step
+// graph costs some 5 us, and on one stream the structure factor, its reduction and
+// the build's first kernel share launches; from here on the overlap gives as much.
+// Us per step (or call) on two streams | on one: FP32C 1,000 ions x 100 wave vectors
+// 34 | 21, 26,998 x 130 45 | 33, 100,000 x 300 82 | 78, 250,000 x 180 113 | 111,
+// 300,000 x 200 108 | 110; FP64 60,000 x 150 69 | 62, 98,304 sites x 211 272 | 261,
+// 130,000 x 200 101 | 103.
+constexpr double side_min_work(int prec) { return prec == RBSOG_FP64 ? 2.2e7 : 5e7; }
 
 struct rbsog_ctx {
     int32_t nsys = 0;
