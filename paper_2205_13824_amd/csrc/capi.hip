@@ -1406,9 +1406,9 @@ void build_work(rbsog_ctx *c, const Tune &t, std::vector<ListItem> &near, std::v
     auto chunks_of = [&](const SysHost &h) { return (int32_t)std::max<int64_t>(1, (h.n + chunk - 1) / chunk); };
     // k tiles per structure-factor block: as the shapes say, or as many as leave
     // the batch enough blocks (the waves that a smaller group leaves free split
-    // the chunk further, but each block stages its particles anew: FP64, where
-    // the sum is long beside the staging, 98,304 sites x 211 29 us against 35 and
-    // 1,000 ions x 100 7.7 against 10; FP32C 1,000 ions 6.8 us against 7.6, but
+    // the chunk further, but an FP32C block stages its particles anew: FP64, whose
+    // sum is long beside that (as measured when it staged them too), 98,304 sites x
+    // 211 29 us against 35 and 1,000 ions x 100 7.7 against 10; FP32C 1,000 ions 6.8 us against 7.6, but
     // 26,998 ions x 130 10.0 against 9.4 and 77,781 x 150 17.4 against 14.5)
     const int64_t enough = c->prec == RBSOG_FP64 ? kRhoBlocks64 : kRhoBlocks32;
     int32_t kt_max = t.rho_kt > 0 ? std::min(t.rho_kt, 16) : 16;
