@@ -1394,8 +1394,9 @@ void tune_cache_store(const std::string &key, const Tune &t) {
     }
 }
 
-// Blocks that the structure factor's k tiles are split for by default.
-constexpr int64_t kRhoBlocks32 = 64, kRhoBlocks64 = 512;
+// Blocks that the FP32C structure factor's k tiles are split for by default.
+constexpr int64_t kRhoBlocks32 = 64;
+constexpr int64_t kCus = 256;
 
 // Work lists of the batch.  Near: runs of kListHomes slots of one system;
 // rho: particle chunks of about t.rho_chunk slots x k-tile groups; far: runs
@@ -1404,21 +1405,35 @@ void build_work(rbsog_ctx *c, const Tune &t, std::vector<ListItem> &near, std::v
                 std::vector<FarItem> &far) {
     const int64_t chunk = t.rho_chunk, fb = t.far_block;
     auto chunks_of = [&](const SysHost &h) { return (int32_t)std::max<int64_t>(1, (h.n + chunk - 1) / chunk); };
-    // k tiles per structure-factor block: as the shapes say, or as many as leave
-    // the batch enough blocks (the waves that a smaller group leaves free split
-    // the chunk further, but an FP32C block stages its particles anew: FP64, whose
-    // sum is long beside that (as measured when it staged them too), 98,304 sites x
-    // 211 29 us against 35 and 1,000 ions x 100 7.7 against 10; FP32C 1,000 ions 6.8 us against 7.6, but
-    // 26,998 ions x 130 10.0 against 9.4 and 77,781 x 150 17.4 against 14.5)
-    const int64_t enough = c->prec == RBSOG_FP64 ? kRhoBlocks64 : kRhoBlocks32;
+    // k tiles per structure-factor block: as the shapes say, or, FP32C, as many as
+    // leave the batch enough blocks (the waves that a smaller group leaves free
+    // split the chunk further, but each block stages its particles anew: 1,000 ions
+    // x 100 6.8 us against 7.6, but 26,998 ions x 130 10.0 against 9.4 and 77,781 x
+    // 150 17.4 against 14.5); FP64, which stages nothing, as many as give the CU of
+    // the most blocks the fewest tiles (480 | 960 blocks: 300,000 ions x 200 x 40 steps
+    // 7.58 | 7.76 ms; 430 | 860: 110,000 x 150 x 60 4.84 | 5.25; but 384 | 768: 98,304
+    // sites x 211 x 30 7.91 | 7.78; a tenth fewer at least: 192,000 sites x 500 x 20 in 480
+    // | 3,840 12.6 | 13.1)
     int32_t kt_max = t.rho_kt > 0 ? std::min(t.rho_kt, 16) : 16;
-    for (; t.rho_kt <= 0 && kt_max > 1; kt_max = (kt_max + 1) / 2) {
-        int64_t blocks = 0;
-        for (const SysHost &h : c->sys) {
-            const int32_t ktiles = (h.P + 63) / 64, kt = std::min(ktiles, kt_max);
-            blocks += (int64_t)chunks_of(h) * ((ktiles + kt - 1) / kt);
+    if (t.rho_kt <= 0) {
+        double least = 1e300;
+        for (int32_t kt_try = 16;; kt_try = (kt_try + 1) / 2) {
+            int64_t blocks = 0;
+            int32_t tiles = 1;
+            for (const SysHost &h : c->sys) {
+                const int32_t ktiles = (h.P + 63) / 64, kt = std::min(ktiles, kt_try);
+                blocks += (int64_t)chunks_of(h) * ((ktiles + kt - 1) / kt);
+                tiles = std::max(tiles, kt);
+            }
+            if (c->prec != RBSOG_FP64) {
+                kt_max = kt_try;
+                if (blocks >= kRhoBlocks32) break;
+            } else if (const double load = (double)((blocks + kCus - 1) / kCus * tiles); load < 0.9 * least) {
+                least = load;
+                kt_max = kt_try;
+            }
+            if (kt_try == 1) break;
         }
-        if (blocks >= enough) break;
     }
     int64_t pofs = 0, choff = 0;
     for (int32_t s = 0; s < c->nsys; ++s) {
