@@ -370,15 +370,19 @@ rbsog_status rbsog_debug_neighbors(rbsog_ctx *ctx, int32_t sys, int64_t *row_ptr
  *              m.u mod 2^32 on the 32-bit fixed-point coordinates of the
  *              rule above, hardware FP32 sin/cos (two particles of equal
  *              charge through the half sum and half difference of their
- *              phases), FP32 sums over runs of 32 particles added in FP64
+ *              phases), FP32 sums over runs of 32 particles added in FP64.
+ *              The halves may leave out the lowest bit of the difference of
+ *              two u while that shifts no phase of the call by more than 256
+ *              units of 2^-32 turns, half of the hardware sine's step
  *   rho_re, rho_im  device, n_k doubles each, written
  *   stream     hipStream_t to launch on (NULL: the null stream)
  * Asynchronous on `stream`; the result is deterministic (partial sums over
  * particle chunks, added in a fixed order).  Non-finite positions or charges
  * give unspecified values.  The partial sums live in device memory allocated
- * and freed on `stream` for the call (none for calls of one chunk).  E_ARG for sizes out of range or a null
- * pointer, E_OOM if the partial sums cannot be allocated, E_DEVICE if a launch
- * fails; the message is at rbsog_last_error(NULL). */
+ * and freed on `stream` for the call (none for calls of one chunk).  E_ARG for
+ * sizes out of range or a null pointer, E_OOM if the partial sums cannot be
+ * allocated, E_DEVICE if a launch fails; the message is at
+ * rbsog_last_error(NULL). */
 rbsog_status rbsog_structure_factor(int64_t n, const double *x, const double *q, const double *box, int64_t n_k,
                                     const int32_t *m, int32_t precision, double *rho_re, double *rho_im,
                                     void *stream);

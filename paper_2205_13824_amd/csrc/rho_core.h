@@ -38,15 +38,26 @@ __device__ __forceinline__ void fill_turns(double2 *turn) {
 // pair (u1, u2) is written as two records, h = u1 + ((u2 - u1) >> 1) with 2q
 // and d = u1 - h (so u1 = h + d and u2 = h - d up to one unit of 2^-32 of the
 // box: the pair's phases are m.h +- m.d mod 2^32), the particles left single
-// after all pairs as (u, q).  Returns the block's number of pairs; the records
-// fill st32[0, particles).  Ends with a barrier.
+// after all pairs as (u, q).  EVEN with `even` (the same in every thread): only
+// particles whose coordinates agree in their lowest bits are paired, whose
+// halves are exact, and more of them stay single.  Returns the block's number of
+// pairs; the records fill st32[0, particles).  Ends with a barrier.
+template <bool EVEN = false>
 __device__ __forceinline__ int stage_pairs(bool have, uint32_t ux, uint32_t uy, uint32_t uz, uint32_t qb, uint4 *st32,
-                                           int2 *wcnt) {
+                                           int2 *wcnt, bool even = false) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float q = __uint_as_float(qb);
     const bool pos = q > 0.f;
     const uint64_t all = __builtin_amdgcn_ballot_w64(have), plus = __builtin_amdgcn_ballot_w64(have && pos);
-    const uint64_t mine = pos ? plus : (all & ~plus);
+    uint64_t mine = pos ? plus : (all & ~plus);
+    if constexpr (EVEN) {
+        if (even) {
+            for (const uint32_t b : {ux, uy, uz}) {
+                const uint64_t odd = __builtin_amdgcn_ballot_w64((b & 1u) != 0u);
+                mine &= (b & 1u) ? odd : ~odd;
+            }
+        }
+    }
     const uint64_t lt = (1ull << lane) - 1ull;
     const uint64_t below = mine & lt, above = mine & ~(lt | (1ull << lane));
     const int rank = __builtin_popcountll(below), ncls = __builtin_popcountll(mine);

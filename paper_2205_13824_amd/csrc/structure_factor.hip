@@ -49,6 +49,15 @@ constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) double2 scratch[kScratchComplex];
 
+// FP32C pairs any two particles of equal charge while every wave vector of the
+// block has |m_x| + |m_y| + |m_z| up to this.  Half a pair's difference drops its
+// lowest bit, so one of the two stands a unit of 2^-32 of the box beside its place
+// and its phase up to |m|_1 units off: with 256 units of rounding (half of the
+// 2^-23 turns that the hardware sine takes) no more than the 512 that truncating
+// every phase would cost.  Larger vectors pair where the difference is even, and
+// no phase is off by more than its rounding.
+constexpr uint64_t kPairAnyMax = 256;
+
 // Shape of a call: k tiles and particle streams of a block, groups of k tiles,
 // chunks and particles per chunk.
 struct SfPlan {
@@ -105,6 +114,11 @@ __global__ __launch_bounds__(1024, F64 ? 1 : 8) void k_sf_partial(int64_t n, con
     const int64_t j0 = c * chunk;
     const int64_t j1 = j0 + chunk < n ? j0 + chunk : n;
     const double L[3] = {Lx, Ly, Lz};
+    bool even = false;
+    if constexpr (!F64) {
+        const uint64_t l1 = (uint64_t)llabs((long long)mx) + llabs((long long)my) + llabs((long long)mz);
+        even = __syncthreads_or(l1 > kPairAnyMax) != 0;
+    }
     double re = 0.0, im = 0.0;
     for (int64_t jb = j0; jb < j1; jb += kStage) {
         const int cnt = (int)(j1 - jb < kStage ? j1 - jb : kStage);
@@ -132,7 +146,7 @@ __global__ __launch_bounds__(1024, F64 ? 1 : 8) void k_sf_partial(int64_t n, con
                 w = w >= 0.0 ? (w > kTwo32 - 1.0 ? kTwo32 - 1.0 : w) : 0.0;
                 u[d] = (uint32_t)w;
             }
-            const int np = stage_pairs(have, u[0], u[1], u[2], __float_as_uint((float)qj), st32, wcnt);
+            const int np = stage_pairs<true>(have, u[0], u[1], u[2], __float_as_uint((float)qj), st32, wcnt, even);
             if (st < streams)
                 sum_staged32<true>(st32, np, cnt - 2 * np, (uint32_t)mx, (uint32_t)my, (uint32_t)mz, st, streams, re, im);
         }
