@@ -1052,66 +1052,53 @@ rbsog_status upload_by_id(rbsog_ctx *c, const double *host, double *dev, const c
     return fail(c, RBSOG_E_NONFINITE, "%s of particle %d is not finite", what, bad);
 }
 
-// The whole sum of Gaussians and its force weights as polynomials of y = 2 x /
-// r_c^2 - 1 over x in [0, r_c^2]: Chebyshev interpolation at kChebNodes nodes,
-// cut at each form's degree, in powers of y.  A form whose cut exceeds its
-// tolerance of the sum at x = 0 (its largest value) does not hold.
+// The whole sum of Gaussians and its force weights as polynomials of z = 1 +
+// zs x over x in [0, r_c^2] (zs as the kernel holds it): Chebyshev interpolation at
+// kChebNodes nodes, cut at each form's degree, in powers of z.  A form whose cut
+// exceeds its tolerance of the sum at z = 0 does not hold.
 constexpr int kChebNodes = 40;
 template <class Co>
-bool poly_form(const long double *c, double tol, Co &co, int which) {
-    constexpr int NP = sizeof(co.gp) / sizeof(co.gp[0]);
-    using R = std::remove_reference_t<decltype(co.ys)>;
-    long double cut = 0.0L, top = 0.0L;
-    for (int n = 0; n < kChebNodes; ++n) {
-        top += std::fabs(c[n]);
-        if (n >= NP) cut += std::fabs(c[n]);
-    }
-    // T_n in powers of y, by T_{n+1} = 2 y T_n - T_{n-1}
-    long double t0[NP + 1] = {1.0L}, t1[NP + 1] = {0.0L, 1.0L}, p[NP] = {};
-    for (int n = 0; n < NP; ++n) {
-        for (int k = 0; k < NP; ++k) p[k] += c[n] * t0[k];
-        long double t2[NP + 1];
-        for (int k = 0; k <= NP; ++k) t2[k] = (k ? 2.0L * t1[k - 1] : 0.0L) - t0[k];
-        std::copy(t1, t1 + NP + 1, t0);
-        std::copy(t2, t2 + NP + 1, t1);
-    }
-    for (int k = 0; k < NP; ++k) (which ? co.pp : co.gp)[k] = (R)p[k];
-    return cut <= tol * top;
-}
-
-void build_poly(SysHost &h) {
-    constexpr int NN = kChebNodes;
+bool poly_form(const SysHost &h, double tol, Co &co) {
+    constexpr int NN = kChebNodes, NP = sizeof(co.gp) / sizeof(co.gp[0]);
+    using R = std::remove_reference_t<decltype(co.zs)>;
     // cos(pi k / (2 NN)), k < 4 NN: the nodes and every T_n at them
     static const std::vector<long double> cosine = [] {
         std::vector<long double> t(4 * NN);
         for (int k = 0; k < 4 * NN; ++k) t[k] = std::cos(3.141592653589793238462643383279502884L * k / (2 * NN));
         return t;
     }();
-    const double rc2 = h.rc * h.rc;
+    co.zs = (R)(-1.0 / (h.rc * h.rc));
     long double f[2][NN] = {};
     for (int j = 0; j < NN; ++j) {
-        const long double x = 0.5L * rc2 * (1.0L + cosine[2 * j + 1]);
+        const long double z = 0.5L * (1.0L + cosine[2 * j + 1]), x = (z - 1.0L) / (long double)co.zs;
         for (size_t l = 0; l < h.s.size(); ++l) {
             const long double a = 1.0L / ((long double)h.s[l] * h.s[l]);
-            const long double e = h.omega[l] * std::exp((double)(-x * a));
+            const long double e = h.omega[l] * std::exp(-x * a);
             f[0][j] += 2.0L * a * e;
             f[1][j] += e;
         }
     }
-    bool ok64 = true, ok32 = true;
+    bool ok = true;
     for (int which = 0; which < 2; ++which) {
-        long double c[NN] = {};
+        long double c[NN] = {}, cut = 0.0L;
         for (int n = 0; n < NN; ++n) {
             for (int j = 0; j < NN; ++j) c[n] += f[which][j] * cosine[n * (2 * j + 1) % (4 * NN)];
             c[n] *= (n ? 2.0L : 1.0L) / NN;
+            if (n >= NP) cut += std::fabs(c[n]);
         }
-        ok64 = poly_form(c, kPolyTol64, h.co64, which) && ok64;
-        ok32 = poly_form(c, kPolyTol32, h.co32, which) && ok32;
+        // T_n(2 z - 1) in powers of z, by T_{n+1} = 2 (2 z - 1) T_n - T_{n-1}
+        long double t0[NP + 1] = {1.0L}, t1[NP + 1] = {-1.0L, 2.0L}, p[NP] = {};
+        for (int n = 0; n < NP; ++n) {
+            for (int k = 0; k < NP; ++k) p[k] += c[n] * t0[k];
+            long double t2[NP + 1];
+            for (int k = 0; k <= NP; ++k) t2[k] = (k ? 4.0L * t1[k - 1] : 0.0L) - 2.0L * t1[k] - t0[k];
+            std::copy(t1, t1 + NP + 1, t0);
+            std::copy(t2, t2 + NP + 1, t1);
+        }
+        for (int k = 0; k < NP; ++k) (which ? co.pp : co.gp)[k] = (R)p[k];
+        ok = ok && cut <= tol * p[0];
     }
-    h.co64.poly = ok64 ? 1 : 0;
-    h.co32.poly = ok32 ? 1 : 0;
-    h.co64.ys = 2.0 / rc2;
-    h.co32.ys = (float)(2.0 / rc2);
+    return ok;
 }
 
 // Split coefficients of the near kernel for one system.
@@ -1159,7 +1146,8 @@ void build_split(SysHost &h, int nexp64, int nexp32) {
         h.co32.pt[k] = (float)pf.first;
         h.co32.ft[k] = (float)pf.second;
     }
-    build_poly(h);
+    h.co64.poly = poly_form(h, kPolyTol64, h.co64) ? 1 : 0;
+    h.co32.poly = poly_form(h, kPolyTol32, h.co32) ? 1 : 0;
 }
 
 // Cell grid and near-list thresholds of one system for a skin.  skin > 0:

@@ -926,11 +926,11 @@ template <bool F64, int FORM, bool WE>
 struct PairConst {
     using R = typename std::conditional<F64, double, float>::type;
     static constexpr int NP = (F64 ? kPolyDeg64 : kPolyDeg32) + 1;
-    R ys, gp[FORM == kFormPoly ? NP : 1], pp[FORM == kFormPoly && WE ? NP : 1];
+    R zs, gp[FORM == kFormPoly ? NP : 1], pp[FORM == kFormPoly && WE ? NP : 1];
     __device__ __forceinline__ void load(typename CoefOf<F64>::type *co) {
         if constexpr (FORM == kFormPoly) {
-            ys = co->ys;
-            asm volatile("" : "+s"(ys));
+            zs = co->zs;
+            asm volatile("" : "+s"(zs));
 #pragma unroll
             for (int k = 0; k < NP; ++k) {
                 gp[k] = co->gp[k];
@@ -988,15 +988,19 @@ __device__ __forceinline__ void pair_kernel(const PairConst<F64, FORM, WE> &pc, 
         if constexpr (F64) rinv = rsqrt64(x);
         else rinv = __builtin_amdgcn_rsqf(x);
         if constexpr (FORM == kFormPoly) {
+            // the constants are taken from 1/r^3 and 1/r first, which loses
+            // nothing where the sum is close to them
             constexpr int NP = PairConst<F64, FORM, WE>::NP;
-            const R y = f(x, pc.ys, (R)-1);
+            const R z = f(x, pc.zs, (R)1);
             gs = pc.gp[NP - 1];
 #pragma unroll
-            for (int k = NP - 2; k >= 0; --k) gs = f(gs, y, pc.gp[k]);
+            for (int k = NP - 2; k >= 1; --k) gs = f(gs, z, pc.gp[k]);
+            gk = f(-gs, z, f(rinv, rinv * rinv, -pc.gp[0]));
             if constexpr (WE) {
                 ph = pc.pp[NP - 1];
 #pragma unroll
-                for (int k = NP - 2; k >= 0; --k) ph = f(ph, y, pc.pp[k]);
+                for (int k = NP - 2; k >= 1; --k) ph = f(ph, z, pc.pp[k]);
+                hk = f(-ph, z, rinv - pc.pp[0]);
             }
         } else {
             constexpr int NT = (F64 ? kTailDeg64 : kTailDeg32) + 1;
@@ -1021,9 +1025,9 @@ __device__ __forceinline__ void pair_kernel(const PairConst<F64, FORM, WE> &pc, 
 #pragma unroll
             for (int l = 0; l < NE; ++l) term(l);
             for (int l = NE; l < co->nexp; ++l) term(l);
+            gk = f(rinv, rinv * rinv, -gs);
+            hk = rinv - ph;
         }
-        gk = f(rinv, rinv * rinv, -gs);
-        hk = rinv - ph;
     }
 }
 

@@ -72,13 +72,19 @@ constexpr int kTailDeg32 = 6;
 constexpr int kMaxExp = 24;  // narrow Gaussians per split (more is rejected)
 
 // List pass, polynomial form: where the whole sum of Gaussians over x in [0,
-// r_c^2] is a polynomial of y = 2 x / r_c^2 - 1 of degree kPolyDeg to below
-// kPolyTol of its value at 0 (Chebyshev coefficients of e^{-a y} fall like
-// (a/2)^n / n!, a = r_c^2 / (2 s_0^2): 1.9 for Table 1 row 2, 0.99 for row 1),
-// it takes the place of the exponentials and the tail; other splits keep them.
+// r_c^2] is a polynomial of degree kPolyDeg to below kPolyTol of its value at
+// r_c^2, its smallest (Chebyshev coefficients fall like (a/2)^n / n!, a = r_c^2 /
+// (2 s_0^2): 1.9 for Table 1 row 2, 0.99 for row 1), it takes the place of the
+// exponentials and the tail; other splits keep them.  In powers of z = 1 - x/r_c^2:
+// towards r_c, where the sum comes close to 1/r and 1/r^3 and its rounding counts
+// most, z goes to 0 and the leading powers carry one sign, so that little more than
+// the constant's rounding remains.  (Powers of 2 x/r_c^2 - 1 cancel there: rounding
+// of the sum in units of 2^-24 of 1/r^3, relative RMS over r_c/10 to r_c, row 2, r_c
+// 10 | 3.5: the exponentials 0.70 | 0.70, those powers 1.69 | 0.81, these 0.64 | 0.60.
+// FP32C needs degree 11: at 10 the terms left out are as large as the rounding.)
 constexpr int kPolyDeg64 = 18;
-constexpr int kPolyDeg32 = 10;
-constexpr double kPolyTol64 = 5e-16;
+constexpr int kPolyDeg32 = 11;
+constexpr double kPolyTol64 = 1e-16;
 constexpr double kPolyTol32 = 1e-8;
 
 template <typename R, int NT, int NP>
@@ -90,9 +96,9 @@ struct SplitCoef {
     R ft[NT];       // sum_{l>=nexp} 2 omega_l/s_l^2 e^{-x/s_l^2} = sum_k ft[k] x^k
     int32_t nexp;
     int32_t poly;   // the polynomial form holds
-    R ys;           // 2 / r_c^2
-    R gp[NP];       // sum_l 2 omega_l/s_l^2 e^{-x/s_l^2} = sum_k gp[k] y^k
-    R pp[NP];       // sum_l omega_l e^{-x/s_l^2} = sum_k pp[k] y^k
+    R zs;           // -1 / r_c^2: z = 1 + zs x
+    R gp[NP];       // sum_l 2 omega_l/s_l^2 e^{-x/s_l^2} = sum_k gp[k] z^k
+    R pp[NP];       // sum_l omega_l e^{-x/s_l^2} = sum_k pp[k] z^k
 };
 using SplitCoef64 = SplitCoef<double, kTailDeg64 + 1, kPolyDeg64 + 1>;
 using SplitCoef32 = SplitCoef<float, kTailDeg32 + 1, kPolyDeg32 + 1>;
