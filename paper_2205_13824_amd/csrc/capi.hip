@@ -2209,10 +2209,6 @@ rbsog_status rbsog_forces(rbsog_ctx *c, double *F_out, double *E_out) {
     c->builds_made = c->stat->nbuild;
     TRY(check_list(c, c->stat->flag, c->stat->pmax));
     const int32_t bad = c->stat->bad;
-    if (bad != INT32_MAX) {
-        const int32_t none = INT32_MAX;
-        HIPCHK(c, hipMemcpy(c->bad, &none, sizeof none, hipMemcpyHostToDevice));
-    }
     TRY(check_flag(c, c->stat->flag));
     // without a kick no kernel of the evaluation looks at the sum of the two forces
     if (bad != INT32_MAX) return fail(c, RBSOG_E_NONFINITE, "force on particle %d is not finite", bad);

@@ -82,15 +82,16 @@ __global__ __launch_bounds__(kBlock) void k_forces_out(int64_t n, const int32_t 
 }
 
 // Error flags, the largest list count, the builds made and the finiteness
-// verdict to the host (one kernel in place of a copy each).
+// verdict to the host (one kernel in place of a copy each); *bad holds INT32_MAX
+// again afterwards, whatever the host makes of the report.
 __global__ void k_status(const int32_t *__restrict__ flag, const int32_t *__restrict__ pmax,
-                         const int64_t *__restrict__ nbuild, const int32_t *__restrict__ bad,
-                         IoStat *__restrict__ st) {
+                         const int64_t *__restrict__ nbuild, int32_t *__restrict__ bad, IoStat *__restrict__ st) {
     if (threadIdx.x != 0) return;
     st->nbuild = *nbuild;
     st->flag = *flag;
     st->pmax = *pmax;
     st->bad = *bad;
+    *bad = INT_MAX;
 }
 
 // Kinetic energy of the velocities as they stand: per far item and wave (a
@@ -143,7 +144,7 @@ void launch_forces_out(const EvalArgs &a, double *rows, int32_t *bad, hipStream_
     hipLaunchKernelGGL(k_forces_out, dim3(blocks_for(a.N)), dim3(kBlock), 0, s, a.N, a.cur.id, a.Fn, a.Ff, rows, bad);
 }
 
-void launch_status(const EvalArgs &a, const int32_t *bad, IoStat *st, hipStream_t s) {
+void launch_status(const EvalArgs &a, int32_t *bad, IoStat *st, hipStream_t s) {
     hipLaunchKernelGGL(k_status, dim3(1), dim3(64), 0, s, a.flag, a.pmax, a.nbuild, bad, st);
 }
 

@@ -389,8 +389,8 @@ void launch_rows_in(const EvalArgs &a, const double *rows, double *dst, int32_t 
 void launch_rows_out(const EvalArgs &a, const double *src, double *rows, bool wrap, hipStream_t s);
 // F_N + F* into rows, the smallest index of a non-finite force to *bad
 void launch_forces_out(const EvalArgs &a, double *rows, int32_t *bad, hipStream_t s);
-// the error flags, the largest list count, the builds made and *bad to st
-void launch_status(const EvalArgs &a, const int32_t *bad, IoStat *st, hipStream_t s);
+// the error flags, the largest list count, the builds made and *bad to st; *bad reset
+void launch_status(const EvalArgs &a, int32_t *bad, IoStat *st, hipStream_t s);
 // kinetic energy of every system from the velocities as they stand
 void launch_kinetic_now(const EvalArgs &a, const FarItem *items, int32_t nitems, int32_t block_size, hipStream_t s);
 
