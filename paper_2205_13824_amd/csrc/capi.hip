@@ -1009,25 +1009,43 @@ struct Fetch {
     int64_t bytes;
 };
 
-// The pieces to the host, after everything enqueued; waits for them.
-rbsog_status fetch(rbsog_ctx *c, std::initializer_list<Fetch> list) {
-    int64_t off = 0;
+// The pieces to the host, after everything enqueued; waits for them.  `check`, given
+// the outcome of what was enqueued (the status block), comes before any of the
+// caller's memory is written and ends the transfer unless it returns RBSOG_OK.
+template <class Check>
+rbsog_status fetch(rbsog_ctx *c, std::initializer_list<Fetch> list, Check check) {
+    constexpr bool CHECKED = !std::is_same_v<Check, std::nullptr_t>;
+    // where each piece goes: the offset in pinned memory, or -1 for its own
+    int64_t off = 0, at[4];
+    bool direct = false;
+    size_t k = 0;
     for (const Fetch &f : list) {
-        if (!f.bytes) continue;
         const bool pin = off + f.bytes <= c->pin_bytes;
-        HIPCHK(c, hipMemcpyAsync(pin ? (void *)(c->pin + off) : f.host, f.dev, (size_t)f.bytes, hipMemcpyDeviceToHost,
-                                 c->stream));
+        at[k] = pin ? off : -1;
         if (pin) off += f.bytes;
+        else direct = true;
+        if (f.bytes && (pin || !CHECKED))
+            HIPCHK(c, hipMemcpyAsync(pin ? (void *)(c->pin + at[k]) : f.host, f.dev, (size_t)f.bytes,
+                                     hipMemcpyDeviceToHost, c->stream));
+        ++k;
     }
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    off = 0;
-    for (const Fetch &f : list)
-        if (f.bytes && off + f.bytes <= c->pin_bytes) {
-            std::memcpy(f.host, c->pin + off, (size_t)f.bytes);
-            off += f.bytes;
-        }
+    if constexpr (CHECKED) {
+        TRY(check());
+        k = 0;
+        for (const Fetch &f : list)
+            if (at[k++] < 0)
+                HIPCHK(c, hipMemcpyAsync(f.host, f.dev, (size_t)f.bytes, hipMemcpyDeviceToHost, c->stream));
+        if (direct) HIPCHK(c, hipStreamSynchronize(c->stream));
+    }
+    k = 0;
+    for (const Fetch &f : list) {
+        if (f.bytes && at[k] >= 0) std::memcpy(f.host, c->pin + at[k], (size_t)f.bytes);
+        ++k;
+    }
     return RBSOG_OK;
 }
+rbsog_status fetch(rbsog_ctx *c, std::initializer_list<Fetch> list) { return fetch(c, list, nullptr); }
 
 // host n x 3 in caller order -> device SoA in the current cell order, through
 // the (idle) gather buffer; a non-finite entry leaves `dev` as it was.
@@ -2205,11 +2223,14 @@ rbsog_status rbsog_forces(rbsog_ctx *c, double *F_out, double *E_out) {
     HIPCHK(c, hipGetLastError());
     const int64_t fb = F_out ? 3 * c->N * (int64_t)sizeof(double) : 0;
     const int64_t eb = E_out ? 4 * (int64_t)c->nsys * (int64_t)sizeof(double) : 0;
-    TRY(fetch(c, {{c->E, E_out, eb}, {rows, F_out, fb}}));
-    c->builds_made = c->stat->nbuild;
-    TRY(check_list(c, c->stat->flag, c->stat->pmax));
-    const int32_t bad = c->stat->bad;
-    TRY(check_flag(c, c->stat->flag));
+    IoStat st{};
+    TRY(fetch(c, {{c->E, E_out, eb}, {rows, F_out, fb}}, [&]() -> rbsog_status {
+        st = *c->stat;
+        c->builds_made = st.nbuild;
+        TRY(check_list(c, st.flag, st.pmax));
+        return check_flag(c, st.flag);
+    }));
+    const int32_t bad = st.bad;
     // without a kick no kernel of the evaluation looks at the sum of the two forces
     if (bad != INT32_MAX) return fail(c, RBSOG_E_NONFINITE, "force on particle %d is not finite", bad);
     if (E_out)
