@@ -419,6 +419,20 @@ rbsog_status rbsog_debug_pairs(rbsog_ctx *ctx, int32_t sys, int32_t *kinds, int6
                                int64_t cap);
 rbsog_status rbsog_debug_list(rbsog_ctx *ctx, int32_t sys, int64_t *row_ptr, int32_t *cols, int64_t cap);
 
+/* Debug report of the kernels that the context's next evaluation takes, chosen by
+ * its sizes and options (a step's if stepping is nonzero, else that of
+ * rbsog_forces).  Nothing is launched.
+ *   out  host, n int32 (1 <= n <= RBSOG_ROUTE_COUNT), entry i for RBSOG_ROUTE_i */
+enum {
+    RBSOG_ROUTE_NEAR_FORM = 0,  /* list pass: 0 exponentials, 1 one polynomial, 2 core-shell table */
+    RBSOG_ROUTE_STREAMS = 1,    /* 2: the structure factor runs beside the near part */
+    RBSOG_ROUTE_SHARED = 2,     /* 1: it and its reduction share the launches of the near part */
+    RBSOG_ROUTE_ONE_BLOCK = 3,  /* 1: one block re-sorts the whole batch */
+    RBSOG_ROUTE_FAR_WAVES = 4,  /* waves that share the records of a far group of 64 particles */
+    RBSOG_ROUTE_COUNT = 5
+};
+rbsog_status rbsog_debug_routes(rbsog_ctx *ctx, int32_t stepping, int32_t *out, int32_t n);
+
 /* Per-kernel timing with HIP events; later steps launch kernel by kernel (no
  * graphs).  enable 1: every kernel alone on the context's stream (its time
  * with the whole device); enable 2: as in the steps, the structure factor (and

@@ -676,6 +676,25 @@ EvalArgs make_args(rbsog_ctx *c, bool stepping, double dt) {
     return a;
 }
 
+// The kernels that an evaluation takes.
+struct Route {
+    bool fork;   // the structure factor on the second stream, beside the near part
+    bool carry;  // one stream: it shares a launch with the build's first kernel, its reduction one with the list pass
+    bool one;    // the whole batch re-sorted by one block
+};
+Route route_of(const rbsog_ctx *c, const EvalArgs &a, bool stepping) {
+    Route r;
+    // one stream while profiling kernels alone, and for systems with a lot of far work
+    r.fork = c->prof_on != 1 && c->use_side();
+    r.carry = !r.fork && !c->prof_on && !a.always_build && !c->dbg_pairs && c->work <= kSideMaxWork && a.K > 0 &&
+              !a.zmode && a.red_waves == 1;
+    // steps of a small batch on a kept list re-sort in one kernel (few of them
+    // build); an evaluation that the host has asked to build takes the kernels
+    // that use the whole device
+    r.one = stepping && !a.always_build && resort_in_one(a);
+    return r;
+}
+
 // Enqueue one force evaluation (with the velocity-Verlet kick-drift before
 // and the closing kick after it when stepping).  The list-build kernels run
 // every time and return at once unless the displacement check (or the host)
@@ -705,17 +724,13 @@ rbsog_status enqueue_eval(rbsog_ctx *c, bool stepping, double dt, bool kinetic, 
     if (head) TRY(timed(c, K_KDQ, [&] { launch_kdq(a, s); }));
     // the structure factor and its reduction need the copy of the positions
     // taken by the kick/drift (or the previous far) kernel only: they run on the
-    // side stream beside the re-sort and the near part (one stream while
-    // profiling kernels alone, and for systems with a lot of far work)
-    const bool fork = c->prof_on != 1 && c->use_side();
+    // side stream beside the re-sort and the near part, or share its launches
+    const Route rt = route_of(c, a, stepping);
+    const bool fork = rt.fork, carry = rt.carry, one = rt.one;
     // building at every step, the far force joins them there (the near part
     // is long enough to hide it); it is then read back in the new order
     const bool far_side = a.always_build != 0;
     const int32_t fb = c->tune.far_block;
-    // small evaluations on one stream: the structure factor shares a launch with the
-    // build's first kernel, its reduction one with the list pass
-    const bool carry = !fork && !c->prof_on && !a.always_build && !c->dbg_pairs && c->work <= kSideMaxWork &&
-                       a.K > 0 && !a.zmode && a.red_waves == 1;
     if (fork) {
         HIPCHK(c, hipEventRecord(c->ev_fork, s));
         HIPCHK(c, hipStreamWaitEvent(c->side, c->ev_fork, 0));
@@ -725,10 +740,6 @@ rbsog_status enqueue_eval(rbsog_ctx *c, bool stepping, double dt, bool kinetic, 
             TRY(timed_on(c, K_FARSIDE, c->side, [&] { launch_far_side(a, f64, c->far_items, c->n_far, fb, c->side); }));
         HIPCHK(c, hipEventRecord(c->ev_join, c->side));
     }
-    // steps of a small batch on a kept list re-sort in one kernel (few of them
-    // build); an evaluation that the host has asked to build takes the kernels
-    // that use the whole device
-    const bool one = stepping && !a.always_build && resort_in_one(a);
     if (carry) launch_rho_build(a, f64, c->rho_items, c->n_rho, one, s);
     if (one && !carry) {
         TRY(timed(c, K_SORTG, [&] { launch_resort_one(a, s); }));
@@ -2714,6 +2725,22 @@ rbsog_status rbsog_debug_list(rbsog_ctx *c, int32_t sys, int64_t *row_ptr, int32
         }
     }
     return csr_of_pairs(c, h, pairs, row_ptr, cols, cap);
+}
+
+rbsog_status rbsog_debug_routes(rbsog_ctx *c, int32_t stepping, int32_t *out, int32_t n) {
+    TRY(check_ctx(c));
+    if (!out || n < 1 || n > RBSOG_ROUTE_COUNT)
+        return fail(c, RBSOG_E_ARG, "need room for 1 to %d entries", (int)RBSOG_ROUTE_COUNT);
+    const EvalArgs a = make_args(c, stepping != 0, 0.0);
+    const Route r = route_of(c, a, stepping != 0);
+    int32_t all[RBSOG_ROUTE_COUNT];
+    all[RBSOG_ROUTE_NEAR_FORM] = a.near_form;
+    all[RBSOG_ROUTE_STREAMS] = r.fork ? 2 : 1;
+    all[RBSOG_ROUTE_SHARED] = r.carry ? 1 : 0;
+    all[RBSOG_ROUTE_ONE_BLOCK] = r.one ? 1 : 0;
+    all[RBSOG_ROUTE_FAR_WAVES] = far_waves(a, c->prec == RBSOG_FP64);
+    std::copy(all, all + n, out);
+    return RBSOG_OK;
 }
 
 rbsog_status rbsog_profile(rbsog_ctx *c, int32_t enable) {

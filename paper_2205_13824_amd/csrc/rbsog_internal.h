@@ -456,6 +456,8 @@ void launch_rho_reduce(const EvalArgs &a, hipStream_t s);
 // (items of at most block_size particles, block_size in {64, 128, 256})
 void launch_far(const EvalArgs &a, bool f64, const FarItem *items, int32_t nitems, int32_t block_size,
                 hipStream_t s);
+// waves that share the records of a group of 64 particles in it
+int32_t far_waves(const EvalArgs &a, bool f64);
 void launch_far_side(const EvalArgs &a, bool f64, const FarItem *items, int32_t nitems, int32_t block_size,
                      hipStream_t s);
 void launch_far_finish(const EvalArgs &a, const FarItem *items, int32_t nitems, int32_t block_size, hipStream_t s);

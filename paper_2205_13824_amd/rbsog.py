@@ -35,7 +35,7 @@ EXPORTS = ("rbsog_default_opts", "rbsog_sog_table1", "rbsog_init", "rbsog_init_b
            "rbsog_set_nose_hoover", "rbsog_get_kinetic", "rbsog_set_msd_origin", "rbsog_get_msd",
            "rbsog_structure_factor", "rbsog_structure_factor_noalloc", "rbsog_get_forces_subset",
            "rbsog_debug_record_pairs", "rbsog_debug_pairs", "rbsog_debug_list", "rbsog_save_state",
-           "rbsog_load_state", "rbsog_probe_count", "rbsog_probe_name", "rbsog_probe_rates")
+           "rbsog_load_state", "rbsog_debug_routes", "rbsog_probe_count", "rbsog_probe_name", "rbsog_probe_rates")
 
 
 class RbsogError(RuntimeError):
@@ -105,6 +105,7 @@ def lib():
             "rbsog_load_state": (i32, [vp, vp, i64]),
             "rbsog_debug_pairs": (i32, [vp, i32, vp, vp, vp, i64]),
             "rbsog_debug_list": (i32, [vp, i32, vp, vp, i64]),
+            "rbsog_debug_routes": (i32, [vp, i32, vp, i32]),
             "rbsog_profile": (i32, [vp, i32]),
             "rbsog_profile_read": (i32, [vp, i32, P(ctypes.c_char_p), P(dbl), P(i64)]),
             "rbsog_sync": (i32, [vp]),
@@ -387,6 +388,16 @@ def rbsog_debug_pairs(ctx, sys: int = 0):
 def rbsog_debug_list(ctx, sys: int = 0):
     """(row_ptr, cols): the near list of the latest build (CSR over local ids)."""
     return _csr_call(ctx, sys, lib().rbsog_debug_list)
+
+
+ROUTES = ("near_form", "streams", "shared", "one_block", "far_waves")
+
+
+def rbsog_debug_routes(ctx, stepping: bool = True) -> dict:
+    """The kernels of the next evaluation, by name."""
+    out = np.zeros(len(ROUTES), dtype=np.int32)
+    _check(lib().rbsog_debug_routes(ctx, int(stepping), _ptr(out), out.size), ctx)
+    return dict(zip(ROUTES, out.tolist()))
 
 
 def rbsog_profile(ctx, enable):

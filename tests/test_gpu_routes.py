@@ -1,0 +1,73 @@
+"""Which kernels an evaluation takes, by what rbsog_debug_routes reports, at the sizes
+and options where the choice changes: the list pass's pair kernel by the split (the
+results of its forms agree, so that only the report tells them apart) and the waves
+that share a far group's records."""
+import numpy as np
+import pytest
+
+from paper_2205_13824_amd import rbsog as R
+
+pytestmark = pytest.mark.gpu
+
+F64, F32C = R.RBSOG_FP64, R.RBSOG_FP32C
+
+
+def _batch(sizes, P, prec, rc=3.0, rows=None, **kw):
+    rng = np.random.default_rng(sum(sizes))
+    pos, q, box = [], [], []
+    for n in sizes:
+        L = max(10.0, (n / 0.1) ** (1 / 3))
+        box.append(np.array([L, L, L]))
+        pos.append(rng.random((n, 3)) * L)
+        q.append(np.where(np.arange(n) % 2 == 0, 1.0, -1.0))
+    sogs = [R.rbsog_sog_table1(row, rc) for row in rows] if rows else None
+    return R.Batch(pos, q, box, rc, P, list(range(len(sizes))), precision=prec, sogs=sogs, **kw)
+
+
+def _routes(b, stepping=True):
+    r = R.rbsog_debug_routes(b.ctx, stepping)
+    b.close()
+    return r
+
+
+@pytest.mark.parametrize("prec", [F64, F32C])
+@pytest.mark.parametrize("rc", [1.0, 3.5, 4.9])
+@pytest.mark.parametrize("rows,form", [([1], 1), ([2], 1), ([3], 0), ([4], 0), ([5], 0), ([2, 1, 2], 1), ([2, 3, 1], 0)])
+def test_pair_kernel_of_the_list_pass(prec, rc, rows, form):
+    assert _routes(_batch([200] * len(rows), 8, prec, rc=rc, rows=rows))["near_form"] == form
+
+
+def test_pair_kernel_of_the_core_shell_table():
+    assert _routes(_batch([200], 8, F32C, near_table=True))["near_form"] == 2
+
+
+# the waves that test_gpu_far_split.py's cases are about
+@pytest.mark.parametrize("sizes,P,f64,f32", [([64], 2, 1, 1), ([1000], 31, 4, 4), ([1002], 65, 16, 16),
+                                             ([1000], 4357, 16, 16), ([20002], 129, 16, 8), ([40000], 97, 8, 4),
+                                             ([66000], 33, 4, 2), ([132000], 21, 2, 1), ([264000], 9, 1, 1),
+                                             ([500, 64, 3070], 40, 8, 8)])
+def test_waves_of_a_far_group(sizes, P, f64, f32):
+    assert _routes(_batch(sizes, P, F64))["far_waves"] == f64
+    assert _routes(_batch(sizes, P, F32C))["far_waves"] == f32
+
+
+# two streams from 5e7 (FP64 2.2e7) particles x wave vectors on, up to 4e9; one block
+# re-sorts steps of up to 8,192 particles
+@pytest.mark.parametrize("prec,sizes,P,streams,one", [(F32C, [8192], 100, 1, 1), (F32C, [8194], 100, 1, 0),
+                                                      (F32C, [100000], 500, 1, 0), (F32C, [100000], 502, 2, 0),
+                                                      (F64, [100000], 220, 1, 0), (F64, [100000], 222, 2, 0),
+                                                      (F64, [4000, 90], 100, 1, 1)])
+def test_streams_and_shared_launches(prec, sizes, P, streams, one):
+    b = _batch(sizes, P, prec)
+    calls = R.rbsog_debug_routes(b.ctx, False)
+    assert (calls["streams"], calls["shared"], calls["one_block"]) == (streams, 2 - streams, 0)
+    steps = _routes(b)
+    assert (steps["streams"], steps["shared"], steps["one_block"]) == (streams, 2 - streams, one)
+
+
+def test_room_is_checked():
+    b = _batch([100], 8, F32C)
+    out = np.zeros(8, dtype=np.int32)
+    for args in ((None, 1), (R._ptr(out), 0), (R._ptr(out), len(R.ROUTES) + 1)):
+        assert R.lib().rbsog_debug_routes(b.ctx, 1, *args) == -1
+    b.close()
