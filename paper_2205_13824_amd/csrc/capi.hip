@@ -157,8 +157,12 @@ constexpr double kSideMaxWork = 4e9;
 // Us per step (or call) on two streams | on one: FP32C 1,000 ions x 100 wave vectors
 // 34 | 21, 26,998 x 130 45 | 33, 100,000 x 300 82 | 78, 250,000 x 180 113 | 111,
 // 300,000 x 200 108 | 110; FP64 60,000 x 150 69 | 62, 98,304 sites x 211 272 | 261,
-// 130,000 x 200 101 | 103.
-constexpr double side_min_work(int prec) { return prec == RBSOG_FP64 ? 2.2e7 : 5e7; }
+// 130,000 x 200 101 | 103.  With a zero-frequency mode term, whose dipole takes a
+// launch more, from fewer pairs on: FP32C 100,000 x 100 57.1 | 54.8, 200,000 x 90 64.7 |
+// 66.7, 200,000 x 200 75.8 | 81.8; FP64 100,000 x 100 62.7 | 65.2.
+constexpr double side_min_work(int prec, bool zmode) {
+    return (prec == RBSOG_FP64 ? 2.2e7 : 5e7) * (zmode ? 0.3 : 1.0);
+}
 
 struct rbsog_ctx {
     int32_t nsys = 0;
@@ -274,10 +278,12 @@ struct rbsog_ctx {
     // part: when its (particle, k) work, sum of n P, is small enough that the two
     // do not each fill the device (<= kSideMaxWork; larger systems run the kernels
     // one after the other: both are bound by vector issue there, and the overlap
-    // only shares the same units) and, on a kept list, large enough to pay for the
-    // two edges between the queues (> side_min_work)
+    // only shares the same units) and, where one stream could share launches,
+    // large enough to pay for the two edges between the queues (> side_min_work)
     double work = 0.0;
-    bool use_side() const { return work <= kSideMaxWork && (!(skin_cur > 0.0) || work > side_min_work(prec)); }
+    bool use_side(bool shared, bool zmode) const {
+        return work <= kSideMaxWork && (!shared || work > side_min_work(prec, zmode));
+    }
     hipGraph_t graph[2][GV_COUNT] = {};
     hipGraphExec_t graph_exec[2][GV_COUNT] = {};
     double graph_dt_m[2][GV_COUNT] = {};
@@ -684,10 +690,12 @@ struct Route {
 };
 Route route_of(const rbsog_ctx *c, const EvalArgs &a, bool stepping) {
     Route r;
-    // one stream while profiling kernels alone, and for systems with a lot of far work
-    r.fork = c->prof_on != 1 && c->use_side();
-    r.carry = !r.fork && !c->prof_on && !a.always_build && !c->dbg_pairs && c->work <= kSideMaxWork && a.K > 0 &&
-              !a.zmode && a.red_waves == 1;
+    // one stream while profiling kernels alone, and for systems with a lot of far
+    // work; evaluations that cannot share the launches keep two streams whatever
+    // their size, as one stream would put every kernel behind the other
+    const bool can = !a.always_build && a.K > 0 && a.red_waves == 1;
+    r.fork = c->prof_on != 1 && c->use_side(can, a.zmode != 0);
+    r.carry = can && !r.fork && !c->prof_on && !c->dbg_pairs && c->work <= kSideMaxWork;
     // steps of a small batch on a kept list re-sort in one kernel (few of them
     // build); an evaluation that the host has asked to build takes the kernels
     // that use the whole device
@@ -754,6 +762,7 @@ rbsog_status enqueue_eval(rbsog_ctx *c, bool stepping, double dt, bool kinetic, 
     } else {
         TRY(timed(c, K_LIST, [&] { launch_list_build(a, f64, c->list_items, c->n_list, c->build_slots, s, !one); }));
         TRY(timed(c, K_NEAR, [&] { launch_near(a, f64, c->list_items, c->n_list, s, carry); }));
+        if (carry) launch_dipole(a, s);
     }
     if (fork) {
         HIPCHK(c, hipStreamWaitEvent(s, c->ev_join, 0));

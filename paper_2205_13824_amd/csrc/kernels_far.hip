@@ -654,6 +654,10 @@ void launch_rho_reduce(const EvalArgs &a, hipStream_t s) {
     if (a.K <= 0) return;
     if (a.red_waves == 4) hipLaunchKernelGGL(k_rho_reduce_block, dim3((unsigned)a.K), dim3(256), 0, s, a);
     else hipLaunchKernelGGL(k_rho_reduce, dim3((unsigned)((a.K + 3) / 4)), dim3(256), 0, s, a);
+    launch_dipole(a, s);
+}
+
+void launch_dipole(const EvalArgs &a, hipStream_t s) {
     if (a.zmode) hipLaunchKernelGGL(k_dipole, dim3((unsigned)a.nsys), dim3(256), 0, s, a);
 }
 

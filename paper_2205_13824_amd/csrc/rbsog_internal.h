@@ -437,8 +437,7 @@ void launch_list_build(const EvalArgs &a, bool f64, const ListItem *items, int32
 void launch_near_cells(const EvalArgs &a, bool f64, const NearItem *items, int32_t nitems, int32_t slots,
                        hipStream_t s);
 // near forces and energies from the list; `reduce`: also the structure factor's
-// reduction (launch_rho_reduce where a.red_waves is 1 and no system has a
-// zero-frequency mode term)
+// reduction (as launch_rho_reduce where a.red_waves is 1, without the dipole)
 void launch_near(const EvalArgs &a, bool f64, const ListItem *items, int32_t nitems, hipStream_t s, bool reduce);
 // neighbour list of one system (debug export): counts per local id, then fill
 void launch_neighbor_count(const EvalArgs &a, int32_t sys, int64_t n, int64_t p0, const int32_t *id_cur,
@@ -452,6 +451,8 @@ void launch_rho(const EvalArgs &a, bool f64, const RhoItem *items, int32_t nitem
 // energies; then per system the far energy (with the zero-mode term) and
 // the sequence cursor moved on
 void launch_rho_reduce(const EvalArgs &a, hipStream_t s);
+// the dipole of batches with a zero-frequency mode term (part of the above)
+void launch_dipole(const EvalArgs &a, hipStream_t s);
 // far force; with a.kick the closing half kick v += dt/(2m) (F_N + F*) follows
 // (items of at most block_size particles, block_size in {64, 128, 256})
 void launch_far(const EvalArgs &a, bool f64, const FarItem *items, int32_t nitems, int32_t block_size,

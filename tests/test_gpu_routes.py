@@ -71,3 +71,31 @@ def test_room_is_checked():
     for args in ((None, 1), (R._ptr(out), 0), (R._ptr(out), len(R.ROUTES) + 1)):
         assert R.lib().rbsog_debug_routes(b.ctx, 1, *args) == -1
     b.close()
+
+
+# two streams from 0.3 of that with a zero-frequency mode term
+@pytest.mark.parametrize("prec,n,P,streams", [(F32C, 100000, 150, 1), (F32C, 100000, 151, 2), (F64, 60000, 110, 1),
+                                              (F64, 60000, 111, 2)])
+def test_streams_with_zero_modes(prec, n, P, streams):
+    r = _routes(_batch([n], P, prec, zero_mode=1))
+    assert (r["streams"], r["shared"]) == (streams, 2 - streams)
+
+
+@pytest.mark.parametrize("prec", [F64, F32C])
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("sizes,P", [([1000], 31), ([3070, 66, 9000], 40)])
+def test_zero_modes_share_launches_like_other_batches(prec, mode, sizes, P):
+    """With a zero-frequency mode term the launches are shared too; timed kernel by
+    kernel, each has its own: the same sums, so the same bits."""
+    out = []
+    for timed in (0, 1):
+        b = _batch(sizes, P, prec, zero_mode=mode, device_chains=8)
+        r = R.rbsog_debug_routes(b.ctx)
+        assert (r["streams"], r["shared"]) == (1, 1)
+        R.rbsog_profile(b.ctx, timed)
+        F, E = b.forces()
+        b.step(11, 1e-4)
+        out.append((F, E, *R.rbsog_get_state(b.ctx, b.n), R.rbsog_get_energy(b.ctx)))
+        b.close()
+    for x, y in zip(*out):
+        np.testing.assert_array_equal(x, y)
