@@ -429,7 +429,8 @@ enum {
     RBSOG_ROUTE_SHARED = 2,     /* 1: it and its reduction share the launches of the near part */
     RBSOG_ROUTE_ONE_BLOCK = 3,  /* 1: one block re-sorts the whole batch */
     RBSOG_ROUTE_FAR_WAVES = 4,  /* waves that share the records of a far group of 64 particles */
-    RBSOG_ROUTE_COUNT = 5
+    RBSOG_ROUTE_BUILD_WIDE = 5, /* 1: the list build's grids take the whole device */
+    RBSOG_ROUTE_COUNT = 6
 };
 rbsog_status rbsog_debug_routes(rbsog_ctx *ctx, int32_t stepping, int32_t *out, int32_t n);
 

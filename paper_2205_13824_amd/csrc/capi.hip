@@ -164,6 +164,14 @@ constexpr double side_min_work(int prec, bool zmode) {
     return (prec == RBSOG_FP64 ? 2.2e7 : 5e7) * (zmode ? 0.3 : 1.0);
 }
 
+// Particles from which the build kernels of a kept list take the whole device also
+// beside the structure factor: their blocks that return at once cost a step less
+// than a build gains.  Us a step with few blocks | the whole device, builds in a
+// thirtieth of the steps: 300,000 ions FP64 141.1 | 143.7, FP32C 85.3 | 85.7, 600,000
+// FP64 322.7 | 322.5, FP32C 169.2 | 167.7, 2,097,152 x 1000 FP32C 1,216 | 1,199, x 100
+// 362 | 354; with a build in most steps, 2,097,152 x 1000 1,798 | 1,653.
+constexpr int64_t kWideMin = 1 << 20;
+
 struct rbsog_ctx {
     int32_t nsys = 0;
     std::vector<SysHost> sys;
@@ -621,6 +629,7 @@ EvalArgs make_args(rbsog_ctx *c, bool stepping, double dt) {
     a.rebuild = c->rebuild;
     a.pairs = c->skin_cur > 0.0 ? c->pairs : nullptr;
     a.always_build = c->skin_cur > 0.0 ? 0 : 1;
+    a.due = a.wide = 1;  // (steps on a kept list: route_of)
     a.pcnt = c->pcnt;
     a.icap = c->icap;
     a.list_hm = c->list_hm ? 1 : 0;
@@ -687,6 +696,8 @@ struct Route {
     bool fork;   // the structure factor on the second stream, beside the near part
     bool carry;  // one stream: it shares a launch with the build's first kernel, its reduction one with the list pass
     bool one;    // the whole batch re-sorted by one block
+    bool due;    // the evaluation builds for certain (EvalArgs::due)
+    bool wide;   // the build's grids take the whole device (EvalArgs::wide)
 };
 Route route_of(const rbsog_ctx *c, const EvalArgs &a, bool stepping) {
     Route r;
@@ -700,6 +711,10 @@ Route route_of(const rbsog_ctx *c, const EvalArgs &a, bool stepping) {
     // build); an evaluation that the host has asked to build takes the kernels
     // that use the whole device
     r.one = stepping && !a.always_build && resort_in_one(a);
+    // steps on a kept list mostly build nothing; other evaluations follow new
+    // positions from the host
+    r.due = a.always_build || !stepping;
+    r.wide = r.due || !r.fork || a.N >= kWideMin;
     return r;
 }
 
@@ -735,6 +750,8 @@ rbsog_status enqueue_eval(rbsog_ctx *c, bool stepping, double dt, bool kinetic, 
     // side stream beside the re-sort and the near part, or share its launches
     const Route rt = route_of(c, a, stepping);
     const bool fork = rt.fork, carry = rt.carry, one = rt.one;
+    a.due = rt.due ? 1 : 0;
+    a.wide = rt.wide ? 1 : 0;
     // building at every step, the far force joins them there (the near part
     // is long enough to hide it); it is then read back in the new order
     const bool far_side = a.always_build != 0;
@@ -2748,6 +2765,7 @@ rbsog_status rbsog_debug_routes(rbsog_ctx *c, int32_t stepping, int32_t *out, in
     all[RBSOG_ROUTE_SHARED] = r.carry ? 1 : 0;
     all[RBSOG_ROUTE_ONE_BLOCK] = r.one ? 1 : 0;
     all[RBSOG_ROUTE_FAR_WAVES] = far_waves(a, c->prec == RBSOG_FP64);
+    all[RBSOG_ROUTE_BUILD_WIDE] = r.wide ? 1 : 0;
     std::copy(all, all + n, out);
     return RBSOG_OK;
 }

@@ -9,6 +9,8 @@
 // list build, so these passes stream it coalesced and a re-sort moves
 // particles only as far as they drifted.  The list-build kernels read the
 // rebuild flag first and return at once when it is clear.
+#include <type_traits>
+
 #include "rbsog_internal.h"
 #include "rbsog_math.h"
 #include "rho_block.h"
@@ -156,13 +158,16 @@ __device__ int32_t block_exclusive_scan(int32_t v, int32_t *total) {
 }
 
 // The kernels of a list build run at every evaluation with a kept list and
-// return at once unless a build is due, so their blocks are large and few:
-// kBuildThreads threads, at most kBuildGrid blocks that stride, so that they pass
-// the few wave slots that the structure factor leaves free (512 blocks: 300,000
-// ions 84.8 us a step against 83.7; 64: 84.0; a build's own time is the same
-// within 2 %).
+// return at once unless a build is due.  Beside the structure factor (EvalArgs::wide
+// 0) their blocks are large and few: kBuildThreads threads, at most kBuildGrid
+// blocks that stride, so that they pass the few wave slots that it leaves free (512
+// blocks: 300,000 ions 84.8 us a step against 83.7; 64: 84.0).  A build itself takes
+// longer in them, so that evaluations which build for certain, and those with
+// nothing beside the build, take blocks of kWideThreads, at most kWideGrid.
 constexpr int kBuildThreads = 1024;
 constexpr int64_t kBuildGrid = 128;
+constexpr int kWideThreads = 256;
+constexpr int64_t kWideGrid = 2048;
 
 // Exclusive scan of the counts of n cells by one block, tile after tile of four
 // counts per thread: the cells' starts, the scatter's fill counters, and
@@ -215,7 +220,7 @@ __device__ __forceinline__ void bin_particles(const EvalArgs &a, int64_t block, 
     __builtin_amdgcn_s_setprio(2);
     if (!*a.rebuild) return;
     const int64_t N = a.N;
-    for (int64_t base = block * kBuildThreads; base < N; base += blocks * kBuildThreads) {
+    for (int64_t base = block * blockDim.x; base < N; base += blocks * blockDim.x) {
         const int64_t t0 = base + threadIdx.x;
         const bool valid = t0 < N;
         const int64_t t = valid ? t0 : N - 1;
@@ -337,8 +342,8 @@ __global__ __launch_bounds__(kBuildThreads) void k_cell_scatter(EvalArgs a) {
 // its keys in registers.  More (water-shaped sites at r_c = 10: about 150 a
 // cell): one wave per cell, a slot per lane, every key broadcast; an insertion
 // sort by one thread took 2 ms a build there.
-// CELLS: cells per block, 256 (one thread each, larger ones left to the
-// waves) or 16 (one wave each).
+// CELLS: cells per block of THREADS, a quarter of the threads (one thread each,
+// larger ones left to the waves) or one per wave.
 constexpr int kRankMax = 16;
 
 // Slots [lo, hi) of one cell ordered by a wave.
@@ -375,15 +380,16 @@ __device__ __forceinline__ void sort_cell_thread(const int32_t *__restrict__ src
     }
 }
 
-// Slots [k0, k1) of the new order gathered from the state by a block: two
-// slots per thread and pass, all loads issued before the stores.
+// Slots [k0, k1) of the new order gathered from the state by a block of THREADS:
+// two slots per thread and pass, all loads issued before the stores.
+template <int THREADS>
 __device__ __forceinline__ void gather_slots(const EvalArgs &a, const int32_t *out, int64_t k0, int64_t k1) {
     const int64_t N = a.N;
     constexpr int U = 2;
-    for (int64_t kb = k0 + threadIdx.x; kb < k1; kb += U * kBuildThreads) {
+    for (int64_t kb = k0 + threadIdx.x; kb < k1; kb += U * THREADS) {
         int64_t tt[U];
 #pragma unroll
-        for (int j = 0; j < U; ++j) tt[j] = kb + j * kBuildThreads < k1 ? out[kb + j * kBuildThreads] : -1;
+        for (int j = 0; j < U; ++j) tt[j] = kb + j * THREADS < k1 ? out[kb + j * THREADS] : -1;
         double xv[U][3], vv[U][3], qv[U];
         uint32_t uv[U][3];
         float qfv[U];
@@ -403,7 +409,7 @@ __device__ __forceinline__ void gather_slots(const EvalArgs &a, const int32_t *o
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            const int64_t k = kb + j * kBuildThreads;
+            const int64_t k = kb + j * THREADS;
             if (tt[j] < 0) continue;
             for (int d = 0; d < 3; ++d) {
                 a.nxt.x[d * N + k] = xv[j][d];
@@ -419,14 +425,14 @@ __device__ __forceinline__ void gather_slots(const EvalArgs &a, const int32_t *o
 #pragma unroll
             for (int j = 0; j < U; ++j) {
                 if (tt[j] < 0) continue;
-                for (int d = 0; d < 3; ++d) a.nxt.dsp[d * N + kb + j * kBuildThreads] = a.cur.dsp[d * N + tt[j]];
+                for (int d = 0; d < 3; ++d) a.nxt.dsp[d * N + kb + j * THREADS] = a.cur.dsp[d * N + tt[j]];
             }
         }
     }
 }
 
-template <int CELLS>
-__global__ __launch_bounds__(kBuildThreads) void k_sort_gather(EvalArgs a) {
+template <int CELLS, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_sort_gather(EvalArgs a) {
     // the critical path's waves ahead of the structure factor's beside them
     __builtin_amdgcn_s_setprio(2);
     if (!*a.rebuild) return;
@@ -434,7 +440,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_sort_gather(EvalArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     int32_t *out = a.sorted;
     for (int64_t c0 = (int64_t)blockIdx.x * CELLS; c0 < a.C; c0 += (int64_t)gridDim.x * CELLS) {
-        if constexpr (CELLS == kBuildThreads / 64) {
+        if constexpr (CELLS == THREADS / 64) {
             const int64_t c = c0 + wave;
             if (c < a.C) {
                 sort_cell_wave(a.src, a.skey, out, a.cell_start[c], a.cell_start[c + 1], lane);
@@ -454,7 +460,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_sort_gather(EvalArgs a) {
                 a.cell_count[c] = a.cell_fill[c] = 0;
             }
             __syncthreads();
-            for (int k = wave; k < nbig; k += kBuildThreads / 64) {
+            for (int k = wave; k < nbig; k += THREADS / 64) {
                 const int64_t cb = c0 + big[k];
                 sort_cell_wave(a.src, a.skey, out, a.cell_start[cb], a.cell_start[cb + 1], lane);
             }
@@ -462,7 +468,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_sort_gather(EvalArgs a) {
         // the block's permutation entries are visible to the whole block here
         __syncthreads();
         const int64_t c1 = c0 + CELLS < a.C ? c0 + CELLS : a.C;
-        gather_slots(a, out, a.cell_start[c0], a.cell_start[c1]);
+        gather_slots<THREADS>(a, out, a.cell_start[c0], a.cell_start[c1]);
         // the next group's permutation entries are written after every
         // thread has read this group's
         __syncthreads();
@@ -661,22 +667,26 @@ void launch_kdq(const EvalArgs &a, hipStream_t s) {
 
 int64_t scan_blocksums_size(int64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
 
-inline unsigned build_grid(int64_t blocks) {
-    return (unsigned)(blocks < kBuildGrid ? (blocks < 1 ? 1 : blocks) : kBuildGrid);
+inline unsigned capped(int64_t blocks, int64_t cap) { return (unsigned)(blocks < cap ? (blocks < 1 ? 1 : blocks) : cap); }
+// Threads of a build block, and the grid for n items at `per` a block.
+inline int build_threads(const EvalArgs &a) { return a.wide ? kWideThreads : kBuildThreads; }
+inline unsigned build_grid(const EvalArgs &a, int64_t n, int per) {
+    return capped(grid_for(n, per), a.wide ? kWideGrid : kBuildGrid);
 }
 
 // More cells than the scatter scans for itself: scanned by one block up to this
-// many (its 17 tiles at 68,921 cells take about 20 us of the one evaluation in
-// some thirty that builds, and one launch instead of two on all others), by two
-// kernels above and where every evaluation builds.
+// many (its 17 tiles at 68,921 cells take about 60 us of the one step in some
+// thirty that builds, and one launch of some 4 us instead of two on all others), by
+// two kernels (about 10 us there) above and where the evaluation builds for certain.
 constexpr int64_t kScanOne = 131072;
 
 void launch_bin(const EvalArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(k_bin, dim3(build_grid(grid_for(a.N, kBuildThreads))), dim3(kBuildThreads), 0, s, a);
+    const int threads = build_threads(a);
+    hipLaunchKernelGGL(k_bin, dim3(build_grid(a, a.N, threads)), dim3((unsigned)threads), 0, s, a);
 }
 
 void launch_rho_build(const EvalArgs &a, bool f64, const RhoItem *items, int32_t nitems, bool one, hipStream_t s) {
-    const dim3 grid((unsigned)nitems + (one ? 1u : build_grid(grid_for(a.N, kBuildThreads)))), block(kBuildThreads);
+    const dim3 grid((unsigned)nitems + (one ? 1u : build_grid(a, a.N, kBuildThreads))), block(kBuildThreads);
     if (f64 && one) hipLaunchKernelGGL((k_rho_build<true, true>), grid, block, 0, s, a, items, nitems);
     else if (f64) hipLaunchKernelGGL((k_rho_build<true, false>), grid, block, 0, s, a, items, nitems);
     else if (one) hipLaunchKernelGGL((k_rho_build<false, true>), grid, block, 0, s, a, items, nitems);
@@ -687,7 +697,7 @@ bool scan_apart(const EvalArgs &a) { return a.C > kScanLds; }
 
 void launch_scan(const EvalArgs &a, hipStream_t s) {
     const int64_t n = a.C;
-    if (n <= kScanOne && !a.always_build) {
+    if (n <= kScanOne && !a.due) {
         hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kBuildThreads), 0, s, a.cell_count, n, a.cell_start, a.cell_fill,
                            (const int32_t *)a.rebuild);
         return;
@@ -700,7 +710,8 @@ void launch_scan(const EvalArgs &a, hipStream_t s) {
 }
 
 void launch_cell_scatter(const EvalArgs &a, hipStream_t s) {
-    const dim3 grid(build_grid(grid_for(a.N, kBuildThreads))), block(kBuildThreads);
+    const int threads = scan_apart(a) ? build_threads(a) : kBuildThreads;
+    const dim3 grid(build_grid(a, a.N, threads)), block((unsigned)threads);
     if (scan_apart(a)) hipLaunchKernelGGL(k_cell_scatter<false>, grid, block, 0, s, a);
     else hipLaunchKernelGGL(k_cell_scatter<true>, grid, block, 0, s, a);
 }
@@ -713,11 +724,19 @@ void launch_resort_one(const EvalArgs &a, hipStream_t s) {
 }
 
 void launch_sort_gather(const EvalArgs &a, hipStream_t s) {
+    auto go = [&](auto cells, auto threads) {
+        constexpr int CELLS = decltype(cells)::value, THREADS = decltype(threads)::value;
+        hipLaunchKernelGGL((k_sort_gather<CELLS, THREADS>), dim3(build_grid(a, a.C, CELLS)), dim3(THREADS), 0, s, a);
+    };
+    using std::integral_constant;
+    constexpr integral_constant<int, kBuildThreads> large{};
+    constexpr integral_constant<int, kWideThreads> small{};
     // one wave per cell where cells hold more than a thread ranks
-    if (a.N > kRankMax * a.C)
-        hipLaunchKernelGGL(k_sort_gather<16>, dim3(build_grid(grid_for(a.C, 16))), dim3(kBuildThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_sort_gather<256>, dim3(build_grid(grid_for(a.C, 256))), dim3(kBuildThreads), 0, s, a);
+    const bool waves = a.N > kRankMax * a.C;
+    if (a.wide && waves) go(integral_constant<int, kWideThreads / 64>{}, small);
+    else if (a.wide) go(integral_constant<int, kWideThreads / 4>{}, small);
+    else if (waves) go(integral_constant<int, kBuildThreads / 64>{}, large);
+    else go(integral_constant<int, kBuildThreads / 4>{}, large);
 }
 
 }  // namespace rbsog

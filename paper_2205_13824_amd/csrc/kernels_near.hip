@@ -1790,14 +1790,16 @@ void near_cells_launch(const EvalArgs &a, bool f64, int32_t slots, dim3 grid, di
 void launch_list_build(const EvalArgs &a, bool f64, const ListItem *items, int32_t nitems, int32_t slots,
                        hipStream_t s, bool copy_back) {
     // one item per virtual block (a wave per quarter); a multiple of 8 so
-    // that the XCD mapping is a permutation of the blocks; at most kBuildBlocks
-    // launched (grid-stride: seven per CU, as many as their LDS lets run), then
-    // the blocks of the copy back
-    constexpr int32_t kBuildBlocks = 1792;
+    // that the XCD mapping is a permutation of the blocks; a limited number
+    // launched (grid-stride), then the blocks of the copy back.  Beside the
+    // structure factor at most seven per CU, as many as their LDS lets run, and
+    // one of the copy; else (a.wide) more of both, which start as others end.
+    const int32_t build_max = a.wide ? 4096 : 1792;
+    const int64_t copy_max = a.wide ? 1024 : 256;
     int32_t nblk = (nitems + 7) / 8 * 8;
     if (nblk < 8) nblk = 8;
-    const int32_t gblk = std::min(nblk, kBuildBlocks);
-    const int64_t ncopy = copy_back ? std::min<int64_t>(256, std::max<int64_t>(1, grid_for(a.N, 64 * kNW))) : 0;
+    const int32_t gblk = std::min(nblk, build_max);
+    const int64_t ncopy = copy_back ? std::min<int64_t>(copy_max, std::max<int64_t>(1, grid_for(a.N, 64 * kNW))) : 0;
     const dim3 grid((unsigned)(gblk + ncopy)), block(64 * kNW);
     (void)f64;  // the build's test is the same in both precisions
     list_build_launch(a, slots, grid, block, items, nitems, nblk, gblk, s);

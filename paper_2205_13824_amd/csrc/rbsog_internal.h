@@ -244,6 +244,8 @@ struct EvalArgs {
     int32_t near_form;     // how the list pass evaluates the Gaussians (kForm...)
     int32_t list_hm;       // nonzero: home-major blocks of the near list (long lists)
     int32_t always_build;  // nonzero: every evaluation builds (no displacement check, no list kept)
+    int32_t due;           // 1: this evaluation builds for certain (every one does, or the host moved the particles)
+    int32_t wide;          // 1: grids of the build kernels for the whole device (0: the structure factor runs beside them)
     uint32_t *pairs;
     int32_t *pcnt;
     int64_t icap;

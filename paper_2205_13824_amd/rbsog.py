@@ -390,7 +390,7 @@ def rbsog_debug_list(ctx, sys: int = 0):
     return _csr_call(ctx, sys, lib().rbsog_debug_list)
 
 
-ROUTES = ("near_form", "streams", "shared", "one_block", "far_waves")
+ROUTES = ("near_form", "streams", "shared", "one_block", "far_waves", "build_wide")
 
 
 def rbsog_debug_routes(ctx, stepping: bool = True) -> dict:

@@ -73,6 +73,18 @@ def test_room_is_checked():
     b.close()
 
 
+# the list build has the whole device where nothing runs beside it, where the
+# evaluation builds for certain, and from 2^20 particles on
+@pytest.mark.parametrize("prec,sizes,P,skin,wide", [
+    (F32C, [100000], 500, None, 1), (F32C, [100000], 502, None, 0), (F64, [100000], 222, None, 0),
+    (F32C, [100000], 502, 0.0, 1), (F32C, [2 ** 20 - 2], 60, None, 0), (F32C, [2 ** 20], 60, None, 1),
+    (F32C, [2000] * 30, 10, None, 1)])
+def test_grids_of_the_list_build(prec, sizes, P, skin, wide):
+    b = _batch(sizes, P, prec, skin=skin)
+    assert R.rbsog_debug_routes(b.ctx, False)["build_wide"] == 1
+    assert _routes(b)["build_wide"] == wide
+
+
 # two streams from 0.3 of that with a zero-frequency mode term
 @pytest.mark.parametrize("prec,n,P,streams", [(F32C, 100000, 150, 1), (F32C, 100000, 151, 2), (F64, 60000, 110, 1),
                                               (F64, 60000, 111, 2)])
