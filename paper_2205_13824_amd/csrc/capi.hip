@@ -1507,17 +1507,20 @@ void build_work(rbsog_ctx *c, const Tune &t, std::vector<ListItem> &near, std::v
     }
 }
 
-// Default shapes: kRhoChunks structure-factor chunks and 256-particle far blocks
-// over the batch.  512 chunks of 16 waves hold every wave slot of the device (two
-// blocks per CU), and the build kernels and the near pass beside them wait for
-// the first of them to end; with 480, 32 CUs keep half their slots for those.
-// Steps at 512 | 480 chunks: 300,000 ions 89.5 | 83.7 us, 2,097,152 ions 1,246 |
-// 1,212, 48 systems 119 | 115, water-shaped 331,776 sites 459 | 447 (384 chunks:
-// 85, 1,306, 114, 450; 496: 89, 1,266, 118, 460).
-constexpr int64_t kRhoChunks = 480;
+// Default shapes: structure-factor chunks and 256-particle far blocks over the
+// batch.  512 chunks of 16 waves hold every wave slot of the device (two blocks per
+// CU), and the build kernels and the near pass beside them wait for the first of
+// them to end; with 480, 32 CUs keep half their slots for those.  Steps at 512 | 480
+// chunks: 300,000 ions 89.5 | 83.7 us, 2,097,152 ions 1,246 | 1,212, 48 systems 119 |
+// 115, water-shaped 331,776 sites 459 | 447 (384 chunks: 85, 1,306, 114, 450; 496: 89,
+// 1,266, 118, 460).  On one stream nothing is beside them: 8,000,000 ions x 1000 4,545
+// | 4,660, 5,000,000 x 900 FP64 6,980 | 7,180, 150,000 x 200 63.5 | 65.8.
+constexpr int64_t kRhoChunksBeside = 480, kRhoChunksAlone = 512;
 Tune default_tune(const rbsog_ctx *c) {
     Tune t;
-    t.rho_chunk = (int32_t)std::max<int64_t>(256, (c->N + kRhoChunks - 1) / kRhoChunks);
+    const int64_t chunks =
+        c->use_side(c->skin > 0.0, c->sys[0].zmode != 0) ? kRhoChunksBeside : kRhoChunksAlone;
+    t.rho_chunk = (int32_t)std::max<int64_t>(256, (c->N + chunks - 1) / chunks);
     t.far_block = 256;
     return t;
 }

@@ -73,6 +73,17 @@ def test_room_is_checked():
     b.close()
 
 
+# 480 chunks of particles beside the near part, 512 where the structure factor is alone
+# (one stream, above 4e9 pairs too)
+@pytest.mark.parametrize("prec,n,P,skin,chunks", [(F32C, 400000, 100, None, 512), (F32C, 400000, 200, None, 480),
+                                                  (F64, 200000, 100, None, 512), (F64, 200000, 200, None, 480),
+                                                  (F32C, 400000, 100, 0.0, 480), (F32C, 400000, 10100, None, 512)])
+def test_chunks_of_the_structure_factor(prec, n, P, skin, chunks):
+    b = _batch([n], P, prec, skin=skin)
+    assert R.rbsog_info(b.ctx)["rho_chunk"] == -(-n // chunks)
+    b.close()
+
+
 # the list build has the whole device where nothing runs beside it, where the
 # evaluation builds for certain, and from 2^20 particles on
 @pytest.mark.parametrize("prec,sizes,P,skin,wide", [
