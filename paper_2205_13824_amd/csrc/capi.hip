@@ -1437,8 +1437,9 @@ void tune_cache_store(const std::string &key, const Tune &t) {
     }
 }
 
-// Blocks that the FP32C structure factor's k tiles are split for by default.
-constexpr int64_t kRhoBlocks32 = 64;
+// Blocks that the structure factor's k tiles are split for by default (FP32C, and
+// where every step builds).
+constexpr int64_t kRhoBlocks = 64;
 constexpr int64_t kCus = 256;
 
 // Work lists of the batch.  Near: runs of kListHomes slots of one system;
@@ -1448,7 +1449,7 @@ void build_work(rbsog_ctx *c, const Tune &t, std::vector<ListItem> &near, std::v
                 std::vector<FarItem> &far) {
     const int64_t chunk = t.rho_chunk, fb = t.far_block;
     auto chunks_of = [&](const SysHost &h) { return (int32_t)std::max<int64_t>(1, (h.n + chunk - 1) / chunk); };
-    // k tiles per structure-factor block: as the shapes say, or, FP32C, as many as
+    // k tiles per structure-factor block: as the shapes say, or (FP32C) as many as
     // leave the batch enough blocks (the waves that a smaller group leaves free
     // split the chunk further, but each block stages its particles anew: 1,000 ions
     // x 100 6.8 us against 7.6, but 26,998 ions x 130 10.0 against 9.4 and 77,781 x
@@ -1456,8 +1457,11 @@ void build_work(rbsog_ctx *c, const Tune &t, std::vector<ListItem> &near, std::v
     // the most blocks the fewest tiles (480 | 960 blocks: 300,000 ions x 200 x 40 steps
     // 7.58 | 7.76 ms; 430 | 860: 110,000 x 150 x 60 4.84 | 5.25; but 384 | 768: 98,304
     // sites x 211 x 30 7.91 | 7.78; a tenth fewer at least: 192,000 sites x 500 x 20 in 480
-    // | 3,840 12.6 | 13.1)
+    // | 3,840 12.6 | 13.1).  Where every step builds, the near part is the longer and
+    // shares the device with them: as in FP32C (100,000 ions x 200, us a step in 391 |
+    // 1,563 blocks 110.7 | 116.7)
     int32_t kt_max = t.rho_kt > 0 ? std::min(t.rho_kt, 16) : 16;
+    const bool by_load = c->prec == RBSOG_FP64 && c->skin > 0.0;
     if (t.rho_kt <= 0) {
         double least = 1e300;
         for (int32_t kt_try = 16;; kt_try = (kt_try + 1) / 2) {
@@ -1468,9 +1472,9 @@ void build_work(rbsog_ctx *c, const Tune &t, std::vector<ListItem> &near, std::v
                 blocks += (int64_t)chunks_of(h) * ((ktiles + kt - 1) / kt);
                 tiles = std::max(tiles, kt);
             }
-            if (c->prec != RBSOG_FP64) {
+            if (!by_load) {
                 kt_max = kt_try;
-                if (blocks >= kRhoBlocks32) break;
+                if (blocks >= kRhoBlocks) break;
             } else if (const double load = (double)((blocks + kCus - 1) / kCus * tiles); load < 0.9 * least) {
                 least = load;
                 kt_max = kt_try;

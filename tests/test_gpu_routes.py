@@ -84,6 +84,17 @@ def test_chunks_of_the_structure_factor(prec, n, P, skin, chunks):
     b.close()
 
 
+# FP64 blocks of fewer k tiles where that lightens the fullest CU, not where every step
+# builds: 391 chunks of 4 tiles make 782 blocks of 2 or 1,564 of 1
+@pytest.mark.parametrize("prec,n,P,skin,ktile", [(F64, 100000, 200, None, 1), (F64, 100000, 200, 0.0, 4),
+                                                 (F64, 1000, 100, None, 1), (F64, 1000, 100, 0.0, 1),
+                                                 (F32C, 100000, 200, None, 4), (F32C, 100000, 200, 0.0, 4)])
+def test_k_tiles_of_a_structure_factor_block(prec, n, P, skin, ktile):
+    b = _batch([n], P, prec, skin=skin)
+    assert R.rbsog_info(b.ctx)["rho_ktile"] == ktile
+    b.close()
+
+
 # the list build has the whole device where nothing runs beside it, where the
 # evaluation builds for certain, and from 2^20 particles on
 @pytest.mark.parametrize("prec,sizes,P,skin,wide", [
