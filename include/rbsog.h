@@ -399,6 +399,11 @@ rbsog_status rbsog_structure_factor_noalloc(int64_t n, const double *x, const do
                                             int64_t n_k, const int32_t *m, int32_t precision, double *rho_re,
                                             double *rho_im, void *stream);
 
+/* Debug report of the launch shape of either call (needs no device).
+ *   out  host, 4 int64: k tiles of 64 wave vectors and particle streams of a block
+ *        of 16 waves, groups of k tiles, particle chunks */
+rbsog_status rbsog_debug_structure_factor_plan(int64_t n, int64_t n_k, int32_t precision, int64_t *out);
+
 /* Debug record of the pairs the near kernels accept: with cap > 0 (at most
  * 2^31-1) every later evaluation records, from the near kernel that evaluates
  * it (the list pass, which evaluates every evaluation with the near list, the

@@ -68,6 +68,23 @@ SfPlan sf_plan(int64_t n, int64_t nk, bool f64) {
     SfPlan p;
     const int64_t tiles = (nk + 63) / 64;
     p.kt = (int32_t)(tiles < kSfWaves ? tiles : kSfWaves);
+    if (tiles > kSfWaves) {
+        // several groups: the k tiles of a block that take the least time over all of
+        // them.  A group's time goes with the waves that a SIMD runs of it, over its
+        // particle streams, and one tile's for the staging of every particle: 17
+        // tiles in groups of 16 and 1 take twice the time of 16, in three groups of 6
+        // (12 waves in two streams) 1.2 times (1,999,998 particles x 1025 FP32C, us:
+        // 1,020 -> 700)
+        int64_t best = INT64_MAX;
+        for (int32_t kt = kSfWaves; kt >= 4; --kt) {
+            const int64_t groups = (tiles + kt - 1) / kt, streams = kSfWaves / kt, waves = kt * streams;
+            const int64_t cost = groups * ((waves + 3) / 4 * 4 * kSfWaves / streams + kSfWaves);
+            if (cost < best) {
+                best = cost;
+                p.kt = kt;
+            }
+        }
+    }
     p.streams = kSfWaves / p.kt;
     p.groups = (tiles + p.kt - 1) / p.kt;
     // chunks of at least kSfMinChunk particles that give two blocks per CU
@@ -260,6 +277,21 @@ rbsog_status scratch_of_current_device(double2 **out) {
 using namespace rbsog;
 
 extern "C" {
+
+rbsog_status rbsog_debug_structure_factor_plan(int64_t n, int64_t n_k, int32_t precision, int64_t *out) {
+    const char *who = "rbsog_debug_structure_factor_plan";
+    const double box[3] = {1.0, 1.0, 1.0};
+    const int32_t m = 1;
+    const rbsog_status st = sf_check(n, box, box, box, n_k, &m, precision, box, box, who);
+    if (st != RBSOG_OK) return st;
+    if (!out) return fail_noctx(RBSOG_E_ARG, "%s: out is null", who);
+    const SfPlan p = sf_plan(n, n_k, precision == RBSOG_FP64);
+    out[0] = p.kt;
+    out[1] = p.streams;
+    out[2] = p.groups;
+    out[3] = p.nchunk;
+    return RBSOG_OK;
+}
 
 rbsog_status rbsog_structure_factor(int64_t n, const double *x, const double *q, const double *box, int64_t n_k,
                                     const int32_t *m, int32_t precision, double *rho_re, double *rho_im,

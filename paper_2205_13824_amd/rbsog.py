@@ -35,7 +35,8 @@ EXPORTS = ("rbsog_default_opts", "rbsog_sog_table1", "rbsog_init", "rbsog_init_b
            "rbsog_set_nose_hoover", "rbsog_get_kinetic", "rbsog_set_msd_origin", "rbsog_get_msd",
            "rbsog_structure_factor", "rbsog_structure_factor_noalloc", "rbsog_get_forces_subset",
            "rbsog_debug_record_pairs", "rbsog_debug_pairs", "rbsog_debug_list", "rbsog_save_state",
-           "rbsog_load_state", "rbsog_debug_routes", "rbsog_probe_count", "rbsog_probe_name", "rbsog_probe_rates")
+           "rbsog_load_state", "rbsog_debug_routes", "rbsog_debug_structure_factor_plan", "rbsog_probe_count",
+           "rbsog_probe_name", "rbsog_probe_rates")
 
 
 class RbsogError(RuntimeError):
@@ -116,6 +117,7 @@ def lib():
             "rbsog_set_thermostat": (i32, [vp, dbl, dbl, u64]),
             "rbsog_structure_factor": (i32, [i64, vp, vp, vp, i64, vp, i32, vp, vp, vp]),
             "rbsog_structure_factor_noalloc": (i32, [i64, vp, vp, vp, i64, vp, i32, vp, vp, vp]),
+            "rbsog_debug_structure_factor_plan": (i32, [i64, i64, i32, vp]),
             "rbsog_probe_count": (i32, []),
             "rbsog_probe_name": (ctypes.c_char_p, [i32]),
             "rbsog_probe_rates": (i32, [i32, i32, vp, i32]),
@@ -360,6 +362,13 @@ def rbsog_structure_factor(n: int, x_dev: int, q_dev: int, box, n_k: int, m_dev:
     b = _f64(box, (3,))
     f = lib().rbsog_structure_factor_noalloc if noalloc else lib().rbsog_structure_factor
     _check(f(int(n), x_dev, q_dev, _ptr(b), int(n_k), m_dev, int(precision), rho_re_dev, rho_im_dev, stream))
+
+
+def rbsog_debug_structure_factor_plan(n: int, n_k: int, precision: int) -> dict:
+    """Launch shape of rbsog_structure_factor: tiles and streams of a block, groups, chunks."""
+    out = np.zeros(4, dtype=np.int64)
+    _check(lib().rbsog_debug_structure_factor_plan(int(n), int(n_k), int(precision), _ptr(out)))
+    return dict(zip(("tiles", "streams", "groups", "chunks"), out.tolist()))
 
 
 def rbsog_debug_record_pairs(ctx, cap: int):
