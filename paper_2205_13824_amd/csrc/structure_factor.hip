@@ -118,6 +118,7 @@ __global__ __launch_bounds__(1024, F64 ? 1 : 8) void k_sf_partial(int64_t n, con
     __shared__ double2 red[1024];
     __shared__ uint4 st32[F64 ? 1 : kStage];
     __shared__ int2 wcnt[F64 ? 1 : 16];
+    __shared__ int32_t large[F64 ? 1 : kSfWaves];  // FP32C: a wave holds a vector above kPairAnyMax
     __shared__ Stage64 st64[F64 ? kStage : 1];
     __shared__ double2 turn[F64 ? rmath::kTurnTab : 1];
     if constexpr (F64) fill_turns(turn);
@@ -134,7 +135,10 @@ __global__ __launch_bounds__(1024, F64 ? 1 : 8) void k_sf_partial(int64_t n, con
     bool even = false;
     if constexpr (!F64) {
         const uint64_t l1 = (uint64_t)llabs((long long)mx) + llabs((long long)my) + llabs((long long)mz);
-        even = __syncthreads_or(l1 > kPairAnyMax) != 0;
+        const uint64_t over = __builtin_amdgcn_ballot_w64(l1 > kPairAnyMax);
+        if (lane == 0) large[wave] = over != 0 ? 1 : 0;
+        __syncthreads();
+        even = __builtin_amdgcn_ballot_w64(large[lane & 15] != 0) != 0;
     }
     double re = 0.0, im = 0.0;
     for (int64_t jb = j0; jb < j1; jb += kStage) {
