@@ -674,7 +674,12 @@ EvalArgs make_args(rbsog_ctx *c, bool stepping, double dt) {
     a.fuse = 0;
     a.advance = 0;
     a.zmode = 0;
-    for (const SysHost &h : c->sys) a.zmode |= h.zmode != 0 ? 1 : 0;
+    for (const SysHost &h : c->sys) {
+        a.zmode |= h.zmode != 0 ? 1 : 0;
+        const int64_t groups = (h.n + 63) / 64;
+        a.far_groups += groups;
+        a.far_span = (int32_t)std::max<int64_t>(a.far_span, std::min<int64_t>(groups, c->tune.far_block / 64));
+    }
     // four waves per record once a system has more chunks than one wave
     // takes in a round of eight loads per lane
     int32_t nch = 0;
@@ -1566,7 +1571,8 @@ rbsog_status apply_tune(rbsog_ctx *c, const Tune &t) {
     c->n_list = (int32_t)near.size();
     c->n_rho = (int32_t)rho.size();
     c->n_far = (int32_t)far.size();
-    // wave slots of the kinetic-energy partials that a smaller far block leaves unused stay 0
+    // wave slots of the kinetic-energy partials that a smaller far block, or smaller
+    // systems than a block, leave unused stay 0
     HIPCHK(c, hipMemset(c->kpart, 0, (size_t)4 * c->n_far * sizeof(double)));
     for (int32_t s = 0; s < c->nsys; ++s) TRY(upload_sysdev(c, s));
     c->tune = t;

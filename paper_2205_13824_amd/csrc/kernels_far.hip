@@ -666,16 +666,19 @@ void launch_dipole(const EvalArgs &a, hipStream_t s) {
 // W = 1 and at the W taken: 1,000 ions x 100 FP32C 10.1 -> 5.8 us (16), FP64 21 ->
 // 5.8; 26,998 ions x 130 11.3 -> 7.2 (8; 16: 9.4); 77,781 x 150 13.2 -> 10.5 (2);
 // 98,304 x 211 FP64 40.7 -> 21.2 (4; 2: 25.8); 300,000 x 200 FP64 54 (2: 62).
+// (Counted are the groups that hold particles, two for a system of 66, and no more
+// are launched for an item than the fullest one has: 240 systems of 66, 264 groups
+// counted and 960 launched | 480 and 480: 56.3 | 48.6 us a step.)
 int32_t far_waves(const EvalArgs &a, bool f64) {
-    const int64_t all = (a.N + 63) / 64, per = a.nsys ? a.K / a.nsys : 0;
+    const int64_t per = a.nsys ? a.K / a.nsys : 0;
     int32_t w = 16;
-    while (w > 1 && (all * w > (f64 ? 8192 : 4096) || per < 4 * w)) w >>= 1;
+    while (w > 1 && (a.far_groups * w > (f64 ? 8192 : 4096) || per < 4 * w)) w >>= 1;
     return w;
 }
 
 template <bool F64, int FUSE>
 static void far_split(const EvalArgs &a, const FarItem *items, int32_t nitems, int32_t block_size, hipStream_t s) {
-    const int32_t groups = block_size / 64, w = far_waves(a, F64);
+    const int32_t w = far_waves(a, F64), groups = w > 1 ? a.far_span : block_size / 64;
     const dim3 grid((unsigned)(nitems * groups)), block((unsigned)(64 * w));
     switch (w) {
         case 16: hipLaunchKernelGGL((k_far<F64, FUSE, 16>), grid, block, 0, s, a, items, nitems, groups); break;

@@ -289,6 +289,8 @@ struct EvalArgs {
     double c1, c2;
     uint64_t tseed;
     int64_t *tstep;        // thermostatted steps taken (noise counter)
+    int64_t far_groups;    // groups of 64 particles of one system that hold any
+    int32_t far_span;      // most such groups of a far item
     int32_t advance;       // 1: the evaluation's last far kernel moves the sequence cursors on
     int32_t zmode;         // 1: some system has a zero-frequency mode term
     // nonzero (plain velocity Verlet on a kept near list): the far kernel

@@ -45,7 +45,9 @@ def test_pair_kernel_of_the_core_shell_table():
 @pytest.mark.parametrize("sizes,P,f64,f32", [([64], 2, 1, 1), ([1000], 31, 4, 4), ([1002], 65, 16, 16),
                                              ([1000], 4357, 16, 16), ([20002], 129, 16, 8), ([40000], 97, 8, 4),
                                              ([66000], 33, 4, 2), ([132000], 21, 2, 1), ([264000], 9, 1, 1),
-                                             ([500, 64, 3070], 40, 8, 8)])
+                                             ([500, 64, 3070], 40, 8, 8),
+                                             # systems of two groups each: 480, 512 and 1,026 of them
+                                             ([66] * 240, 100, 16, 8), ([66] * 256, 100, 16, 8), ([66] * 513, 100, 4, 2)])
 def test_waves_of_a_far_group(sizes, P, f64, f32):
     assert _routes(_batch(sizes, P, F64))["far_waves"] == f64
     assert _routes(_batch(sizes, P, F32C))["far_waves"] == f32
