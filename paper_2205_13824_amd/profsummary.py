@@ -43,13 +43,18 @@ def sources_sha256() -> str:
 
 # the source file that defines each kernel of the library
 KERNEL_FILES = {
-    "k_rho": "kernels_far.hip", "k_rho_reduce": "kernels_far.hip", "k_far": "kernels_far.hip",
-    "k_far_side": "kernels_far.hip", "k_far_finish": "kernels_far.hip",
+    "k_rho": "kernels_far.hip", "k_rho_reduce": "kernels_far.hip", "k_rho_reduce_block": "kernels_far.hip",
+    "k_dipole": "kernels_far.hip", "k_far": "kernels_far.hip", "k_far_side": "kernels_far.hip",
+    "k_far_finish": "kernels_far.hip", "k_kinetic": "kernels_far.hip", "k_msd": "kernels_far.hip",
     "k_near_list": "kernels_near.hip", "k_near_cells": "kernels_near.hip", "k_list_build": "kernels_near.hip",
     "k_neighbors": "kernels_near.hip",
-    "k_kdq": "kernels_md.hip", "k_bin": "kernels_md.hip", "k_scan_blocks": "kernels_md.hip",
-    "k_scan_apply": "kernels_md.hip", "k_cell_scatter": "kernels_md.hip", "k_sort_gather": "kernels_md.hip",
-    "k_kinetic": "kernels_md.hip", "k_msd": "kernels_md.hip", "k_fill_i32": "kernels_md.hip",
+    "k_kdq": "kernels_md.hip", "k_bin": "kernels_md.hip", "k_scan_one": "kernels_md.hip",
+    "k_scan_blocks": "kernels_md.hip", "k_scan_apply": "kernels_md.hip", "k_cell_scatter": "kernels_md.hip",
+    "k_sort_gather": "kernels_md.hip", "k_resort_one": "kernels_md.hip", "k_rho_build": "kernels_md.hip",
+    "k_invert_ids": "kernels_md.hip", "k_gather_forces": "kernels_md.hip", "k_fill_i32": "kernels_md.hip",
+    "k_rows_finite": "kernels_io.hip", "k_rows_in": "kernels_io.hip", "k_rows_out": "kernels_io.hip",
+    "k_forces_out": "kernels_io.hip", "k_status": "kernels_io.hip", "k_kin_items": "kernels_io.hip",
+    "k_kin_sum": "kernels_io.hip",
     "k_refill": "kernels_sample.hip", "k_sf_partial": "structure_factor.hip", "k_sf_reduce": "structure_factor.hip",
     "k_probe": "probe_rates.hip",
 }
@@ -57,14 +62,16 @@ KERNEL_FILES = {
 
 def kernel_sha16(kernel: str):
     """First 16 hex digits of the hash of the file that defines `kernel`
-    (short name, template arguments allowed) and the shared headers; None
-    for kernels outside the library."""
+    (short name, template arguments allowed) and every header beside it (the
+    bodies that several files share stand there); None for kernels outside the
+    library."""
     base = kernel.split("<")[0]
     src = KERNEL_FILES.get(base)
     if src is None:
         return None
     h = hashlib.sha256()
-    for name in (src, "rbsog_internal.h", "rbsog_math.h"):
+    headers = sorted(os.path.basename(p) for p in glob.glob(os.path.join(HERE, "csrc", "*.h")))
+    for name in (src, *headers):
         with open(os.path.join(HERE, "csrc", name), "rb") as f:
             h.update(name.encode())
             h.update(f.read())
