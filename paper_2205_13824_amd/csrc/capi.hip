@@ -1156,6 +1156,7 @@ bool poly_form(const SysHost &h, double tol, Co &co) {
             std::copy(t2, t2 + NP + 1, t1);
         }
         for (int k = 0; k < NP; ++k) (which ? co.pp : co.gp)[k] = (R)p[k];
+        if (which) co.pp_lo = (R)(p[0] - (long double)co.pp[0]);
         ok = ok && cut <= tol * p[0];
     }
     return ok;

@@ -926,11 +926,15 @@ template <bool F64, int FORM, bool WE>
 struct PairConst {
     using R = typename std::conditional<F64, double, float>::type;
     static constexpr int NP = (F64 ? kPolyDeg64 : kPolyDeg32) + 1;
-    R zs, gp[FORM == kFormPoly ? NP : 1], pp[FORM == kFormPoly && WE ? NP : 1];
+    R zs, gp[FORM == kFormPoly ? NP : 1], pp[FORM == kFormPoly && WE ? NP : 1], pp_lo;
     __device__ __forceinline__ void load(typename CoefOf<F64>::type *co) {
         if constexpr (FORM == kFormPoly) {
             zs = co->zs;
             asm volatile("" : "+s"(zs));
+            if constexpr (WE) {
+                pp_lo = co->pp_lo;
+                asm volatile("" : "+s"(pp_lo));
+            }
 #pragma unroll
             for (int k = 0; k < NP; ++k) {
                 gp[k] = co->gp[k];
@@ -988,19 +992,21 @@ __device__ __forceinline__ void pair_kernel(const PairConst<F64, FORM, WE> &pc, 
         if constexpr (F64) rinv = rsqrt64(x);
         else rinv = __builtin_amdgcn_rsqf(x);
         if constexpr (FORM == kFormPoly) {
-            // the constants are taken from 1/r^3 and 1/r first, which loses
-            // nothing where the sum is close to them
             constexpr int NP = PairConst<F64, FORM, WE>::NP;
             const R z = f(x, pc.zs, (R)1);
             gs = pc.gp[NP - 1];
 #pragma unroll
-            for (int k = NP - 2; k >= 1; --k) gs = f(gs, z, pc.gp[k]);
-            gk = f(-gs, z, f(rinv, rinv * rinv, -pc.gp[0]));
+            for (int k = NP - 2; k >= 0; --k) gs = f(gs, z, pc.gp[k]);
+            // (one rounding of the size of 1/r^3, where pairs are close)
+            gk = f(rinv, rinv * rinv, -gs);
             if constexpr (WE) {
                 ph = pc.pp[NP - 1];
 #pragma unroll
                 for (int k = NP - 2; k >= 1; --k) ph = f(ph, z, pc.pp[k]);
-                hk = f(-ph, z, rinv - pc.pp[0]);
+                // both parts of the constant from 1/r first, which loses nothing
+                // where the sum is close to it: the potentials are added up over
+                // all pairs, and a constant's rounding would be too
+                hk = f(-ph, z, (rinv - pc.pp[0]) - pc.pp_lo);
             }
         } else {
             constexpr int NT = (F64 ? kTailDeg64 : kTailDeg32) + 1;

@@ -79,9 +79,9 @@ constexpr int kMaxExp = 24;  // narrow Gaussians per split (more is rejected)
 // towards r_c, where the sum comes close to 1/r and 1/r^3 and its rounding counts
 // most, z goes to 0 and the leading powers carry one sign, so that little more than
 // the constant's rounding remains.  (Powers of 2 x/r_c^2 - 1 cancel there: rounding
-// of the sum in units of 2^-24 of 1/r^3, relative RMS over r_c/10 to r_c, row 2, r_c
-// 10 | 3.5: the exponentials 0.70 | 0.70, those powers 1.69 | 0.81, these 0.64 | 0.60.
-// FP32C needs degree 11: at 10 the terms left out are as large as the rounding.)
+// of the sum in units of 2^-24 of 1/r^3, RMS over r_c/10 to r_c, row 2, r_c 10 | 3.5:
+// the exponentials 0.70 | 0.70, those powers 1.69 | 0.81, these 0.64 | 0.60.  FP32C
+// needs degree 11: at 10 the terms left out are as large as the rounding.)
 constexpr int kPolyDeg64 = 18;
 constexpr int kPolyDeg32 = 11;
 constexpr double kPolyTol64 = 1e-16;
@@ -98,7 +98,8 @@ struct SplitCoef {
     int32_t poly;   // the polynomial form holds
     R zs;           // -1 / r_c^2: z = 1 + zs x
     R gp[NP];       // sum_l 2 omega_l/s_l^2 e^{-x/s_l^2} = sum_k gp[k] z^k
-    R pp[NP];       // sum_l omega_l e^{-x/s_l^2} = sum_k pp[k] z^k
+    R pp[NP];       // sum_l omega_l e^{-x/s_l^2} = sum_k pp[k] z^k + pp_lo
+    R pp_lo;        // what rounding leaves of the constant
 };
 using SplitCoef64 = SplitCoef<double, kTailDeg64 + 1, kPolyDeg64 + 1>;
 using SplitCoef32 = SplitCoef<float, kTailDeg32 + 1, kPolyDeg32 + 1>;
