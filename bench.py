@@ -193,17 +193,24 @@ def traffic_table(workload):
 
 def traffic_of(tab, key, fp64):
     """HBM bytes per launch of the kernel the profile steps time for `key`:
-    the first template argument is the precision, and the variant whose
-    remaining flags are all false is the one timed (the far kernel of the
-    single profiled steps does not open the next step; the near list pass
-    records no pairs and sums no energies there)."""
+    the first template argument is the precision; of the variants, the single
+    profiled steps launch the far kernel that does not open the next step
+    (second argument 0) and the list pass that sums energies and records no
+    pairs (fourth and fifth)."""
     want = f"{KERNEL_NAMES[key]}<{'true' if fp64 else 'false'}"
     cands = [k for k in tab if k == want + ">" or k.startswith(want + ",")]
-    plain = [k for k in cands if all(x.strip() == "false" for x in k[len(want) + 1:-1].split(",") if x.strip())]
-    pick = plain[0] if plain else (cands[0] if cands else None)
-    if pick is None:
+    if not cands:
         return None
-    rd, wr = tab[pick]
+
+    def timed(k):
+        args = [x.strip() for x in k[k.index("<") + 1:-1].split(",")]
+        if key == "far":
+            return args[1] == "0"
+        if key == "near":
+            return args[3:5] == ["true", "false"]
+        return True
+
+    rd, wr = tab[next((k for k in cands if timed(k)), cands[0])]
     return rd + wr
 
 

@@ -11,27 +11,29 @@
 // evaluated are exactly those within r_c.
 //
 // Build: work items are 64 consecutive particles (homes) of one system in
-// cell order, one wave per item.  The candidates of a home cell are the
-// particles of its 27 (or fewer) neighbouring cells (cells are at least
+// cell order, one block of four waves per item, a quarter of the homes each.  The
+// candidates of a home cell are the particles of its 27 (or fewer) neighbouring cells (cells are at least
 // r_c (1 + skin) wide); the three cells of a row are contiguous in cell order,
 // so they are up to 18 contiguous ranges of the sorted arrays.  The wave holds
 // candidates on its lanes and tests every (home, candidate) pair with the
 // home broadcast; accepted pairs are compacted with a ballot into an LDS ring
-// and written out 64 at a time.  The list of item b is the entries
-// [b icap, b icap + count) of the pair array.
+// and appended to their homes' lists 64 at a time, in the item's block of icap
+// entries.
 //
-// Evaluation: one block of four waves per item; the waves take turns over the
-// item's pairs, 64 per pass, sum each home's forces with a segmented scan
-// across the wave and keep them in per-wave LDS slots, added in a fixed order
-// at the end, so results are the same on every run.  Blocks are dealt to the
-// 8 XCDs so that each XCD sweeps one contiguous slab of items and keeps its
-// candidates in its own L2.
+// Evaluation (the list pass): one block per item, a home per lane (short lists)
+// or a home per wave (long ones), each home's pairs summed in one order, so results
+// are the same on every run.  Where every step builds, the fused cell kernel
+// evaluates pairs from its ring instead.  Blocks are dealt to the 8 XCDs so that
+// each XCD sweeps one contiguous slab of items and keeps its candidates in its own
+// L2.
 //
-// Gaussians with r_c^2/s_l^2 <= kTailTau are summed as one polynomial in r^2
-// (their Taylor series, truncated below rounding), the narrow ones with an
-// exponential each.  Pair inclusion follows the fixed-point rule of rbsog.h:
-// an FP32 test decides every pair outside a narrow band around r_c, the exact
-// FP64 rule decides the rest, so the pairs are bit-exact in both precisions.
+// Gaussians: the whole sum as one polynomial where it converges fast enough; else
+// those with r_c^2/s_l^2 <= kTailTau as one polynomial in r^2 (their Taylor
+// series, truncated below rounding) and the narrow ones with an exponential each.
+// Pair inclusion follows the fixed-point rule of rbsog.h: a fast test (FP32 on the
+// fixed-point differences; FP64 coordinates in the FP64 list pass) decides every
+// pair outside a narrow band around r_c, the exact FP64 rule decides the rest, so
+// the pairs are bit-exact in both precisions.
 #include <algorithm>
 #include <type_traits>
 
@@ -1156,12 +1158,12 @@ __device__ __forceinline__ R wave_total(R v) {
 // sums its home's pairs in registers, and the four waves' sums are added in a
 // fixed order.  Home-major blocks (HM): see below.
 //
-// A pass over 64 pairs takes about 45 vector instructions and two dependent
+// A pass over 64 pairs takes about 40 vector instructions and two dependent
 // loads (the list entries, then the candidates' records), so the loop keeps
 // list entries kE and records kG passes ahead and looks at an entry only when
 // its record is requested: one entry and one record ahead, with the entry
 // tested in the pass of its load, each pass waited for a load.
-// 300,000 ions FP32C 20 -> 16 us, FP64 67 -> 38; 2,097,152 ions FP32C (beside
+// 300,000 ions FP32C 20 -> 17 us, FP64 67 -> 28; 2,097,152 ions FP32C (beside
 // the structure factor) 219 -> 163; water-shaped 331,776 sites FP32C 429 ->
 // 336, 98,304 sites FP64 340 -> 178.
 constexpr int kE = 4;
@@ -1172,9 +1174,10 @@ static_assert(kG<false> < kE && kE % kG<false> == 0, "records are requested from
 // Waves of a home-major block: 16 (FP64 8, whose 80 registers leave a SIMD six
 // waves), so that the waves of a CU work on few places of the box and the
 // gathers of homes that share their candidates meet in L1.  331,776
-// water-shaped sites FP32C: 4 waves 407 us (34 million L1 misses, 11 TB/s
-// from L2), 8 waves 375, 16 waves 336, 16 waves on two items 366; 98,304
-// sites FP64: 4 waves 192, 8 waves 178, 16 waves 188.
+// water-shaped sites FP32C: 4 waves 407 us (39.5 million reads that L1 passes on
+// to L2, of 104 million accesses), 8 waves 375, 16 waves 336 (18.4 million), 16
+// waves on two items 366; 98,304 sites FP64: 4 waves 192 (15.4 million), 8 waves
+// 178 (12.3 million), 16 waves 188.
 template <bool F64>
 constexpr int kHmWaves = F64 ? 8 : 16;
 

@@ -294,7 +294,7 @@ struct EvalArgs {
     int32_t far_span;      // most such groups of a far item
     int32_t advance;       // 1: the evaluation's last far kernel moves the sequence cursors on
     int32_t zmode;         // 1: some system has a zero-frequency mode term
-    // nonzero (plain velocity Verlet on a kept near list): the far kernel
+    // nonzero (velocity Verlet, plain or Langevin, on a kept near list): the far kernel
     // also opens the next step (its half kick with the same force, its drift
     // and quantisation, its displacement check), the near list pass clears
     // the rebuild flag in its place, and the next step starts with its
