@@ -1,13 +1,23 @@
 """Launch shapes of the context-free structure factor (host code only): what every
 plan has to keep, and that counts of k tiles just past a block's 16 waves do not
 leave most of a second group's waves idle."""
+import os
+
 import numpy as np
 import pytest
 
+from paper_2205_13824_amd import build as B
 from paper_2205_13824_amd import rbsog as R
 
 SIZES = [1, 63, 64, 65, 1000, 10002, 200_000, 1_999_998, 2 ** 31 - 1]
 VECTORS = [1, 64, 65, 1000, 1024, 1025, 1100, 1500, 2047, 2049, 4000, 65537, 2 ** 20, 65535 * 256]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def lib():
+    if not os.path.exists(R.LIB_PATH):
+        B.build()
+    return R.lib()
 
 
 @pytest.mark.parametrize("prec", [R.RBSOG_FP64, R.RBSOG_FP32C])
