@@ -1525,12 +1525,22 @@ void build_work(rbsog_ctx *c, const Tune &t, std::vector<ListItem> &near, std::v
 // 115, water-shaped 331,776 sites 459 | 447 (384 chunks: 85, 1,306, 114, 450; 496: 89,
 // 1,266, 118, 460).  On one stream nothing is beside them: 8,000,000 ions x 1000 4,545
 // | 4,660, 5,000,000 x 900 FP64 6,980 | 7,180, 150,000 x 200 63.5 | 65.8.
+// Every system's last chunk is its own; a batch that this takes past 512 would start a
+// third block on some CUs and has 480 of the mean size (20 systems of 149,910 ions in
+// all x 120 FP32C, 37 steps: 521 | 489 chunks 4,770 | 4,430 us; 40 of 178,472 x 103
+// FP64: 533 | 503 5,590 | 5,270).
 constexpr int64_t kRhoChunksBeside = 480, kRhoChunksAlone = 512;
 Tune default_tune(const rbsog_ctx *c) {
     Tune t;
-    const int64_t chunks =
-        c->use_side(c->skin > 0.0, c->sys[0].zmode != 0) ? kRhoChunksBeside : kRhoChunksAlone;
-    t.rho_chunk = (int32_t)std::max<int64_t>(256, (c->N + chunks - 1) / chunks);
+    auto chunk_of = [&](int64_t chunks) { return std::max<int64_t>(256, (c->N + chunks - 1) / chunks); };
+    int64_t chunk = chunk_of(kRhoChunksBeside);
+    if (!c->use_side(c->skin > 0.0, c->sys[0].zmode != 0)) {
+        const int64_t alone = chunk_of(kRhoChunksAlone);
+        int64_t total = 0;
+        for (const SysHost &h : c->sys) total += (h.n + alone - 1) / alone;
+        if (total <= kRhoChunksAlone) chunk = alone;
+    }
+    t.rho_chunk = (int32_t)chunk;
     t.far_block = 256;
     return t;
 }

@@ -86,6 +86,29 @@ def test_chunks_of_the_structure_factor(prec, n, P, skin, chunks):
     b.close()
 
 
+# ragged systems of a batch stay within the 512 blocks that the device holds at once
+# (their last chunks would make more of 512 of the mean size), equal ones that fit keep
+# the 512
+RAGGED = [500 + 2 * ((37 * i * i) % 3251) for i in range(40)]
+
+
+@pytest.mark.parametrize("prec", [F64, F32C])
+@pytest.mark.parametrize("sizes,chunks", [(RAGGED, 480), ([51200] * 4, 512), ([50200, 51000, 51800, 51800], 480)])
+def test_chunks_of_a_batch(prec, sizes, chunks):
+    b = _batch(sizes, 66, prec)
+    chunk = R.rbsog_info(b.ctx)["rho_chunk"]
+    assert chunk == -(-sum(sizes) // chunks)
+    assert sum(-(-n // chunk) for n in sizes) <= 512
+    b.close()
+
+
+@pytest.mark.parametrize("sizes", [RAGGED])
+def test_k_tiles_of_a_batch(sizes):
+    b = _batch(sizes, 103, F64)
+    assert R.rbsog_info(b.ctx)["rho_ktile"] == 2
+    b.close()
+
+
 # FP64 blocks of fewer k tiles where that lightens the fullest CU, not where every step
 # builds: 391 chunks of 4 tiles make 782 blocks of 2 or 1,564 of 1
 @pytest.mark.parametrize("prec,n,P,skin,ktile", [(F64, 100000, 200, None, 1), (F64, 100000, 200, 0.0, 4),
